@@ -58,6 +58,9 @@ def compile_host(verbose=False):
 
 def prebuild_mechanisms(builds=None):
     """Compile the device code of the committed mechanisms into the cache."""
+    # torch brings its own hipRTC; loaded first it is the compiler a program
+    # that imports torch gets, and the cache key names the compiler
+    import torch  # noqa: F401
     sys.path.insert(0, str(ROOT))
     from paper_2508_16105_amd import _lib
     mdir = ROOT / "workloads" / "mech"

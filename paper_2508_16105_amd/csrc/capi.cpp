@@ -24,15 +24,17 @@
 using namespace chemmi;
 
 namespace {
-// a cell's state, Jacobian and LU factors live in one lane's registers
 // Mechanisms with up to kLaneSpecies species run one cell per lane (the
 // cell's Jacobian and LU factors in one lane's registers); larger ones run
-// wave-cooperatively.  At 13 species the lane form spills registers but keeps
-// 64 cells in flight per SIMD against 8, and wins on large fields (28 M cells:
-// 7.2 s against 9.4 s); the wave-cooperative form has the shorter latency per
-// cell.  From 14 species on, the lane form's spills grow steeply and the
-// wave-cooperative form is 3-4x faster even on a 65 k-cell field (14, 15, 16
-// and 18 species measured), so 13 is the default limit.
+// wave-cooperatively (16 lanes a cell).  At 13 species the two are close: the
+// lane form spills but keeps 64 cells in flight per SIMD against 8 and gives
+// the higher rate when work abounds (50,000 fixed steps: 124 us against 245),
+// the wave-cooperative form takes a third of the time per substep of a cell
+// and wins where the costliest cell is what is waited for (20,000-cell field:
+// 40 ms against 138; 1M cells: 242 against 303).  From 14 species on, the lane
+// form's spills grow steeply (14, 15, 16 and 18 species measured at 3-4 times
+// the time of the wave-cooperative form of that day, which has become 2-3
+// times faster), so 13 is the default limit.
 // CHEM_LANE_MAX_SPECIES overrides the choice at load time (the lane form is
 // built for at most kMaxLaneSpecies species).
 constexpr int kLaneSpecies = 13;
@@ -278,7 +280,10 @@ int chem_eval_source(const chem_mechanism* mc, int64_t ncell, const double* T, c
     if (int rc = device_state(m, (hipStream_t)stream, &d)) return rc;
     EvalArgs a{d->par, T, p, Y, (long)ncell, f, J};
     if (m->wide)
-        return launch_1d(d->f_eval, ncell * m->layout.G, 64, &a, sizeof a, (hipStream_t)stream, "chem_eval",
+        return launch_1d(d->f_eval,
+                         std::min<int64_t>(m->layout.lanes(ncell),
+                                           (int64_t)d->num_cu * m->layout.blocks_per_cu() * m->layout.block()),
+                         m->layout.block(), &a, sizeof a, (hipStream_t)stream, "chem_eval",
                          m->layout.lds_bytes());
     return launch_1d(d->f_eval, ncell, 64, &a, sizeof a, (hipStream_t)stream, "chem_eval");
 }
@@ -301,7 +306,7 @@ int chem_step_fixed(const chem_mechanism* mc, int64_t ncell, const double* T, co
     if (int rc = device_state(m, (hipStream_t)stream, &d)) return rc;
     FixedStepArgs a{d->par, T, p, Y, (long)ncell, h, ynew, errnorm, rtol, atol, ok};
     if (m->wide)
-        return launch_1d(d->f_fixed, ncell * m->layout.G, 64, &a, sizeof a, (hipStream_t)stream, "chem_fixed_step",
+        return launch_1d(d->f_fixed, m->layout.lanes(ncell), m->layout.block(), &a, sizeof a, (hipStream_t)stream, "chem_fixed_step",
                          m->layout.lds_bytes());
     return launch_1d(d->f_fixed, ncell, 64, &a, sizeof a, (hipStream_t)stream, "chem_fixed_step",
                      d->stage_lds(64));

@@ -794,51 +794,83 @@ struct Emitter {
 
 std::string generate_mechanism_source(const MechanismData& m) { return Emitter(m).run(); }
 
+namespace {
+
+// number of species slots of a side (a coefficient of 2 takes two slots)
+int molecularity(const std::vector<Term>& side)
+{
+    int n = 0;
+    for (const auto& t : side) n += t.nu;
+    return n;
+}
+
+// species whose third-body efficiency in r is not 1
+std::vector<int> partners(const ReactionData& r)
+{
+    std::vector<int> p;
+    for (size_t k = 0; k < r.eff.size(); ++k)
+        if (r.eff[k] != 1.0) p.push_back((int)k);
+    return p;
+}
+
+bool has_third_body(RxnKind k) { return k == RxnKind::ThirdBody || is_falloff(k); }
+
+}  // namespace
+
 WideLayout wide_layout(const MechanismData& m)
 {
     WideLayout w;
-    const int ns = m.ns(), nr = m.nr(), n = ns + 1;
-    if (n > 64) {
-        w.G = 0;
-        return w;
-    }
-    w.G = 16;
-    while (w.G < n) w.G *= 2;
-    w.maxt = 1;
-    for (const auto& r : m.reactions) w.maxt = std::max<int>(w.maxt, (int)std::max(r.reac.size(), r.prod.size()));
-    if (w.maxt > 3) {
-        w.G = 0;
-        return w;
-    }
-    for (const auto& r : m.reactions) {   // the packed reaction table's field widths
+    const int ns = m.ns(), nr = m.nr();
+    w.G = 0;
+    int maxt = 1, n_eff = 0, n_plog = 0;
+    for (const auto& r : m.reactions) {
+        maxt = std::max<int>(maxt, (int)std::max(r.reac.size(), r.prod.size()));
         for (const auto* side : {&r.reac, &r.prod})
             for (const auto& t : *side)
-                if (t.nu > 3) w.G = 0;
-        if (r.dnu < -4 || r.dnu > 3) w.G = 0;
-    }
-    int n_eff = 0, n_plog = 0;
-    for (const auto& r : m.reactions) {
+                if (t.nu > 3) return w;
+        if (r.dnu < -4 || r.dnu > 3) return w;   // the packed reaction words' field widths
         if (r.kind == RxnKind::Plog) ++n_plog;
         else if (r.kind != RxnKind::Elementary) ++n_eff;
     }
-    if (n_eff > 511 || n_plog > 511 || nr > 65535 || w.G == 0) {
-        w.G = 0;
-        return w;
+    if (ns + 1 > 64 || maxt > 3 || n_eff > 511 || n_plog > 511 || nr > 65535) return w;
+    w.G = 16;
+    const std::vector<bool> inert = inert_species(m);
+    w.na = (int)std::count(inert.begin(), inert.end(), false);
+    const int ni = ns - w.na, nact = w.na + 1;
+    w.r = (nact + 15) / 16;
+    w.ri = (ni + 1 + 15) / 16;
+    w.molr = w.molp = 1;
+    for (const auto& r : m.reactions) {
+        w.molr = std::max(w.molr, molecularity(r.reac));
+        w.molp = std::max(w.molp, molecularity(r.prod));
+        if (has_third_body(r.kind)) {
+            ++w.ntb;
+            w.maxp = std::max<int>(w.maxp, (int)partners(r).size());
+        }
     }
-    w.nslot = 2 * w.maxt;
-    w.pw = w.nslot + 2;
-    w.jw = (ns + 1) % 2 ? ns + 1 : ns + 2;
-    w.l_y = 0;
-    w.l_c = w.l_y + n;
-    w.l_g = w.l_c + ns;
-    w.l_h = w.l_g + ns;
-    w.l_q = w.l_h + ns;
-    w.l_p = w.l_q + nr;
-    w.l_j = w.l_p + nr * w.pw;
-    w.l_t0 = w.l_j + ns * w.jw;
-    w.l_w = w.l_t0 + ns;
-    w.lds_cell = w.l_w + n;
-    w.adj_lds_cell = 2 * w.lds_cell + 2 * n;
+    const SpeciesKc kc = plan_species_kc(m);
+    for (int j = 0; j < nr; ++j)
+        if (m.reactions[j].reversible && !kc.product_form[j]) w.lnkc = true;
+    // the scratch of a cell, as the device code lays it out
+    const int sp = ns + 1, nrw = nr + 1, mol = std::max(w.molr, w.molp);
+    const int l_a = (w.lnkc ? 5 : 4) * sp;
+    const int fwd = l_a + std::max(16 * w.r, std::max(5, w.molr + w.molp) * nrw + w.ntb * (1 + w.maxp));
+    const int rev = 2 * (l_a + 2 * sp + 2 * mol * nrw + 2 * (w.ntb * w.maxp + 1));    // dual numbers
+    // cells 16 doubles apart modulo the 64 banks, so two cells' rows do not collide
+    auto pad = [](int n) { return n + (48 - n % 32) % 32; };
+    w.lds_cell = pad(fwd);
+    w.adj_lds_cell = pad(std::max(fwd, rev));
+    const int words = (w.molr + 3) / 4 + (w.molp + 3) / 4 + 1, npt = 16 * (w.r + w.ri);
+    w.table = 3 * nr + 38 * npt + (11 + w.maxp) * w.ntb + (words * nr + w.maxp * w.ntb + 1) / 2;
+    // a workgroup is four waves of four cells that share the tables; fewer waves,
+    // then fewer cells a wave, where that does not fit the 160 KB of LDS
+    auto shape = [&](int cell, int& wpb, int& cpw) {
+        wpb = cpw = 4;
+        while (wpb * cpw > 1 && (size_t)(w.table + wpb * cpw * cell) * sizeof(double) > 160 * 1024)
+            (wpb > 1 ? wpb : cpw) /= 2;
+    };
+    shape(w.lds_cell, w.wpb, w.cpw);
+    shape(w.adj_lds_cell, w.awpb, w.acpw);
     return w;
 }
 
@@ -846,208 +878,341 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
 {
     Emitter e(m);
     std::ostringstream& o = e.o;
-    const int ns = m.ns(), nr = m.nr();
+    const int ns = m.ns(), nr = m.nr(), na = w.na, ni = ns - na, nact = na + 1;
+    const int npt = 16 * (w.r + w.ri);
+    // position order of the species: changed by some reaction, then the others
+    std::vector<int> ord, inv(ns);
+    for (int pass = 0; pass < 2; ++pass)
+        for (int k = 0; k < ns; ++k)
+            if (e.inert[k] == (pass == 1)) ord.push_back(k);
+    for (int q = 0; q < ns; ++q) inv[ord[q]] = q;
+    // position -> species (-1: T's position or none)
+    std::vector<int> pspec(npt, -1);
+    for (int q = 0; q < na; ++q) pspec[1 + q] = ord[q];
+    for (int q = 0; q < ni; ++q) pspec[16 * w.r + q] = ord[na + q];
+    int maxdnu = 0;
+    bool sri = false, irrev = false;
+    for (const auto& r : m.reactions) {
+        if (r.reversible) maxdnu = std::max(maxdnu, std::abs(r.dnu));
+        sri = sri || r.kind == RxnKind::Sri;
+        irrev = irrev || !r.reversible;
+    }
+    // reactions in evaluation order: those with extra terms first (PLOG, SRI,
+    // Troe, Lindemann, third body), so that as few rounds of 16 lanes as can be
+    // hold any, then the elementary ones
+    std::vector<int> order;
+    for (int kind = 5; kind >= 0; --kind)
+        for (int j = 0; j < nr; ++j)
+            if ((int)m.reactions[j].kind == kind) order.push_back(j);
+    int nfull = 0;
+    for (const auto& r : m.reactions) nfull += r.kind != RxnKind::Elementary;
+    const int full_rounds = (nfull + 15) / 16;
+    const bool has_plog = std::any_of(m.reactions.begin(), m.reactions.end(),
+                                      [](const ReactionData& r) { return r.kind == RxnKind::Plog; });
+    auto yn = [](bool b) { return b ? "true" : "false"; };
     o << "// generated mechanism tables (wave-cooperative form): " << m.name << " (" << ns << " species, " << nr
       << " reactions)\n"
       << "namespace mech {\n"
       << "constexpr int NS = " << ns << ";\n"
       << "constexpr int NR = " << nr << ";\n"
       << "constexpr int N = NS + 1;\n"
-      << "constexpr int G = " << w.G << ";            // lanes per cell\n"
-      << "constexpr int MAXT = " << w.maxt << ";         // most terms on a reaction side\n"
-      << "constexpr int NSLOT = " << w.nslot << ", PW = " << w.pw << ", JW = " << w.jw << ";\n"
-      << "constexpr int L_Y = " << w.l_y << ", L_C = " << w.l_c << ", L_G = " << w.l_g << ", L_H = " << w.l_h
-      << ", L_Q = " << w.l_q << ", L_P = " << w.l_p << ", L_J = " << w.l_j << ", L_T0 = " << w.l_t0
-      << ", L_W = " << w.l_w << ";\n"
-      << "constexpr int LDS_CELL = " << w.lds_cell << ";  // doubles of LDS scratch per cell\n"
-      << "constexpr int ADJ_LDS_CELL = " << w.adj_lds_cell << ";  // per cell in the adjoint\n"
+      << "constexpr int NA = " << na << ", NI = " << ni << ", NACT = " << nact
+      << ";   // species some reaction changes, the others; unknowns of a step\n"
+      << "constexpr int R = " << w.r << ", RI = " << w.ri << ", NPT = " << npt << ";   // positions a lane, in all\n"
+      << "constexpr int MOLR = " << w.molr << ", MOLP = " << w.molp << ", MAXDNU = " << maxdnu << ";\n"
+      << "constexpr int NTB = " << w.ntb << ", MAXP = " << w.maxp << ";\n"
+      << "constexpr int FULL_ROUNDS = " << full_rounds << ";   // leading rounds with slots other than elementary\n"
+      << "constexpr int LDS_CELL = " << w.lds_cell << ", ADJ_LDS_CELL = " << w.adj_lds_cell
+      << ";   // doubles of scratch per cell\n"
+      << "constexpr int CPW = " << w.cpw << ", ACPW = " << w.acpw << ";   // cells per wave\n"
+      << "constexpr int WPS = " << w.waves_per_simd() << ";   // waves per SIMD the registers are shared by\n"
       << "constexpr double RU = " << lit(kRu) << ";\n"
+      << "constexpr double RU_PATM = " << lit(kRu / kPatm) << ", PATM_RU = " << lit(kPatm / kRu) << ";\n"
       << "constexpr double LN_PATM_R = " << lit(std::log(kPatm / kRu)) << ";\n"
-      << "constexpr double LN10 = " << lit(std::log(10.0)) << ";\n";
+      << "constexpr double LN10 = " << lit(std::log(10.0)) << ";\n"
+      << "// reaction forms present (the kernels leave out the code of the absent ones)\n"
+         "constexpr bool HAS_PLOG = " << yn(has_plog) << ", HAS_SRI = " << yn(sri) << ", HAS_IRREV = " << yn(irrev)
+      << ", HAS_LNKC = " << yn(w.lnkc) << ";\n";
     e.thermo_table();
-    o << "__constant__ double TMID[NS] = {";
-    for (int k = 0; k < ns; ++k) o << lit(m.species[k].tmid) << (k + 1 < ns ? ", " : "};\n");
-    // reactions in evaluation order: grouped by kind so a round of lanes mostly
-    // takes one branch
-    std::vector<int> order;
-    for (int kind = 0; kind < 6; ++kind)
-        for (int j = 0; j < nr; ++j)
-            if ((int)m.reactions[j].kind == kind) order.push_back(j);
-    std::vector<int> slot_of(nr);
-    for (int s = 0; s < nr; ++s) slot_of[order[s]] = s;
-    // per slot: its EFF row (third body and falloff) or its PLOG table (PLOG)
-    std::vector<int> effrow(nr, -1);
-    int neff = 0, nplog = 0;
-    for (int s = 0; s < nr; ++s) {
-        const RxnKind k = m.reactions[order[s]].kind;
-        if (k == RxnKind::Plog) effrow[s] = nplog++;
-        else if (k != RxnKind::Elementary) effrow[s] = neff++;
-    }
-    auto ints = [&](const char* name, const std::vector<int>& v) {
-        o << "__constant__ int " << name << "[" << std::max<size_t>(v.size(), 1) << "] = {";
+    auto ints = [&](const std::string& decl, const std::vector<int>& v) {
+        o << decl << "[" << std::max<size_t>(v.size(), 1) << "] = {";
         if (v.empty()) o << "0";
         for (size_t i = 0; i < v.size(); ++i) o << v[i] << (i + 1 < v.size() ? ", " : "");
         o << "};\n";
     };
-    auto dbls = [&](const char* name, const std::vector<double>& v) {
-        o << "__constant__ double " << name << "[" << std::max<size_t>(v.size(), 1) << "] = {";
+    auto dbls = [&](const std::string& decl, const std::vector<double>& v) {
+        o << decl << "[" << std::max<size_t>(v.size(), 1) << "] = {";
         if (v.empty()) o << "0.0";
         for (size_t i = 0; i < v.size(); ++i) o << lit(v[i]) << (i + 1 < v.size() ? ", " : "");
         o << "};\n";
     };
-    // per slot: original index; species of the MAXT reactant then MAXT product
-    // slots (-1: unused)
-    std::vector<int> orig, sp;
-    std::vector<double> low, troe, eff, plog;
+    const std::string ci = "__constant__ int ", cd = "__constant__ double ";
+    o << "// by position: species, its T_mid, W and 1/W (0 where none sits); the NASA-7\n"
+         "// rows, coefficient by coefficient, low range then high, so that the lanes of\n"
+         "// a group read consecutive words\n";
+    ints(ci + "PSPEC", pspec);
+    std::vector<double> tm, pw(2 * npt, 0.0), th;
+    for (int q = 0; q < npt; ++q) {
+        const int k = pspec[q];
+        tm.push_back(k >= 0 ? m.species[k].tmid : 1000.0);
+        if (k >= 0) {
+            pw[q] = m.species[k].W;
+            pw[npt + q] = 1.0 / m.species[k].W;
+        }
+    }
+    for (int c = 0; c < 19; ++c)
+        for (int half = 0; half < 2; ++half)
+            for (int q = 0; q < npt; ++q) {
+                const int k = pspec[q];
+                if (k < 0) {
+                    th.push_back(0.0);
+                    continue;
+                }
+                const double* a = half == 0 ? m.species[k].lo : m.species[k].hi;
+                const double v[19] = {a[0], a[1], a[2], a[3], a[4], a[1] / 2, a[2] / 3, a[3] / 4, a[4] / 5,
+                                      a[5], a[1] / 2, a[2] / 6, a[3] / 12, a[4] / 20, a[6] - a[0],
+                                      a[1], 2 * a[2], 3 * a[3], 4 * a[4]};
+                th.push_back(v[c]);
+            }
+    dbls(cd + "PTMID", tm);
+    dbls(cd + "PW", pw);
+    dbls(cd + "TH", th);
+    o << "// species in position order: 1/W, original index\n";
+    std::vector<double> iwm;
+    for (int q = 0; q < ns; ++q) iwm.push_back(1.0 / m.species[ord[q]].W);
+    dbls(cd + "IWM", iwm);
+    ints(ci + "COLSPEC", ord);
+    // per slot: words of reactant, then product species (position order, a byte
+    // each, ns: none), then kind | irreversible << 3 | product form of K_c << 4 |
+    // (dnu + 4) << 5 | reactant slots << 8 | product slots << 12 | row << 16
+    std::vector<std::vector<int>> rs(nr), ps(nr);
+    std::vector<int> row(nr, 0);
+    std::vector<int> tb;                    // slots with a third body, in order
+    std::vector<double> low, troe, plog;
     std::vector<int> plog_off(1, 0);
     for (int s = 0; s < nr; ++s) {
         const auto& r = m.reactions[order[s]];
-        orig.push_back(order[s]);
-        for (int t = 0; t < w.maxt; ++t) sp.push_back(t < (int)r.reac.size() ? r.reac[t].sp : -1);
-        for (int t = 0; t < w.maxt; ++t) sp.push_back(t < (int)r.prod.size() ? r.prod[t].sp : -1);
-        low.insert(low.end(), {r.lnA0, r.b0, r.EaR0});
-        const bool tr = r.kind == RxnKind::Troe;
-        if (r.kind == RxnKind::Sri)
-            troe.insert(troe.end(), {r.sri[0], -r.sri[1], 1.0 / r.sri[2], r.sri[1], std::log(r.sri[3]), r.sri[4],
-                                     0.0, 0.0});
-        else
-            troe.insert(troe.end(), {tr ? 1.0 - r.alpha : 0.0, tr ? r.alpha : 0.0, tr ? 1.0 / r.T3 : 0.0,
-                                     tr ? 1.0 / r.T1 : 0.0, tr && r.has_T2 ? r.T2 : 0.0,
-                                     tr ? -(1.0 - r.alpha) / r.T3 : 0.0, tr ? -r.alpha / r.T1 : 0.0,
-                                     tr && r.has_T2 ? 1.0 : 0.0});
+        for (const auto& t : r.reac)
+            for (int q = 0; q < t.nu; ++q) rs[s].push_back(inv[t.sp]);
+        for (const auto& t : r.prod)
+            for (int q = 0; q < t.nu; ++q) ps[s].push_back(inv[t.sp]);
         if (r.kind == RxnKind::Plog) {
-            for (const auto& e : r.plog) plog.insert(plog.end(), {e.lnp, e.lnA, e.b, e.EaR});
+            row[s] = (int)plog_off.size() - 1;
+            for (const auto& x : r.plog) plog.insert(plog.end(), {x.lnp, x.lnA, x.b, x.EaR});
             plog_off.push_back((int)(plog.size() / 4));
-        } else if (effrow[s] >= 0) {
-            for (int k = 0; k < ns; ++k) eff.push_back(r.eff[k]);
+        } else if (has_third_body(r.kind)) {
+            row[s] = (int)tb.size();
+            tb.push_back(s);
+            low.insert(low.end(), {r.lnA0, r.b0, r.EaR0});
+            const bool tr = r.kind == RxnKind::Troe;
+            if (r.kind == RxnKind::Sri)
+                troe.insert(troe.end(), {r.sri[0], -r.sri[1], 1.0 / r.sri[2], r.sri[1], std::log(r.sri[3]), r.sri[4],
+                                         0.0, 0.0});
+            else
+                troe.insert(troe.end(), {tr ? 1.0 - r.alpha : 0.0, tr ? r.alpha : 0.0, tr ? 1.0 / r.T3 : 0.0,
+                                         tr ? 1.0 / r.T1 : 0.0, tr && r.has_T2 ? r.T2 : 0.0,
+                                         tr ? -(1.0 - r.alpha) / r.T3 : 0.0, tr ? -r.alpha / r.T1 : 0.0,
+                                         tr && r.has_T2 ? 1.0 : 0.0});
         }
     }
-    // packed per slot, for one load per reaction round: species slots (8 bits
-    // each: species index + 1 in the low 6 bits, coefficient in the top 2;
-    // 0 = unused) in two words, then kind | irreversible << 3 | (dnu + 4) << 4 |
-    // (EFF row or PLOG table + 1) << 7 | orig << 16
-    {
-        std::vector<int> pack;
-        for (int s = 0; s < nr; ++s) {
-            const auto& r = m.reactions[order[s]];
-            unsigned long long slots = 0;
-            for (int t = 0; t < 2 * w.maxt; ++t) {
-                const bool isr = t < w.maxt;
-                const auto& side = isr ? r.reac : r.prod;
-                const int q = isr ? t : t - w.maxt;
-                unsigned v = 0;
-                if (q < (int)side.size()) v = (unsigned)(side[q].sp + 1) | ((unsigned)side[q].nu << 6);
-                slots |= (unsigned long long)v << (8 * t);
+    const int wr = (w.molr + 3) / 4, wp = (w.molp + 3) / 4;
+    std::vector<int> packed((size_t)(wr + wp + 1) * nr);
+    for (int s = 0; s < nr; ++s) {
+        const auto& r = m.reactions[order[s]];
+        for (int side = 0; side < 2; ++side) {
+            const auto& v = side == 0 ? rs[s] : ps[s];
+            const int nw = side == 0 ? wr : wp;
+            for (int q = 0; q < nw; ++q) {
+                unsigned x = 0;
+                for (int b = 0; b < 4; ++b)
+                    x |= (unsigned)(4 * q + b < (int)v.size() ? v[4 * q + b] : ns) << (8 * b);
+                packed[(size_t)(side * wr + q) * nr + s] = (int)x;
             }
-            pack.push_back((int)(unsigned)(slots & 0xffffffffull));
-            pack.push_back((int)(unsigned)(slots >> 32));
-            pack.push_back((int)((unsigned)r.kind | ((r.reversible ? 0u : 1u) << 3) | ((unsigned)(r.dnu + 4) << 4) |
-                                 ((unsigned)(effrow[s] + 1) << 7) | ((unsigned)order[s] << 16)));
         }
-        o << "// per slot: species slots (two words, 8 bits each: index + 1 | nu << 6), then\n"
-             "// kind | irreversible << 3 | (dnu + 4) << 4 | (EFF row or PLOG table + 1) << 7 |\n"
-             "// original index << 16\n";
-        ints("RX_PACK", pack);
+        const bool pform = r.reversible && e.kc.product_form[order[s]];
+        packed[(size_t)(wr + wp) * nr + s] =
+            (int)((unsigned)r.kind | (r.reversible ? 0u : 8u) | (pform || !r.reversible ? 16u : 0u) |
+                  ((unsigned)(r.dnu + 4) << 5) | ((unsigned)rs[s].size() << 8) | ((unsigned)ps[s].size() << 12) |
+                  ((unsigned)row[s] << 16));
     }
-    o << "// reactions in evaluation order (slot s): original index (kind, species\n"
-         "// slots and coefficients are in RX_PACK)\n";
-    ints("RX_ORIG", orig);
-    o << "// low-pressure limit (ln A0 SI, b0, Ea0/R); Troe: 1-alpha, alpha, 1/T***,\n"
-         "// 1/T*, T**, -(1-alpha)/T***, -alpha/T*, [T** given]; SRI: a, -b, 1/c, b, ln d, e\n";
-    dbls("RX_LOW", low);
-    dbls("RX_TROE", troe);
-    {
-        bool sri = false, irrev = false;
-        for (const auto& r : m.reactions) {
-            sri = sri || r.kind == RxnKind::Sri;
-            irrev = irrev || !r.reversible;
+    o << "// reactions in evaluation order (slot s): original index; packed words\n";
+    ints(ci + "RX_ORIG", order);
+    ints(ci + "RX_WORDS", packed);
+    o << "// third-body and falloff slots, in order: low-pressure limit (ln A0 SI, b0, Ea0/R);\n"
+         "// Troe: 1-alpha, alpha, 1/T***, 1/T*, T**, -(1-alpha)/T***, -alpha/T*, [T** given];\n"
+         "// SRI: a, -b, 1/c, b, ln d, e; the collision partners of efficiency other than 1\n"
+         "// and that efficiency less 1\n";
+    auto columns = [&](const std::vector<double>& v, int n) {    // row by row -> column by column
+        std::vector<double> c;
+        for (int q = 0; q < n; ++q)
+            for (int t = 0; t < w.ntb; ++t) c.push_back(v[(size_t)t * n + q]);
+        return c;
+    };
+    dbls(cd + "RX_LOW", columns(low, 3));
+    dbls(cd + "RX_TROE", columns(troe, 8));
+    std::vector<int> tsp((size_t)w.maxp * w.ntb, ns);
+    std::vector<double> tc((size_t)w.maxp * w.ntb, 0.0);
+    for (int t = 0; t < w.ntb; ++t) {
+        const auto& r = m.reactions[order[tb[t]]];
+        const auto p = partners(r);
+        for (size_t q = 0; q < p.size(); ++q) {
+            tsp[q * w.ntb + t] = inv[p[q]];
+            tc[q * w.ntb + t] = r.eff[p[q]] - 1.0;
         }
-        o << "// reaction forms present (the kernels leave out the code of the absent ones)\n"
-             "constexpr bool HAS_PLOG = " << (nplog > 0 ? "true" : "false") << ";\n"
-             "constexpr bool HAS_SRI = " << (sri ? "true" : "false") << ";\n"
-             "constexpr bool HAS_IRREV = " << (irrev ? "true" : "false") << ";\n";
     }
+    ints(ci + "TBP_SP", tsp);
+    dbls(cd + "TBP_C", tc);
     o << "// PLOG tables: entries RX_PLOG_OFF[t] .. RX_PLOG_OFF[t+1] of (ln p, ln A SI, b, Ea/R)\n";
-    ints("RX_PLOG_OFF", plog_off);
-    dbls("RX_PLOG", plog);
-    o << "// third-body efficiencies, one dense row per non-elementary reaction\n";
-    dbls("EFF", eff);
-    // species -> reactions that change it (slot, net coefficient)
-    std::vector<int> off(1, 0), srx, snu;
-    for (int k = 0; k < ns; ++k) {
-        for (int s = 0; s < nr; ++s) {
-            const auto& r = m.reactions[order[s]];
-            int v = 0;
-            for (auto& t : r.reac) if (t.sp == k) v -= t.nu;
-            for (auto& t : r.prod) if (t.sp == k) v += t.nu;
-            if (v) {
-                srx.push_back(s);
-                snu.push_back(v);
+    ints(ci + "RX_PLOG_OFF", plog_off);
+    dbls(cd + "RX_PLOG", plog);
+
+    // Lists by position, 16 lanes side by side, each padded to the longest of
+    // its 16.  A word: byte offset from the first reaction array | coefficient
+    // << 24; padding points at an entry that stays zero, with coefficient 0.
+    const int nrw = nr + 1, narr = std::max(5, w.molr + w.molp), zero = nr;
+    auto net = [&](int s, int k) {
+        int v = 0;
+        for (int x : rs[s]) v -= x == k;
+        for (int x : ps[s]) v += x == k;
+        return v;
+    };
+    auto word = [](int idx, int nu) { return (int)((unsigned)idx * 8u | ((unsigned)nu << 24)); };
+    // one list per position row, walked four words at a time and two such rows
+    // a turn
+    struct Lists {
+        std::vector<int> len, data;
+    };
+    auto longest = [](const std::vector<std::vector<int>>& lanes) {
+        size_t n = 0;
+        for (const auto& v : lanes) n = std::max(n, v.size());
+        return n;
+    };
+    auto add = [&](Lists& l, const std::vector<std::vector<int>>& lanes, int padding) {
+        const size_t n = (longest(lanes) + 7) / 8 * 8;
+        l.len.push_back((int)(n / 4));
+        for (size_t t = 0; t < n; ++t)
+            for (int i = 0; i < 16; ++i) l.data.push_back(t < lanes[i].size() ? lanes[i][t] : padding);
+    };
+    Lists wl, dl, dgl, srl, sxl, spl;
+    for (int r = 0; r < w.r; ++r) {
+        std::vector<std::vector<int>> lw(16), ld(16);
+        for (int i = 0; i < 16; ++i) {
+            const int k = 16 * r + i - 1;
+            if (k < 0 || k >= na) continue;
+            for (int s = 0; s < nr; ++s)
+                if (const int v = net(s, k)) lw[i].push_back(word(s, v));
+            for (int t = 0; t < w.ntb; ++t)
+                if (const int v = net(tb[t], k)) ld[i].push_back(word(narr * nrw + t, v));
+        }
+        add(wl, lw, word(zero, 0));
+        add(dl, ld, word(zero, 0));
+    }
+    // Jacobian rows, column by column, but a species' own column in a list of
+    // its own (all its reactions are in it, a few of them in any other column,
+    // and each column's lists are as long as the longest)
+    std::vector<std::vector<std::vector<std::vector<int>>>> jlist(w.r);
+    for (int r = 0; r < w.r; ++r) {
+        std::vector<std::vector<int>> lg(16);
+        for (int c = 0; c < ns; ++c) {
+            std::vector<std::vector<int>> lj(16);
+            for (int i = 0; i < 16; ++i) {
+                const int k = 16 * r + i - 1;
+                if (k < 0 || k >= na) continue;
+                for (int s = 0; s < nr; ++s) {
+                    const int v = net(s, k);
+                    if (!v) continue;
+                    for (size_t q = 0; q < rs[s].size(); ++q)
+                        if (rs[s][q] == c) lj[i].push_back(word((int)q * nrw + s, v));
+                    if (m.reactions[order[s]].reversible)
+                        for (size_t q = 0; q < ps[s].size(); ++q)
+                            if (ps[s][q] == c) lj[i].push_back(word((w.molr + (int)q) * nrw + s, v));
+                }
+                for (int t = 0; t < w.ntb; ++t) {
+                    const int v = net(tb[t], k);
+                    for (int q = 0; v && q < w.maxp; ++q)
+                        if (tsp[(size_t)q * w.ntb + t] == c && tc[(size_t)q * w.ntb + t] != 0.0)
+                            lj[i].push_back(word(narr * nrw + w.ntb + t * w.maxp + q, v));
+                }
+            }
+            const int own = c + 1 - 16 * r;
+            if (own >= 0 && own < 16 && c < na) lg[own].swap(lj[own]);
+            jlist[r].push_back(lj);
+        }
+        add(dgl, lg, word(zero, 0));
+    }
+    // in groups of JGW columns of similar list length, walked side by side; the
+    // groups of the columns of species some reaction changes come first
+    const int jgw = 8;
+    std::vector<int> grow, gcol, glen, jdata;
+    int jgact = 0;
+    for (int part = 0; part < 2; ++part) {
+        for (int r = 0; r < w.r; ++r) {
+            std::vector<int> cols;
+            for (int c = part == 0 ? 0 : na; c < (part == 0 ? na : ns); ++c) cols.push_back(c);
+            std::stable_sort(cols.begin(), cols.end(), [&](int a, int b) {
+                return longest(jlist[r][a]) > longest(jlist[r][b]);
+            });
+            for (size_t g = 0; g < cols.size(); g += jgw) {
+                const size_t n = (longest(jlist[r][cols[g]]) + 1) / 2 * 2;
+                grow.push_back(r);
+                glen.push_back((int)n);
+                for (int q = 0; q < jgw; ++q) gcol.push_back(g + q < cols.size() ? cols[g + q] : -1);
+                for (size_t t = 0; t < n; ++t)
+                    for (int q = 0; q < jgw; ++q)
+                        for (int i = 0; i < 16; ++i) {
+                            const bool in = g + q < cols.size() && t < jlist[r][cols[g + q]][i].size();
+                            jdata.push_back(in ? jlist[r][cols[g + q]][i][t] : word(zero, 0));
+                        }
             }
         }
-        while ((srx.size() - off.back()) % 4) {   // padded to a multiple of 4 (coefficient 0)
-            srx.push_back(0);
-            snu.push_back(0);
-        }
-        off.push_back((int)srx.size());
+        if (part == 0) jgact = (int)grow.size();
     }
-    o << "// species k: the reactions that change it, SP_RX[SP_OFF[k] .. SP_OFF[k+1]),\n"
-         "// with net coefficients SP_NU (padded to a multiple of 4 by coefficient 0)\n";
-    ints("SP_OFF", off);
-    ints("SP_RX", srx);
-    ints("SP_NU", snu);
-    // the same entries packed for the Jacobian rows, so one round of loads gives
-    // everything an entry needs: slot | (net coefficient & 255) << 16, then the
-    // species of the reaction's slots 0-3 and 4-5 as bytes (index + 1, 0 unused)
-    {
-        std::vector<int> jp;
-        for (size_t e = 0; e < srx.size(); ++e) {
-            const int slot = srx[e];
-            jp.push_back((int)((unsigned)slot | (((unsigned)snu[e] & 255u) << 16)));
-            unsigned b[2] = {0u, 0u};
-            for (int t = 0; t < w.nslot; ++t) {
-                const int spc = sp[slot * w.nslot + t];
-                b[t / 4] |= (unsigned)(spc + 1) << (8 * (t % 4));
+    for (int r = 0; r < w.r + w.ri; ++r) {
+        std::vector<std::vector<int>> lr(16), lx(16), lp(16);
+        for (int i = 0; i < 16; ++i) {
+            const int sp0 = pspec[16 * r + i];
+            if (sp0 < 0) continue;
+            const int k = inv[sp0];
+            for (int s = 0; s < nr; ++s) {
+                for (size_t q = 0; q < rs[s].size(); ++q)
+                    if (rs[s][q] == k) lr[i].push_back((int)q * nrw + s);
+                if (m.reactions[order[s]].reversible)
+                    for (size_t q = 0; q < ps[s].size(); ++q)
+                        if (ps[s][q] == k) lp[i].push_back((int)q * nrw + s);
             }
-            jp.push_back((int)b[0]);
-            jp.push_back((int)b[1]);
+            for (int t = 0; t < w.ntb; ++t)
+                for (int q = 0; q < w.maxp; ++q)
+                    if (tsp[(size_t)q * w.ntb + t] == k && tc[(size_t)q * w.ntb + t] != 0.0) lx[i].push_back(t * w.maxp + q);
         }
-        o << "// per SP entry: slot | (net coefficient & 255) << 16, slot species 0-3, 4-5 (bytes, index + 1)\n";
-        ints("SP_JPACK", jp);
+        add(srl, lr, zero);
+        add(spl, lp, zero);
+        add(sxl, lx, w.ntb * w.maxp);
     }
-    // third-body and falloff reactions t (EFF row t): their slot, and the net
-    // coefficient of every species in them (the dense third-body part of the
-    // Jacobian rows)
-    std::vector<int> tbslot;
-    std::vector<double> nutb;
-    for (int s = 0; s < nr; ++s)
-        if (effrow[s] >= 0 && m.reactions[order[s]].kind != RxnKind::Plog) tbslot.push_back(s);
-    for (int k = 0; k < ns; ++k)
-        for (int s : tbslot) {
-            const auto& r = m.reactions[order[s]];
-            int v = 0;
-            for (auto& t : r.reac) if (t.sp == k) v -= t.nu;
-            for (auto& t : r.prod) if (t.sp == k) v += t.nu;
-            nutb.push_back((double)v);
+    // (a table's lists follow one another in the order the evaluation walks
+    // them; two spare rows at the end, as words are loaded two rows ahead)
+    auto table = [&](const std::string& nm, std::initializer_list<std::pair<const char*, const Lists*>> parts) {
+        std::vector<int> data;
+        for (const auto& q : parts) {
+            ints(std::string("constexpr int ") + q.first + "LEN", q.second->len);
+            data.insert(data.end(), q.second->data.begin(), q.second->data.end());
         }
-    o << "constexpr int NTB = " << tbslot.size() << ";\n"
-         "static_assert(NTB == 0 || sizeof(EFF) == sizeof(double) * NTB * NS, \"one EFF row per third-body "
-         "reaction\");\n"
-         "// third-body or falloff reaction t: its slot (EFF row t); the net coefficient of\n"
-         "// species k in it as a 4-bit field (coefficient + 8), eight per word:\n"
-         "// NU_TB4[k * NTBW + t / 8] >> (4 (t % 8))\n";
-    ints("TB_SLOT", tbslot);
-    {
-        const int ntb = (int)tbslot.size(), ntbw = std::max(1, (ntb + 7) / 8);
-        std::vector<int> packed((size_t)ns * ntbw, 0);
-        for (int k = 0; k < ns; ++k)
-            for (int t = 0; t < ntb; ++t) {
-                const int v = (int)nutb[(size_t)k * ntb + t];
-                packed[(size_t)k * ntbw + t / 8] |= (int)((unsigned)(v + 8) << (4 * (t % 8)));
-            }
-        o << "constexpr int NTBW = " << ntbw << ";\n";
-        ints("NU_TB4", packed);
-    }
+        data.insert(data.end(), 8 * 16, 0);
+        ints(ci + nm, data);
+    };
+    o << "// by row: production rates (reaction slot, net coefficient); third-body part of a\n"
+         "// Jacobian row (d q / d [M] of the slots that change the species); the species'\n"
+         "// own column of it\n";
+    table("RL", {{"W", &wl}, {"D", &dl}, {"DG", &dgl}});
+    o << "// transposed product, by column: reactant slots, third-body corrections, product slots\n";
+    table("TL", {{"SR", &srl}, {"SX", &sxl}, {"SP", &spl}});
+    o << "// Jacobian rows, other columns: partials of the slots and third-body corrections,\n"
+         "// in groups of columns\n"
+      << "constexpr int JGW = " << jgw << ", JGACT = " << jgact << ", JGALL = " << grow.size() << ";\n";
+    ints("constexpr int JGROW", grow);
+    ints("constexpr int JGLEN", glen);
+    ints("constexpr int JGCOL", gcol);
+    jdata.insert(jdata.end(), 2 * jgw * 16, 0);
+    ints(ci + "JL", jdata);
     o << "}  // namespace mech\n";
     return o.str();
 }

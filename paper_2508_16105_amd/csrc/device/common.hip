@@ -51,6 +51,7 @@ struct IntegrateArgs {
     int* nacc;
     int* nrej;
     StepArgs step;
+    unsigned long long* head;  // nullable: counter (zero at launch) the cells are dealt through
 };
 
 }  // namespace chem

@@ -1,23 +1,38 @@
 // wide.hip -- the chemistry step for mechanisms whose per-cell matrices do not
 // fit the registers of one lane (CDNA4, gfx950).
 //
-// G lanes (a power of two, at least n = ns + 1) cooperate on one cell, so a
-// 64-lane wave holds 64 / G cells.  Lane i of a group owns component i of
-// every state-sized vector (i = 0: T, i = 1 + k: Y_k) and row i of the
-// Jacobian, of the step matrix and of its LU factors: n doubles of matrix row
-// and one double per vector stay in registers.  Per source-term evaluation:
-//   - species thermo (NASA-7) in the species' own lanes;
-//   - mixture sums (sum Y/W, c_p, heat release) as group reductions;
-//   - reaction rates spread over the lanes, read from the mechanism tables
-//     (reactions grouped by kind so a round of lanes mostly takes one branch);
-//   - production rates gathered, and Jacobian rows assembled, by each species
-//     lane from the rates and partials in the cell's LDS scratch in a fixed
-//     order (reproducible results);
-// and per step the LU factorisation with partial pivoting (pivot search as a
-// group arg-max, the pivot row broadcast from its lane), the triangular
-// solves (one broadcast per column) and the RMS error norm (a group sum).
-// Reductions leave the same bits in every lane of a group, so the step-size
-// controller runs identically in all of them.
+// G = 16 lanes, one DPP row, cooperate on one cell, so a 64-lane wave holds
+// four cells.  The components of the state are taken in the elimination order
+// T, then the species some reaction changes (NACT positions), then the
+// species no reaction changes.  Lane i owns the positions r * 16 + i for
+// r < R = ceil(NACT / 16): their components of every state-sized vector, and
+// their rows of the step matrix and of its LU factors, all in registers.
+//
+// Why 16 lanes and R rows a lane, not one row a lane: a broadcast from a lane
+// of the group is then one in-row DPP move a register (row_newbcast), with no
+// LDS round trip and no scalar register; the pivot search and the mixture
+// sums are four DPP steps; and the work that every lane repeats (T's powers,
+// the controller, the pivot's reciprocal) serves four cells a wave.  With a
+// lane a row (64 lanes a cell at 33 unknowns, 32 at 17) the same step took
+// 18.2 k vector instructions per cell and 68 us at 17 unknowns.
+//
+// A species no reaction changes has a zero source term and a zero row in the
+// Jacobian, so all its stage vectors are exactly zero and its column of the
+// step matrix never meets anything but zeros: the forward step is the
+// NACT x NACT system.  Such species enter the mixture sums, the third-body
+// concentrations and, in the adjoint, the outputs.
+//
+// Per source-term evaluation:
+//   - species thermo (NASA-7) and equilibrium factors e^{+-G} in the lanes of
+//     the species' positions;
+//   - mixture sums (sum Y/W, c_p, heat release) as DPP butterflies, every lane
+//     of the group ending with the same bits;
+//   - reactions 16 at a time (lane i: slot q * 16 + i), those with third-body,
+//     falloff or PLOG terms first, so that only the leading rounds run that code;
+//   - production rates, Jacobian rows and transposed products gathered by each
+//     lane from the cell's LDS through per-position lists padded to the
+//     longest of the 16 lanes, so every loop has a compile-time length and
+//     the sums have a fixed order (reproducible results).
 //
 // The equations, the RODAS4 tableau and the controller are those of the
 // one-cell-per-lane integrator (the species/energy source of eqs. (20)-(21)
@@ -30,691 +45,929 @@ using chem::RC;
 using chem::Rodas4;
 using chem::StepArgs;
 using chem::finite;
-constexpr int N = mech::N, NS = mech::NS, NR = mech::NR, G = mech::G;
-constexpr int CPW = 64 / G;
-constexpr int NSLOT = mech::NSLOT, PW = mech::PW, JW = mech::JW;
+using chem_math::Dual;
+constexpr int N = mech::N, NS = mech::NS, NR = mech::NR, NA = mech::NA, NI = mech::NI;
+constexpr int NACT = mech::NACT, R = mech::R, RI = mech::RI, NPT = mech::NPT;
+constexpr int G = 16;
+constexpr int SP = NS + 1;           // a species array in LDS, and a last entry of neutral elements
+constexpr int NRW = NR + 1;          // a reaction array in LDS, and a last entry that stays zero
+constexpr int MOLR = mech::MOLR, MOLP = mech::MOLP;
+constexpr int MOLM = MOLR > MOLP ? MOLR : MOLP;
+constexpr int WR = (MOLR + 3) / 4, WP = (MOLP + 3) / 4, NWORDS = WR + WP + 1;
 constexpr int ROUNDS = (NR + G - 1) / G;
-static_assert(N <= G && G <= 64 && (G & (G - 1)) == 0, "group size");
+constexpr int NTB = mech::NTB, MAXP = mech::MAXP;
+static_assert(R * 16 >= NACT && RI * 16 >= NI + 1, "positions");
 
-__device__ __forceinline__ int gl() { return (int)(threadIdx.x & (unsigned)(G - 1)); }
+// ---- LDS: the workgroup's tables, then one scratch per cell ----
+// The tables that an evaluation reads at every reaction and species sit in
+// LDS, one copy for the workgroup's waves: from global memory each read cost
+// an L2 latency in the evaluation's chain (the vector L1 does not hold them
+// all; 32 species: 12.2 k cycles for the reactions of an evaluation, 4.7 k for
+// the thermo, one wave per SIMD).
+//   doubles: ln A, b, Ea/R by slot; NASA-7 rows by position; low-pressure
+//   limits, Troe/SRI constants and partner efficiencies of the third-body
+//   slots; ints: packed words by slot, partner species
+constexpr int T_PAR = 0;
+constexpr int T_TH = 3 * NR;
+constexpr int T_LOW = T_TH + 38 * NPT;
+constexpr int T_TROE = T_LOW + 3 * NTB;
+constexpr int T_TBC = T_TROE + 8 * NTB;
+constexpr int T_INT = T_TBC + MAXP * NTB;                 // in doubles
+constexpr int I_WORDS = 0, I_TBSP = NWORDS * NR, N_INT = NWORDS * NR + MAXP * NTB;
+constexpr int TAB_DOUBLES = T_INT + (N_INT + 1) / 2;
+// per cell (in scalars of the evaluation's type): concentrations, e^{G},
+// e^{-G}, H/RT, then G itself where some reaction needs it, W_k w_k and cp/R
+// (transposed product), then the reaction arrays
+constexpr int L_C = 0, L_GP = SP, L_GM = 2 * SP, L_H = 3 * SP;
+constexpr int L_G = 4 * SP;
+constexpr int L_A = (mech::HAS_LNKC ? 5 : 4) * SP;
+constexpr int NARR = MOLR + MOLP > 5 ? MOLR + MOLP : 5;
+constexpr int L_X = L_A + NARR * NRW;        // third-body terms: NTB, then NTB * MAXP partner corrections
+constexpr int L_WW = L_A, L_CP = L_A + SP;
+constexpr int L_V = L_A + 2 * SP;            // transposed product: MOLM arrays for A, MOLM for H, corrections
+constexpr int L_XA = L_V + 2 * MOLM * NRW;
+constexpr int NXV = NTB * MAXP + 1;
 
-// the lane index behind an opaque zero: compares against it (i == k for
-// every k of an unrolled loop) are made where used instead of being hoisted
-// out of the substep loop as dozens of live lane masks
+__device__ __forceinline__ int gl() { return (int)(threadIdx.x & 15u); }
+__device__ __forceinline__ int gbase() { return (int)(threadIdx.x & 48u); }
+
+// the lane index behind an opaque zero: compares against it (i == k for every
+// k of an unrolled loop) and table words loaded at it are made where used
+// instead of being hoisted out of the substep loop as dozens of live masks and
+// hundreds of live words
 __device__ __forceinline__ int gl_local() { return gl() + mech::opaque_zero(); }
-__device__ __forceinline__ int gbase() { return (int)(threadIdx.x & 63u & ~(unsigned)(G - 1)); }
 
-// value of x in lane `src` of this group; src is the same in every lane of the group
-__device__ __forceinline__ double bcast(double x, int src)
+template <int K>
+struct Int {
+    static constexpr int v = K;
+};
+
+// f(Int<B>{}), ..., f(Int<E - 1>{}): a loop whose index is a constant in the
+// body, for bounds and list lengths that depend on it
+template <int B, int E, class Fn>
+__device__ __forceinline__ void static_for(Fn&& f)
 {
-    if constexpr (G == 64) {
-        const long long b = __double_as_longlong(x);
-        const int lo = __builtin_amdgcn_readlane((int)b, src);
-        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
-        return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-    } else {
-        return __shfl(x, gbase() + src, 64);
+    if constexpr (B < E) {
+        f(Int<B>{});
+        static_for<B + 1, E>(f);
     }
 }
-
-// value of x in lane `src` of this group; src may differ per lane
-__device__ __forceinline__ double gather(double x, int src) { return __shfl(x, gbase() + src, 64); }
 
 template <int CTRL>
 __device__ __forceinline__ double dpp(double x)
 {
     const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-__device__ __forceinline__ double readlane(double x, int lane)
+// value of x in lane k of this group (k a compile-time constant after unrolling)
+__device__ __forceinline__ double bc(double x, int k)
 {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)b, lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    switch (k & 15) {
+    case 0: return dpp<0x150>(x);
+    case 1: return dpp<0x151>(x);
+    case 2: return dpp<0x152>(x);
+    case 3: return dpp<0x153>(x);
+    case 4: return dpp<0x154>(x);
+    case 5: return dpp<0x155>(x);
+    case 6: return dpp<0x156>(x);
+    case 7: return dpp<0x157>(x);
+    case 8: return dpp<0x158>(x);
+    case 9: return dpp<0x159>(x);
+    case 10: return dpp<0x15A>(x);
+    case 11: return dpp<0x15B>(x);
+    case 12: return dpp<0x15C>(x);
+    case 13: return dpp<0x15D>(x);
+    case 14: return dpp<0x15E>(x);
+    default: return dpp<0x15F>(x);
+    }
 }
+__device__ __forceinline__ Dual bc(Dual x, int k) { return Dual(bc(x.v, k), bc(x.d, k)); }
 
-// Group reductions.  Inside each 16-lane row a butterfly over the DPP
-// patterns xor 1, xor 2, mirror-in-8 and mirror-in-16: each step adds a
-// lane's value to its partner's and the partner adds the same two numbers,
-// so every lane of the row ends with the same bits; rows are then combined
-// in a fixed order from their last lanes.
+// value of x in lane `src` of this group; src may differ per lane
+__device__ __forceinline__ double gather(double x, int src) { return __shfl(x, gbase() + src, 64); }
+
+// Group reductions: a butterfly over the DPP patterns xor 1, xor 2,
+// mirror-in-8 and mirror-in-16; each step adds a lane's value to its
+// partner's and the partner adds the same two numbers, so every lane of the
+// group ends with the same bits.
 template <class Op>
 __device__ __forceinline__ double greduce(double x, Op op)
 {
     x = op(x, dpp<0xB1>(x));    // quad_perm [1, 0, 3, 2]
     x = op(x, dpp<0x4E>(x));    // quad_perm [2, 3, 0, 1]
     x = op(x, dpp<0x141>(x));   // row_half_mirror
-    x = op(x, dpp<0x140>(x));   // row_mirror
-    if constexpr (G == 16) {
-        return x;
-    } else if constexpr (G == 32) {
-        const double r0 = readlane(x, 15), r1 = readlane(x, 31), r2 = readlane(x, 47), r3 = readlane(x, 63);
-        return gbase() == 0 ? op(r0, r1) : op(r2, r3);
-    } else {
-        const double r0 = readlane(x, 15), r1 = readlane(x, 31), r2 = readlane(x, 47), r3 = readlane(x, 63);
-        return op(op(r0, r1), op(r2, r3));
-    }
+    return op(x, dpp<0x140>(x));   // row_mirror
 }
-
 __device__ __forceinline__ double gsum(double x)
 {
     return greduce(x, [](double a, double b) { return a + b; });
 }
-
 __device__ __forceinline__ double gmax(double x)
 {
     return greduce(x, [](double a, double b) { return fmax(a, b); });
 }
-
-__device__ __forceinline__ chem_math::Dual gsum(chem_math::Dual x)
-{
-    return chem_math::Dual(gsum(x.v), gsum(x.d));
-}
-
-// bits of this group's lanes in a wave-wide ballot, lane 0 of the group at bit 0
-__device__ __forceinline__ unsigned long long gbits(unsigned long long ballot)
-{
-    if constexpr (G == 64) return ballot;
-    else return (ballot >> gbase()) & ((1ull << G) - 1ull);
-}
+__device__ __forceinline__ Dual gsum(Dual x) { return Dual(gsum(x.v), gsum(x.d)); }
 
 // true in every lane of the group if `bad` holds in any lane of it
 __device__ __forceinline__ bool gany(bool bad)
 {
-    return gbits(__ballot(bad)) != 0ull;
+    return ((__ballot(bad) >> gbase()) & 0xffffull) != 0ull;
 }
 
-// LDS writes of this wave visible to its later LDS reads
+// Order between the LDS accesses of one wave: its LDS instructions execute in
+// program order, so only the compiler has to keep it.
 __device__ __forceinline__ void lds_sync()
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <class S>
-__device__ __forceinline__ S ipow(S c, int nu) { return nu == 1 ? c : (nu == 2 ? c * c : c * c * c); }
-
-// d(c^nu)/dc
-template <class S>
-__device__ __forceinline__ S dipow(S c, int nu) { return nu == 1 ? S(1.0) : (nu == 2 ? 2.0 * c : 3.0 * c * c); }
-
-// add x to an LDS word (only the lane owning the address adds to it)
-__device__ __forceinline__ void lds_add(double* p, double x) { atomicAdd(p, x); }
-__device__ __forceinline__ void lds_add(chem_math::Dual* p, chem_math::Dual x)
+__device__ __forceinline__ void load_tables(double* __restrict__ tab, const double* __restrict__ par)
 {
-    atomicAdd(&p->v, x.v);
-    atomicAdd(&p->d, x.d);
+    int* const ti = (int*)(tab + T_INT);
+    const int t0 = (int)threadIdx.x, nt = (int)blockDim.x;
+    for (int j = t0; j < NR; j += nt) {
+        const int o = mech::RX_ORIG[j];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) tab[T_PAR + q * NR + j] = par[q * NR + o];
+    }
+    for (int j = t0; j < 38 * NPT; j += nt) tab[T_TH + j] = mech::TH[j];
+    for (int j = t0; j < 3 * NTB; j += nt) tab[T_LOW + j] = mech::RX_LOW[j];
+    for (int j = t0; j < 8 * NTB; j += nt) tab[T_TROE + j] = mech::RX_TROE[j];
+    for (int j = t0; j < MAXP * NTB; j += nt) {
+        tab[T_TBC + j] = mech::TBP_C[j];
+        ti[I_TBSP + j] = mech::TBP_SP[j];
+    }
+    for (int j = t0; j < NWORDS * NR; j += nt) ti[I_WORDS + j] = mech::RX_WORDS[j];
+    __syncthreads();
 }
 
-// Evaluation modes of the source terms: the rates; the rates and the
-// Jacobian row; the parameter products w . df/dtheta (adjoint).
-enum : int { F_ONLY = 0, F_JAC = 1, PARAM_VJP = 2 };
+// the temperature-dependent scalars of one evaluation, the same in every lane
+template <class S>
+struct Mix {
+    S T, lnT, iT, lnPRT, ctot, rtp, prt;
+    double p;
+};
 
-// Rate of progress of the reaction in slot j, written to the cell's LDS; with
-// F_JAC also its partials (d q / d C of each species slot, d q / dT at fixed C,
-// and the coefficient of the third-body efficiencies in d q / d C); with
-// PARAM_VJP the products of w . df/dq_j with d q_j / d(ln A, b, Ea) added to g.
-template <class S, int MODE>
-__device__ __forceinline__ void reaction(int j, const unsigned (&pk)[3], const double* __restrict__ par,
-                                         S* __restrict__ L, S T, S lnT, S iT, S lnPRT, S ctot, S irho, S rcpinv,
-                                         double p, S* __restrict__ g)
+// One reaction's rate and derivatives.  q: rate of progress; the others as far
+// as the evaluation needs them: kf, kr the (third-body scaled) rate constants
+// of the two sides; dqT = d q / d T at fixed C; dM the coefficient of the
+// third-body efficiencies in d q / d C; s = sum_m d q / d C_m C_m; qA = d q /
+// d ln A of the main rate; dH = sum nu H/RT.
+template <class S>
+struct Rate {
+    S q, kf, kr, dqT, dM, s, qA, dH;
+};
+
+// FULL: the round may hold slots other than elementary ones.
+// DERIV: derivatives are wanted.
+template <class S, bool FULL, bool DERIV>
+__device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, const S* __restrict__ L,
+                                         const Mix<S>& x, Rate<S>& o, int (&ra)[MOLR], int (&pa)[MOLP], int& misc)
 {
-    constexpr bool JAC = MODE == F_JAC;
-    // the slot's packed table entry (loaded by the caller ahead of time)
-    // kind: 0 elementary, 1 third body, 2 Lindemann, 3 Troe, 4 SRI, 5 PLOG
-    const int kind = (int)(pk[2] & 7u);
-    const bool irrev = mech::HAS_IRREV && ((pk[2] >> 3) & 1u);
-    const int dnu = (int)((pk[2] >> 4) & 7u) - 4;
-    const int er = (int)((pk[2] >> 7) & 511u) - 1;   // EFF row, or PLOG table for kind 5
-    const int oj = (int)(pk[2] >> 16);
-    double pb = par[NR + oj], pe = par[2 * NR + oj];
-    S lnk = lnT * pb;
-    lnk = fma(-iT, pe, lnk);
-    lnk = lnk + par[oj];
-    if (mech::HAS_PLOG && kind == 5) {
+    const int* const words = (const int*)(tab + T_INT) + I_WORDS;
+    const double lnA = tab[T_PAR + j], pb = tab[T_PAR + NR + j], pe = tab[T_PAR + 2 * NR + j];
+    int w[NWORDS];
+#pragma unroll
+    for (int q = 0; q < NWORDS; ++q) w[q] = words[q * NR + j];
+    misc = w[NWORDS - 1];
+#pragma unroll
+    for (int s = 0; s < MOLR; ++s) ra[s] = (w[s / 4] >> (8 * (s % 4))) & 255;
+#pragma unroll
+    for (int s = 0; s < MOLP; ++s) pa[s] = (w[WR + s / 4] >> (8 * (s % 4))) & 255;
+    S pf = L[L_C + ra[0]], pr = L[L_C + pa[0]];
+#pragma unroll
+    for (int s = 1; s < MOLR; ++s) pf = pf * L[L_C + ra[s]];
+#pragma unroll
+    for (int s = 1; s < MOLP; ++s) pr = pr * L[L_C + pa[s]];
+    // 1/K_c = prod_reac e^{G} prod_prod e^{-G} (RT/P_atm)^dnu, the factors
+    // multiplied reactant, product, reactant, ... as the range check took them
+    S ikc = L[L_GP + ra[0]] * L[L_GM + pa[0]];
+#pragma unroll
+    for (int s = 1; s < MOLM; ++s) {
+        if (s < MOLR) ikc = ikc * L[L_GP + ra[s < MOLR ? s : 0]];
+        if (s < MOLP) ikc = ikc * L[L_GM + pa[s < MOLP ? s : 0]];
+    }
+    const int dnu = ((misc >> 5) & 7) - 4;
+#pragma unroll
+    for (int q = 1; q <= mech::MAXDNU; ++q) {
+        const S f = dnu > 0 ? x.rtp : x.prt;
+        ikc = (dnu >= q || dnu <= -q) ? ikc * f : ikc;
+    }
+    if (mech::HAS_LNKC && !((misc >> 4) & 1)) {
+        S lnKc = (double)dnu * x.lnPRT;
+#pragma unroll
+        for (int s = 0; s < MOLR; ++s) lnKc = lnKc - L[L_G + ra[s]];
+#pragma unroll
+        for (int s = 0; s < MOLP; ++s) lnKc = lnKc + L[L_G + pa[s]];
+        ikc = chem_math::exp_poly(-lnKc);
+    }
+    if (mech::HAS_IRREV && ((misc >> 3) & 1)) ikc = 0.0;
+    S lnk = x.lnT * pb;
+    lnk = fma(-x.iT, pe, lnk);
+    lnk = lnk + lnA;
+    const int kind = FULL ? misc & 7 : 0;
+    double eb = pb, ee = pe;
+    if (FULL && mech::HAS_PLOG && kind == 5) {
         // the Arrhenius set at this pressure: linear in ln p between the
         // tabulated pressures, the end sets outside them
-        const double lnp = log(p);
-        const int e0 = mech::RX_PLOG_OFF[er], e1 = mech::RX_PLOG_OFF[er + 1] - 1;
+        const double lnp = log(x.p);
+        const int t = (misc >> 16) & 0xffff;
+        const int e0 = mech::RX_PLOG_OFF[t], e1 = mech::RX_PLOG_OFF[t + 1] - 1;
         const double* E = mech::RX_PLOG;
         int e = e0;
-        double w = 0.0;
+        double v = 0.0;
         if (lnp >= E[4 * e1]) {
             e = e1;
         } else if (lnp > E[4 * e0]) {
             while (e + 1 < e1 && lnp >= E[4 * (e + 1)]) ++e;
-            w = (lnp - E[4 * e]) / (E[4 * (e + 1)] - E[4 * e]);
+            v = (lnp - E[4 * e]) / (E[4 * (e + 1)] - E[4 * e]);
         }
         const int e2 = e < e1 ? e + 1 : e;
-        const double pla = fma(w, E[4 * e2 + 1] - E[4 * e + 1], E[4 * e + 1]);
-        const double plb = fma(w, E[4 * e2 + 2] - E[4 * e + 2], E[4 * e + 2]);
-        const double ple = fma(w, E[4 * e2 + 3] - E[4 * e + 3], E[4 * e + 3]);
-        lnk = lnk + (lnT * plb - iT * ple + pla);
-        pb += plb;
-        pe += ple;
+        const double pla = fma(v, E[4 * e2 + 1] - E[4 * e + 1], E[4 * e + 1]);
+        const double plb = fma(v, E[4 * e2 + 2] - E[4 * e + 2], E[4 * e + 2]);
+        const double ple = fma(v, E[4 * e2 + 3] - E[4 * e + 3], E[4 * e + 3]);
+        lnk = lnk + (x.lnT * plb - x.iT * ple + pla);
+        eb += plb;
+        ee += ple;
     }
-    int sp[NSLOT], nu[NSLOT];
-    S c[NSLOT];
-    S lnKc = 0.0, dH = 0.0, ws = 0.0;
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-        const unsigned v = (pk[s / 4] >> (8 * (s % 4))) & 255u;
-        sp[s] = (int)(v & 63u) - 1;
-        nu[s] = (int)(v >> 6);
-        c[s] = 1.0;
-        if (sp[s] >= 0) {
-            const double sgn = s < mech::MAXT ? -(double)nu[s] : (double)nu[s];
-            lnKc = fma(sgn, L[mech::L_G + sp[s]], lnKc);
-            if (MODE != F_ONLY) dH = fma(sgn, L[mech::L_H + sp[s]], dH);
-            if (MODE == PARAM_VJP) ws = fma(sgn * mech::MWTAB[sp[s]], L[mech::L_W + 1 + sp[s]], ws);
-            c[s] = L[mech::L_C + sp[s]];
-        }
-    }
-    lnKc = fma((double)dnu, lnPRT, lnKc);
-    S Mc = ctot;
-    if (er >= 0 && !(mech::HAS_PLOG && kind == 5)) {
-        for (int m = 0; m < NS; ++m) Mc = fma(mech::EFF[er * NS + m] - 1.0, L[mech::L_C + m], Mc);
-    }
-    S kf, kr, kinf = 0.0, r0 = 0.0, Fb = 1.0, ipr1 = 0.0, iKc = 0.0, Pr = 0.0;
-    S dF_dPr = 0.0, dF_dFc = 0.0, dlogFc_dT = 0.0, dlnF_T = 0.0;
-    if (kind < 2 || (mech::HAS_PLOG && kind == 5)) {
-        kf = chem_math::exp_poly(lnk);
-        kr = irrev ? S(0.0) : chem_math::exp_poly(lnk - lnKc);
-    } else {
-        // P_r = k0 [M] / k_inf, one exponential for the ratio
-        const double* lo = &mech::RX_LOW[j * 3];
-        kinf = chem_math::exp_poly(lnk);
-        const S lnr0 = lo[0] + lo[1] * lnT - lo[2] * iT - lnk;
-        r0 = chem_math::exp_poly(lnr0);
-        Pr = r0 * Mc;
-        const bool floored = !(Pr >= 1e-300);
-        const S logPr = floored ? S(-300.0) : log10(Pr);
-        if (kind == 3) {
-            const double* tr = &mech::RX_TROE[j * 8];
-            const S e3 = chem_math::exp_poly(-T * tr[2]);
-            const S e1 = chem_math::exp_poly(-T * tr[3]);
-            S Fc = tr[0] * e3 + tr[1] * e1;
-            S dFc = tr[5] * e3 + tr[6] * e1;
-            if (tr[7] != 0.0) {
-                const S e2 = chem_math::exp_poly(-tr[4] * iT);
-                Fc += e2;
-                dFc += tr[4] * iT * iT * e2;
+    S kf = chem_math::exp_poly(lnk);
+    S fac = 1.0, Mc = 0.0, dkdM = 0.0, qAf = 1.0, dlnkf = 0.0;
+    if (DERIV) dlnkf = (eb + ee * x.iT) * x.iT;
+    if (FULL && NTB > 0 && kind >= 1 && kind <= 4) {
+        const int t = (misc >> 16) & 0xffff;
+        Mc = x.ctot;
+#pragma unroll 1
+        for (int q = 0; q < MAXP; ++q)
+            Mc = fma(L[L_C + ((const int*)(tab + T_INT))[I_TBSP + q * NTB + t]], tab[T_TBC + q * NTB + t], Mc);
+        if (kind == 1) fac = Mc;
+        if (kind >= 2) {
+            // P_r = k0 [M] / k_inf, one exponential for the ratio
+            const double* lo = tab + T_LOW + t;
+            const S lnr0 = lo[0] + lo[NTB] * x.lnT - lo[2 * NTB] * x.iT - lnk;
+            const S r0 = chem_math::exp_poly(lnr0);
+            const S Pr = r0 * Mc;
+            const bool floored = !(chem_math::value(Pr) >= 1e-300);
+            const S logPr = floored ? S(-300.0) : log10(Pr);
+            S Fb = 1.0, dF_dPr = 0.0, dlnF_T = 0.0;
+            if (kind == 3) {
+                const double* tr = tab + T_TROE + t;
+                const S e3 = chem_math::exp_poly(-x.T * tr[2 * NTB]);
+                const S e1 = chem_math::exp_poly(-x.T * tr[3 * NTB]);
+                S Fc = tr[0] * e3 + tr[1 * NTB] * e1;
+                S dFc = tr[5 * NTB] * e3 + tr[6 * NTB] * e1;
+                if (tr[7 * NTB] != 0.0) {
+                    const S e2 = chem_math::exp_poly(-tr[4 * NTB] * x.iT);
+                    Fc += e2;
+                    dFc += tr[4 * NTB] * x.iT * x.iT * e2;
+                }
+                const S logFc = log10(Fc);
+                const S tc = -0.4 - 0.67 * logFc;
+                const S tn = 0.75 - 1.27 * logFc;
+                const S tu = logPr + tc;
+                const S itd = chem_math::recip(tn - 0.14 * tu);
+                const S tx = tu * itd;
+                const S iop = chem_math::recip(1.0 + tx * tx);
+                const S logF = logFc * iop;
+                Fb = chem_math::exp_poly(mech::LN10 * logF);
+                if (DERIV) {
+                    const S tg = -logFc * 2.0 * tx * (iop * iop);
+                    if (!floored) dF_dPr = tg * tn * (itd * itd);
+                    const S dF_dFc = iop + tg * (-0.67 * tn + 1.27 * tu) * (itd * itd);
+                    dlnF_T = mech::LN10 * dF_dFc * (dFc * chem_math::recip(Fc * mech::LN10));
+                }
+            } else if (mech::HAS_SRI && kind == 4) {
+                // SRI: F = d [a exp(-b/T) + exp(-T/c)]^X T^e, X = 1 / (1 + log10(P_r)^2);
+                // row: a, -b, 1/c, b, ln d, e
+                const double* sr = tab + T_TROE + t;
+                const S sea = sr[0] * chem_math::exp_poly(sr[1 * NTB] * x.iT);
+                const S sec = chem_math::exp_poly(-x.T * sr[2 * NTB]);
+                const S sY = sea + sec;
+                const S lnsY = log(sY);
+                const S sX = chem_math::recip(1.0 + logPr * logPr);
+                Fb = chem_math::exp_poly(sX * lnsY + sr[5 * NTB] * x.lnT + sr[4 * NTB]);
+                if (DERIV) {
+                    if (!floored) dF_dPr = lnsY * (-2.0 / mech::LN10) * logPr * sX * sX;
+                    dlnF_T = sX * (sea * sr[3 * NTB] * x.iT * x.iT - sec * sr[2 * NTB]) / sY + sr[5 * NTB] * x.iT;
+                }
             }
-            const S logFc = log10(Fc);
-            const S tc = -0.4 - 0.67 * logFc;
-            const S tn = 0.75 - 1.27 * logFc;
-            const S tu = logPr + tc;
-            const S tden = tn - 0.14 * tu;
-            const S tx = tu / tden;
-            const S opx2 = 1.0 + tx * tx;
-            const S logF = logFc / opx2;
-            Fb = chem_math::exp_poly(mech::LN10 * logF);
-            if (MODE != F_ONLY) {
-                const S tg = -logFc * 2.0 * tx / (opx2 * opx2);
-                dF_dPr = floored ? S(0.0) : tg * tn / (tden * tden);
-                dF_dFc = 1.0 / opx2 + tg * (-0.67 * tn + 1.27 * tu) / (tden * tden);
-                dlogFc_dT = dFc / (Fc * mech::LN10);
-                dlnF_T = mech::LN10 * dF_dFc * dlogFc_dT;
+            const S ipr1 = chem_math::recip(1.0 + Pr);
+            if (DERIV) {
+                const S dlnk0 = (lo[NTB] + lo[2 * NTB] * x.iT) * x.iT;
+                dlnkf = dlnkf + (ipr1 + dF_dPr) * (dlnk0 - dlnkf) + dlnF_T;
+                dkdM = kf * r0 * Fb * (ipr1 * ipr1 + dF_dPr * ipr1);
+                qAf = Pr * ipr1 - dF_dPr;
             }
-        } else if (mech::HAS_SRI && kind == 4) {
-            // SRI: F = d [a exp(-b/T) + exp(-T/c)]^X T^e, X = 1 / (1 + log10(P_r)^2);
-            // row: a, -b, 1/c, b, ln d, e
-            const double* sr = &mech::RX_TROE[j * 8];
-            const S sea = sr[0] * chem_math::exp_poly(sr[1] * iT);
-            const S sec = chem_math::exp_poly(-T * sr[2]);
-            const S sY = sea + sec;
-            const S lnsY = log(sY);
-            const S sX = 1.0 / (1.0 + logPr * logPr);
-            Fb = chem_math::exp_poly(sX * lnsY + sr[5] * lnT + sr[4]);
-            if (MODE != F_ONLY) {
-                dF_dPr = floored ? S(0.0) : lnsY * (-2.0 / mech::LN10) * logPr * sX * sX;
-                dlnF_T = sX * (sea * sr[3] * iT * iT - sec * sr[2]) / sY + sr[5] * iT;
-            }
-        }
-        ipr1 = 1.0 / (1.0 + Pr);
-        kf = kinf * Pr * ipr1 * Fb;
-        iKc = irrev ? S(0.0) : chem_math::exp_poly(-lnKc);
-        kr = kf * iKc;
-    }
-    S pf = 1.0, pr = 1.0;
-#pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-        if (sp[s] >= 0) {
-            if (s < mech::MAXT) pf *= ipow(c[s], nu[s]);
-            else pr *= ipow(c[s], nu[s]);
+            kf = kf * Pr * ipr1 * Fb;
         }
     }
-    const S fwd = kf * pf, rev = kr * pr;
-    const S q = kind == 1 ? Mc * (fwd - rev) : fwd - rev;
-    if (MODE == PARAM_VJP) {
-        // w . df/dq_j: species rows W_k nu_kj / rho, temperature row
-        // -R T (sum nu H/RT) / (rho c_p); d q / d ln A of the main rate (k_inf
-        // for falloff, through P_r = k0 [M] / k_inf)
-        const S wsum = ws * irho - L[mech::L_W] * (mech::RU * T) * dH * rcpinv;
-        const S qA = (kind >= 2 && !(mech::HAS_PLOG && kind == 5)) ? q * (Pr * ipr1 - dF_dPr) : q;
-        const S gq = wsum * qA;
-        g[0] += gq;
-        g[1] += gq * lnT;
-        g[2] += gq * (-iT * (1.0 / mech::RU));
-        return;
-    }
-    L[mech::L_Q + j] = q;
-    if (!JAC) return;
-    S* P = L + mech::L_P + j * PW;
-    const S fac = kind == 1 ? Mc : S(1.0);
-    const S dlnKc = (dH - (double)dnu) * iT;
-    const S dlnkinf = (pb + pe * iT) * iT;
-    S dlnkf = dlnkinf;
-    S dM = kind == 1 ? fwd - rev : S(0.0);
-    if (kind >= 2 && !(mech::HAS_PLOG && kind == 5)) {
-        const double* lo = &mech::RX_LOW[j * 3];
-        const S dlnk0 = (lo[1] + lo[2] * iT) * iT;
-        dlnkf = dlnkinf + (ipr1 + dF_dPr) * (dlnk0 - dlnkinf) + dlnF_T;
-        const S dkdM = kinf * r0 * Fb * (ipr1 * ipr1 + dF_dPr * ipr1);
-        dM = dkdM * (pf - iKc * pr);
-    }
-    P[NSLOT] = fac * (dlnkf * fwd - (dlnkf - dlnKc) * rev);
-    P[NSLOT + 1] = dM;
+    const S net = fma(-ikc, pr, pf);
+    const S kfn = kf * net;
+    o.q = FULL ? fac * kfn : kfn;
+    if (DERIV) {
+        o.kf = FULL ? fac * kf : kf;
+        o.kr = o.kf * ikc;
+        const S fwd = o.kf * pf, rev = o.kr * pr;
+        S dH = 0.0;
 #pragma unroll
-    for (int s = 0; s < NSLOT; ++s) {
-        // derivative of this side's product with respect to the slot's species
-        S d = 0.0;
-        if (sp[s] >= 0) {
-            const int lo = s < mech::MAXT ? 0 : mech::MAXT;
-            d = dipow(c[s], nu[s]);
+        for (int s = 0; s < MOLP; ++s) dH = dH + L[L_H + pa[s]];
 #pragma unroll
-            for (int t = 0; t < mech::MAXT; ++t)
-                if (lo + t != s && sp[lo + t] >= 0) d *= ipow(c[lo + t], nu[lo + t]);
-            d = s < mech::MAXT ? fac * kf * d : -fac * kr * d;
+        for (int s = 0; s < MOLR; ++s) dH = dH - L[L_H + ra[s]];
+        o.dH = dH;
+        const S dlnKc = (dH - (double)dnu) * x.iT;
+        o.dqT = dlnkf * fwd - (dlnkf - dlnKc) * rev;
+        o.s = (double)((misc >> 8) & 15) * fwd - (double)((misc >> 12) & 15) * rev;
+        o.dM = 0.0;
+        o.qA = o.q;
+        if (FULL && NTB > 0 && kind >= 1 && kind <= 4) {
+            o.dM = kind == 1 ? kfn : dkdM * net;
+            o.s = o.s + Mc * o.dM;
+            if (kind >= 2) o.qA = o.q * qAf;
         }
-        P[s] = d;
     }
 }
 
-// Source terms f = dy/dt of the group's cell at the state whose component i
-// is yi (lane i); with F_JAC row i of the Jacobian in A; with PARAM_VJP
-// (weights w, component wi in lane i) the products w . df/dtheta of the
-// lane's reaction slots r G + i added to g[r].  Every lane of the group calls
-// it together.  S is double, or a dual number for directional derivatives.
-template <class S, int MODE>
-__device__ __forceinline__ S rhs(const double* __restrict__ par, double p, double ip, S yi, S* __restrict__ L,
-                                 S (&A)[N], S wi, S (&g)[ROUNDS][3])
+// product of the concentrations of a side's slots but s (times c)
+template <class S, int MOL>
+__device__ __forceinline__ S others(const S* __restrict__ L, const int (&a)[MOL], int s, S c)
 {
-    constexpr bool JAC = MODE == F_JAC;
-    const int i = gl();
-    const bool sp = i >= 1 && i <= NS;
-    const int k = sp ? i - 1 : 0;
-    // constant tables at an opaque offset: their uniform loads stay inside this
-    // evaluation instead of being hoisted out of the substep loop into SGPRs
-    const int z = mech::opaque_zero();
-    mech::cdbl* MW = (mech::cdbl*)&mech::MWTAB[0] + z;
-    // the packed table entries of the lane's reaction slots, loaded now so the
-    // loads overlap the thermo phase
-    unsigned pk[ROUNDS][3];
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int j = r * G + i;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) pk[r][q] = j < NR ? (unsigned)mech::RX_PACK[3 * j + q] : 0u;
-    }
-    if (i < N) {
-        L[mech::L_Y + i] = yi;
-        if (MODE == PARAM_VJP) L[mech::L_W + i] = wi;
-    }
-    lds_sync();
-    const S T = L[mech::L_Y];
-    const S lnT = log(T);
-    const S iT = chem_math::recip(T);
+    for (int t = 0; t < MOL; ++t)
+        if (t != s) c = c * L[L_C + a[t]];
+    return c;
+}
+
+// Species thermo, mixture sums and the species arrays in LDS: the part of an
+// evaluation before the reactions.  y: the lane's components; ywi: Y/W of its
+// species that no reaction changes.
+template <class S, bool DERIV>
+struct Thermo {
+    S cpR[R], HRT[R], yw[R], dcpR[DERIV ? R : 1];
+    S cpi[RI];
+    S rho, irho, Wbar, sig, cpm, dcpm;
+};
+
+template <class S, bool DERIV>
+__device__ __forceinline__ void thermo(const double* __restrict__ tab, double p, double ip, const S (&y)[R], const double (&ywi)[RI],
+                                       S* __restrict__ L, Mix<S>& x, Thermo<S, DERIV>& th)
+{
+    const int i = gl_local();
+    const S T = bc(y[0], 0);
+    x.T = T;
+    x.p = p;
+    x.lnT = log(T);
+    x.iT = chem_math::recip(T);
     const S T2 = T * T, T3 = T2 * T, T4 = T2 * T2;
-    S cpR = 0.0, HRT = 0.0, Gk = 0.0, dcpR = 0.0;
-    if (sp) {
-        const double* c = &mech::THERMO[k][T < mech::TMID[k] ? 0 : 1][0];
-        S a = T4 * c[4];
-        a = fma(T3, c[3], a);
-        a = fma(T2, c[2], a);
-        a = fma(T, c[1], a);
-        cpR = a + c[0];
-        a = T4 * c[8];
-        a = fma(T3, c[7], a);
-        a = fma(T2, c[6], a);
-        a = fma(T, c[5], a);
-        a = fma(iT, c[9], a);
-        HRT = a + c[0];
-        a = T4 * c[13];
-        a = fma(T3, c[12], a);
-        a = fma(T2, c[11], a);
-        a = fma(T, c[10], a);
-        a = fma(lnT, c[0], a);
-        a = fma(-iT, c[9], a);
-        Gk = a + c[14];
+    const double Tv = chem_math::value(T);
+    S sig = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int a = r * 16 + i;
+        th.yw[r] = y[r] * mech::PW[NPT + a];        // 1/W, 0 at T's position and past the last
+        sig = sig + th.yw[r];
+    }
+#pragma unroll
+    for (int q = 0; q < RI; ++q) sig = sig + ywi[q];
+    sig = gsum(sig);
+    th.sig = sig;
+    th.Wbar = chem_math::recip(sig);
+    th.rho = p * th.Wbar * x.iT * (1.0 / mech::RU);
+    th.irho = mech::RU * T * sig * ip;
+    x.ctot = p * x.iT * (1.0 / mech::RU);
+    x.lnPRT = mech::LN_PATM_R - x.lnT;
+    x.rtp = T * mech::RU_PATM;
+    x.prt = x.iT * mech::PATM_RU;
+    S cpm = 0.0, dcpm = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int a = r * 16 + i;
+        const double* c = tab + T_TH + (Tv < mech::PTMID[a] ? 0 : NPT) + a;
+        constexpr int st = 2 * NPT;
+        S v = T4 * c[4 * st];
+        v = fma(T3, c[3 * st], v);
+        v = fma(T2, c[2 * st], v);
+        v = fma(T, c[1 * st], v);
+        th.cpR[r] = v + c[0];
+        v = T4 * c[8 * st];
+        v = fma(T3, c[7 * st], v);
+        v = fma(T2, c[6 * st], v);
+        v = fma(T, c[5 * st], v);
+        v = fma(x.iT, c[9 * st], v);
+        th.HRT[r] = v + c[0];
+        v = T4 * c[13 * st];
+        v = fma(T3, c[12 * st], v);
+        v = fma(T2, c[11 * st], v);
+        v = fma(T, c[10 * st], v);
+        v = fma(x.lnT, c[0], v);
+        v = fma(-x.iT, c[9 * st], v);
+        const S Gk = v + c[14 * st];
+        if (DERIV) {
+            v = T3 * c[18 * st];
+            v = fma(T2, c[17 * st], v);
+            v = fma(T, c[16 * st], v);
+            th.dcpR[r] = v + c[15 * st];
+            dcpm = fma(th.dcpR[r], th.yw[r], dcpm);
+        }
+        cpm = fma(th.cpR[r], th.yw[r], cpm);
+        if (a >= 1 && a < NACT) {
+            const S gp = chem_math::exp_poly(Gk);
+            L[L_C + a - 1] = th.rho * th.yw[r];
+            L[L_GP + a - 1] = gp;
+            L[L_GM + a - 1] = chem_math::recip(gp);
+            L[L_H + a - 1] = th.HRT[r];
+            if (mech::HAS_LNKC) L[L_G + a - 1] = Gk;
+        }
+    }
+    // the species no reaction changes, and the neutral entry after the last:
+    // they cancel between the sides of any reaction, so only C and cp matter
+#pragma unroll
+    for (int q = 0; q < RI; ++q) {
+        const int m = q * 16 + i;
+        const int a = R * 16 + m;
+        const double* c = tab + T_TH + (Tv < mech::PTMID[a] ? 0 : NPT) + a;
+        constexpr int st = 2 * NPT;
+        S v = T4 * c[4 * st];
+        v = fma(T3, c[3 * st], v);
+        v = fma(T2, c[2 * st], v);
+        v = fma(T, c[1 * st], v);
+        th.cpi[q] = v + c[0];
+        cpm = fma(th.cpi[q], ywi[q], cpm);
+        if (DERIV) {
+            v = T3 * c[18 * st];
+            v = fma(T2, c[17 * st], v);
+            v = fma(T, c[16 * st], v);
+            dcpm = fma(v + c[15 * st], ywi[q], dcpm);
+        }
+        if (m <= NI) {
+            L[L_C + NA + m] = m < NI ? th.rho * ywi[q] : S(1.0);
+            L[L_GP + NA + m] = 1.0;
+            L[L_GM + NA + m] = 1.0;
+            L[L_H + NA + m] = 0.0;
+            if (mech::HAS_LNKC) L[L_G + NA + m] = 0.0;
+        }
+    }
+    th.cpm = gsum(cpm);
+    if (DERIV) th.dcpm = gsum(dcpm);
+}
+
+// A list word: byte offset from the first reaction array | coefficient << 24.
+__device__ __forceinline__ double list_value(const double* __restrict__ Q, int w)
+{
+    return *(const double*)((const char*)Q + (w & 0xffffff));
+}
+__device__ __forceinline__ double list_coef(int w) { return (double)(w >> 24); }
+
+// A stream of list words.  Lists stay rolled loops (unrolled, the 32-species
+// step was 220 KB of code, several times the instruction cache), LC lists side
+// by side: row t of the table holds word t of each of them for the 16 lanes.
+// run(len, use) walks the next len rows (an even number), calling use(q, w) for
+// word w of list q.  The words are loaded two rows ahead, across the lists that
+// follow one another in the table (which ends with two spare rows), so a stream
+// begun before other work has its first words when it is walked.  The address
+// passes through an empty asm, or the compiler would load whole tables ahead of
+// the substep loop and spill them.
+template <int LC>
+struct Stream {
+    typedef const __attribute__((address_space(1))) char gchar;
+    typedef const __attribute__((address_space(1))) int gint;
+    unsigned long long base;
+    int w[2][LC];
+
+    __device__ __forceinline__ int word(int row, int q) const
+    {
+        return *(gint*)((gchar*)base + 4u * (unsigned)gl() + (row * LC + q) * 64);
+    }
+    __device__ __forceinline__ explicit Stream(const int* table)
+    {
+        base = (unsigned long long)table;
+        asm volatile("" : "+s"(base));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < LC; ++q) w[h][q] = word(h, q);
+    }
+    template <class Use>
+    __device__ __forceinline__ void run(int len, Use&& use)
+    {
+#pragma unroll 1
+        for (int t = 0; t < len; t += 2) {
+            base += 2 * LC * 64;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int q = 0; q < LC; ++q) use(q, w[h][q]);
+#pragma unroll
+                for (int q = 0; q < LC; ++q) w[h][q] = word(h, q);
+            }
+        }
+    }
+};
+
+// Source terms f (the lane's components) at the state y; with JAC the lane's
+// rows of the Jacobian's first NC position columns in A.  Every lane of the
+// group calls it together.
+template <bool JAC, int NC>
+__device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, double ip, const double (&y)[R],
+                                    const double (&ywi)[RI], double* __restrict__ L, double (&f)[R],
+                                    double (&A)[R][NC])
+{
+    const int i = gl_local();
+    Mix<double> x;
+    Thermo<double, JAC> th;
+    if (i < NARR) L[L_A + i * NRW + NR] = 0.0;
+    Stream<4> list(&mech::RL[0]);
+    thermo<double, JAC>(tab, p, ip, y, ywi, L, x, th);
+    lds_sync();
+    double* const Q = L + L_A;
+    auto store = [&](int j, const Rate<double>& o) {
+        Q[j] = o.q;
         if (JAC) {
-            a = T3 * c[18];
-            a = fma(T2, c[17], a);
-            a = fma(T, c[16], a);
-            dcpR = a + c[15];
+            Q[NRW + j] = o.dqT;
+            Q[2 * NRW + j] = o.s;
+            Q[3 * NRW + j] = o.kf;
+            Q[4 * NRW + j] = o.kr;
         }
-    }
-    const double W = sp ? MW[k] : 0.0;
-    const double iW = sp ? MW[NS + k] : 0.0;
-    const S yw = sp ? yi * iW : S(0.0);
-    const S sig = gsum(yw);
-    const S Wbar = chem_math::recip(sig);
-    const S rho = p * Wbar * iT * (1.0 / mech::RU);
-    const S irho = mech::RU * T * sig * ip;
-    const S ctot = p * iT * (1.0 / mech::RU);
-    if (sp) {
-        L[mech::L_C + k] = rho * yw;
-        L[mech::L_G + k] = Gk;
-        L[mech::L_H + k] = HRT;
-    }
-    lds_sync();
-    const S lnPRT = mech::LN_PATM_R - lnT;
-    if (MODE == PARAM_VJP) {
-        const S rcp = T * sig * ip / gsum(cpR * yw);
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            const int j = r * G + i;
-            if (j < NR) reaction<S, MODE>(j, pk[r], par, L, T, lnT, iT, lnPRT, ctot, irho, rcp, p, g[r]);
-        }
-        return S(0.0);
-    }
+    };
 #pragma unroll 1
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int j = r * G + i;
-        unsigned pr[3] = {pk[0][0], pk[0][1], pk[0][2]};
-#pragma unroll
-        for (int q = 1; q < ROUNDS; ++q)
-#pragma unroll
-            for (int t = 0; t < 3; ++t) pr[t] = (q == r) ? pk[q][t] : pr[t];
-        if (j < NR) reaction<S, MODE>(j, pr, par, L, T, lnT, iT, lnPRT, ctot, irho, irho, p, g[0]);
-    }
-    lds_sync();
-    // species lists come padded to multiples of 4: four entries' loads in flight
-    const S* __restrict__ Q = L + mech::L_Q;
-    S wdot = 0.0;
-    if (sp) {
-        const int e1 = mech::SP_OFF[k + 1];
-        for (int e = mech::SP_OFF[k]; e < e1; e += 4) {
-            S q[4];
-            double nu[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                nu[u] = (double)mech::SP_NU[e + u];
-                q[u] = Q[mech::SP_RX[e + u]];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) wdot = nu[u] != 0.0 ? fma(nu[u], q[u], wdot) : wdot;
-        }
-    }
-    const S cpm = gsum(cpR * yw);
-    const S hw = gsum(HRT * wdot);
-    const S icpm = chem_math::recip(cpm);
-    const S rcpinv = T * sig * ip * icpm;
-    const S fT = -mech::RU * T * hw * rcpinv;
-    const S fk = W * (irho * wdot);
-    const S fi = sp ? fk : (i == 0 ? fT : S(0.0));
-    if (!JAC) return fi;
-
-    // Row k of the concentration Jacobian: Jc_km = d wdot_k / d C_m (fixed T)
-    // and wT_k = d wdot_k / dT (fixed C) in column NS.  The species partials
-    // of the lane's reactions go into its own LDS row by atomic adds (one
-    // lane per address, applied in program order: reproducible); the
-    // third-body part, dense over m, accumulates in registers.
-    S* Jr = L + mech::L_J + k * JW;
-    if (sp) {
-#pragma unroll
-        for (int m = 0; m <= NS; ++m) Jr[m] = 0.0;
-    }
-    lds_sync();
-    if (sp) {
-        const S* __restrict__ Pb = L + mech::L_P;
-        const int e1 = mech::SP_OFF[k + 1];
-        for (int e = mech::SP_OFF[k]; e < e1; e += 4) {
-            // one round of independent table loads per four entries (slot,
-            // coefficient and slot species packed per entry), then the partials
-            unsigned w[4][3];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) w[u][q] = (unsigned)mech::SP_JPACK[3 * (e + u) + q];
-            int j[4], ms[4][NSLOT];
-            double nu[4];
-            S P[4][NSLOT + 1];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                j[u] = (int)(w[u][0] & 0xffffu);
-                nu[u] = (double)(signed char)(w[u][0] >> 16);
-#pragma unroll
-                for (int s = 0; s < NSLOT; ++s) ms[u][s] = (int)((w[u][1 + s / 4] >> (8 * (s % 4))) & 255u) - 1;
-#pragma unroll
-                for (int s = 0; s <= NSLOT; ++s) P[u][s] = Pb[j[u] * PW + s];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (nu[u] == 0.0) continue;
-#pragma unroll
-                for (int s = 0; s < NSLOT; ++s)
-                    if (ms[u][s] >= 0) lds_add(&Jr[ms[u][s]], nu[u] * P[u][s]);
-                lds_add(&Jr[NS], nu[u] * P[u][NSLOT]);
+    for (int j = i; j < 16 * mech::FULL_ROUNDS; j += 16) {
+        if (j < NR) {
+            Rate<double> o;
+            int ra[MOLR], pa[MOLP], misc;
+            reaction<double, true, JAC>(j, tab, L, x, o, ra, pa, misc);
+            store(j, o);
+            const int kind = misc & 7;
+            if (JAC && NTB > 0 && kind >= 1 && kind <= 4) {
+                const int t = (misc >> 16) & 0xffff;
+                L[L_X + t] = o.dM;
+                for (int q = 0; q < MAXP; ++q) L[L_X + NTB + t * MAXP + q] = tab[T_TBC + q * NTB + t] * o.dM;
             }
         }
     }
-    S R[NS + 1];
+#pragma unroll 2
+    for (int j = 16 * mech::FULL_ROUNDS + i; j < NR; j += 16) {
+        Rate<double> o;
+        int ra[MOLR], pa[MOLP], misc;
+        reaction<double, false, JAC>(j, tab, L, x, o, ra, pa, misc);
+        store(j, o);
+    }
+    lds_sync();
+    double wd[R], wT[R], Sk[R];
 #pragma unroll
-    for (int m = 0; m <= NS; ++m) R[m] = 0.0;
-    // the efficiencies by scalar loads at an opaque offset, so they are loaded
-    // here, one reaction at a time, not hoisted out of the substep loop
-    mech::cdbl* EF = (mech::cdbl*)&mech::EFF[0] + z;
-    // the lane's coefficients in all of them: one load per eight reactions,
-    // ahead of the loop (4-bit fields, coefficient + 8)
-    unsigned tbw[mech::NTBW];
+    for (int r = 0; r < R; ++r) wd[r] = wT[r] = Sk[r] = 0.0;
+    static_for<0, R>([&](auto rc) {
+        constexpr int r = decltype(rc)::v;
+        list.run(mech::WLEN[r], [&](int, int w) {
+            const double nu = list_coef(w);
+            wd[r] = fma(nu, list_value(Q, w), wd[r]);
+            if (JAC) {
+                wT[r] = fma(nu, list_value(Q + NRW, w), wT[r]);
+                Sk[r] = fma(nu, list_value(Q + 2 * NRW, w), Sk[r]);
+            }
+        });
+    });
+    double hw = 0.0;
 #pragma unroll
-    for (int q = 0; q < mech::NTBW; ++q) tbw[q] = sp ? (unsigned)mech::NU_TB4[k * mech::NTBW + q] : 0x88888888u;
+    for (int r = 0; r < R; ++r) hw = fma(th.HRT[r], wd[r], hw);     // T's position has no terms: wd = 0
+    hw = gsum(hw);
+    const double icpm = chem_math::recip(th.cpm);
+    const double rcpinv = x.T * th.sig * ip * icpm;
+    const double fT = -mech::RU * x.T * hw * rcpinv;
 #pragma unroll
-    for (int q = 0; q < mech::NTBW; ++q) {
-#pragma unroll 1
-        for (int t = 8 * q; t < mech::NTB && t < 8 * q + 8; ++t) {
-            const double nut = (double)((int)((tbw[q] >> (4 * (t - 8 * q))) & 15u) - 8);
-            const S d = nut * L[mech::L_P + mech::TB_SLOT[t] * PW + NSLOT + 1];
-            mech::cdbl* eff = EF + t * NS;
+    for (int r = 0; r < R; ++r) f[r] = mech::PW[r * 16 + i] * (th.irho * wd[r]);
+    f[0] = i == 0 ? fT : f[0];
+    if constexpr (JAC) {
+        lds_sync();
+        // the partials d q / d C of every slot, over the arrays just read (a
+        // reaction's rate constants are read before its own words of the
+        // arrays they sit in are overwritten)
+        const int* const words = (const int*)(tab + T_INT) + I_WORDS;
+        Stream<mech::JGW> cols(&mech::JL[0]);
+#pragma unroll 2
+        for (int j = i; j < NR; j += 16) {
+            int ra[MOLR], pa[MOLP];
 #pragma unroll
-            for (int m = 0; m < NS; ++m) R[m] = fma(eff[m], d, R[m]);
+            for (int s = 0; s < MOLR; ++s) ra[s] = (words[(s / 4) * NR + j] >> (8 * (s % 4))) & 255;
+#pragma unroll
+            for (int s = 0; s < MOLP; ++s) pa[s] = (words[(WR + s / 4) * NR + j] >> (8 * (s % 4))) & 255;
+            const double kf = Q[3 * NRW + j], kr = Q[4 * NRW + j];
+#pragma unroll
+            for (int s = 0; s < MOLR; ++s) Q[s * NRW + j] = others<double, MOLR>(L, ra, s, kf);
+#pragma unroll
+            for (int s = 0; s < MOLP; ++s) Q[(MOLR + s) * NRW + j] = others<double, MOLP>(L, pa, s, -kr);
         }
+        lds_sync();
+        // concentration Jacobian Jc_km = d wdot_k / d C_m: the third-body part
+        // common to all columns, then each column's slots and corrections
+        double D[R], own[R];
+        static_for<0, R>([&](auto rc) {
+            constexpr int r = decltype(rc)::v;
+            D[r] = 0.0;
+            list.run(mech::DLEN[r], [&](int, int w) { D[r] = fma(list_coef(w), list_value(Q, w), D[r]); });
+        });
+        static_for<0, R>([&](auto rc) {
+            constexpr int r = decltype(rc)::v;
+            own[r] = D[r];
+            list.run(mech::DGLEN[r], [&](int, int w) { own[r] = fma(list_coef(w), list_value(Q, w), own[r]); });
+        });
+        // (columns in groups of similar list length, those of the step's
+        // unknowns first)
+        static_for<0, NC == NACT ? mech::JGACT : mech::JGALL>([&](auto gc) {
+            constexpr int g = decltype(gc)::v, r = mech::JGROW[g];
+            double acc[mech::JGW];
+#pragma unroll
+            for (int q = 0; q < mech::JGW; ++q) acc[q] = D[r];
+            cols.run(mech::JGLEN[g], [&](int q, int w) { acc[q] = fma(list_coef(w), list_value(Q, w), acc[q]); });
+            static_for<0, mech::JGW>([&](auto qc) {
+                constexpr int q = decltype(qc)::v, m = mech::JGCOL[g * mech::JGW + q];
+                if constexpr (m >= 0) A[r][1 + m] = m < NA && (m + 1) / 16 == r && (m + 1) % 16 == i ? own[r] : acc[q];
+            });
+        });
+        // chain rule to (T, Y), with S_k = sum_l Jc_kl C_l:
+        //   J_km = (W_k/W_m) Jc_km + (Wbar/W_m)(f_k - W_k S_k / rho)
+        //   J_k0 = (W_k / rho)(wT_k - S_k / T) + f_k / T
+        //   J_0m = -R T (rho HJ_m - Wbar HS) / (W_m rho cp) - f_T (cp_m / cp - Wbar / W_m)
+        //   J_00 = -R (cpw + T HwT - HS) / (rho cp) - f_T (dcp / cp - 1/T)
+        // HJ_m = sum_k H_k/RT Jc_km, HS = sum_k H_k/RT S_k, HwT = sum_k H_k/RT wT_k,
+        // cpw = sum_k cp_k/R wdot_k
+        double HS = 0.0, HwT = 0.0, cpw = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            HS = fma(th.HRT[r], Sk[r], HS);
+            HwT = fma(th.HRT[r], wT[r], HwT);
+            cpw = fma(th.cpR[r], wd[r], cpw);
+        }
+        HS = gsum(HS);
+        HwT = gsum(HwT);
+        cpw = gsum(cpw);
+        const double RT = mech::RU * x.T;
+        const double icp = icpm * (1.0 / mech::RU);
+        const double dcp = mech::RU * th.dcpm;
+        double wg[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double W = mech::PW[r * 16 + i];
+            wg[r] = th.Wbar * fma(-W, Sk[r] * th.irho, f[r]);
+            A[r][0] = fma(W * th.irho, wT[r] - Sk[r] * x.iT, f[r] * x.iT);
+        }
+        const double J00 = -mech::RU * (cpw + x.T * HwT - HS) * rcpinv - fT * (dcp * icp - x.iT);
+        A[0][0] = i == 0 ? J00 : A[0][0];
+#pragma unroll
+        for (int m = 0; m < NC - 1; ++m) {
+            double HJ = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) HJ = fma(th.HRT[r], A[r][1 + m], HJ);
+            HJ = gsum(HJ);
+            // cp/R of species m, from the lane that holds its position
+            const double cpm_m = m < NA ? bc(th.cpR[(m + 1) / 16 < R ? (m + 1) / 16 : 0], (m + 1) % 16)
+                                        : bc(th.cpi[m >= NA ? (m - NA) / 16 : 0], (m - NA) % 16);
+            const double iW = mech::IWM[m];
+            const double t = fma(th.rho, HJ, -th.Wbar * HS) * (-RT * rcpinv);
+            const double u = fma(cpm_m, icp * mech::RU, -th.Wbar);
+            const double J0m = fma(-fT, u, t) * iW;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int a = r * 16 + i;
+                double v = fma(A[r][1 + m], mech::PW[a], wg[r]) * iW;
+                if (r == 0) v = i == 0 ? J0m : v;
+                if (r * 16 + 15 >= NACT) v = a < NACT ? v : 0.0;
+                A[r][1 + m] = v;
+            }
+        }
+        if (R * 16 > NACT) A[R - 1][0] = (R - 1) * 16 + i < NACT ? A[R - 1][0] : 0.0;
     }
-    lds_sync();
-    if (sp) {
-#pragma unroll
-        for (int m = 0; m <= NS; ++m) R[m] += Jr[m];
-#pragma unroll
-        for (int m = 0; m <= NS; ++m) Jr[m] = R[m];
-    }
-    lds_sync();
-    // chain rule to (T, Y), with S_k = sum_l Jc_kl C_l:
-    //   J_km = (W_k/W_m) Jc_km + (Wbar/W_m)(f_k - W_k S_k / rho)
-    //   J_k0 = (W_k / rho)(wT_k - S_k / T) + f_k / T
-    //   J_0m = -R T (rho HJ_m - Wbar HS) / (W_m rho cp) - f_T (cp_m / cp - Wbar / W_m)
-    //   J_00 = -R (cpw + T HwT - HS) / (rho cp) - f_T (dcp / cp - 1/T)
-    // HJ_m = sum_k H_k/RT Jc_km, HS = sum_k H_k/RT S_k, HwT = sum_k H_k/RT wT_k,
-    // cpw = sum_k cp_k/R wdot_k
-    S Sk = 0.0, wT = 0.0;
-    if (sp) {
-#pragma unroll
-        for (int m = 0; m < NS; ++m) Sk = fma(R[m], L[mech::L_C + m], Sk);
-        wT = R[NS];
-    }
-    const S HS = gsum(HRT * Sk);
-    const S HwT = gsum(HRT * wT);
-    const S cpw = gsum(cpR * wdot);
-    const S dcpm = gsum(dcpR * yw);
-    const S RT = mech::RU * T;
-    const S icp = icpm * (1.0 / mech::RU);
-    const S dcp = mech::RU * dcpm;
-    if (sp) {
-        S HJ = 0.0;
-        for (int l = 0; l < NS; ++l) HJ = fma(L[mech::L_H + l], L[mech::L_J + l * JW + k], HJ);
-        const S t = fma(rho, HJ, -Wbar * HS) * (-RT * rcpinv);
-        const S u = fma(cpR, icp * mech::RU, -Wbar);
-        L[mech::L_T0 + k] = fma(-fT, u, t) * iW;
-    }
-    lds_sync();
-    if (sp) {
-        const S gk = fma(-W, Sk * irho, fk);
-        const S wg = Wbar * gk;
-#pragma unroll
-        for (int m = 0; m < NS; ++m) A[1 + m] = fma(R[m], W, wg) * MW[NS + m];
-        A[0] = fma(W * irho, wT - Sk * iT, fk * iT);
-    } else if (i == 0) {
-        A[0] = -mech::RU * (cpw + T * HwT - HS) * rcpinv - fT * (dcp * icp - iT);
-#pragma unroll
-        for (int m = 0; m < NS; ++m) A[1 + m] = L[mech::L_T0 + m];
-    } else {
-#pragma unroll
-        for (int m = 0; m < N; ++m) A[m] = 0.0;
-    }
-    return fi;
 }
 
-// LU with partial pivoting of the group's matrix (row i in lane i), in place:
-// multipliers below the diagonal, U above, reciprocal pivots on the diagonal.
-// PV: LDS scratch of the cell for the pivot row (N doubles) and, after it, the
-// pivot indices: piv[k] is the row swapped into k at step k (LINPACK order,
-// the lowest row index among equal magnitudes).  Bit k of the result: some
-// group of the wave swapped at step k.
-__device__ __forceinline__ unsigned long long lu(double (&A)[N], bool& ok, double* __restrict__ PV)
+// ---- linear algebra of the group's NACT x NACT matrix ----
+// A: rows by position; after lu() the multipliers below the diagonal (zero in
+// the lanes on and above it within the diagonal blocks), and above it the
+// rows of U divided by their pivots; U's diagonal blocks in UD; D: 1 / pivot.
+// Row interchanges move whole rows, so a solve permutes its right-hand side
+// once (src: the position whose row came here).
+struct Factors {
+    double A[R][NACT];
+    double UD[R][16];
+    double D[R];
+    int src[R];
+    bool swapped;
+};
+
+// LU with partial pivoting (the lowest position among equal magnitudes).
+__device__ __forceinline__ void lu(Factors& F, bool& ok)
 {
     const int i = gl_local();
-    double* PR = PV;
-    int* piv = (int*)(PV + N);      // read by the solves only on a swap
-    unsigned long long swaps = 0ull;
     ok = true;
+    F.swapped = false;
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        // the column's largest magnitude (a max is exact in any order), then the
-        // lowest row that reaches it
-        const double v = (i >= k && i < N) ? fabs(A[k]) : -1.0;
-        const double vmax = gmax(v);
-        const unsigned long long hit = gbits(__ballot(v == vmax));
-        int idx = hit ? __builtin_ctzll(hit) : k;
-        if (!(vmax > 0.0)) idx = k;
-        if (i == 0) piv[k] = idx;
+    for (int r = 0; r < R; ++r) {
+        F.src[r] = r * 16 + i;
+        F.D[r] = 0.0;
+    }
+    static_for<0, NACT>([&](auto kc) {
+        constexpr int k = decltype(kc)::v, rk = k / 16, lk = k % 16;
+        double v[R], vm = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = -1.0;
+#pragma unroll
+        for (int r = rk; r < R; ++r) {
+            v[r] = fabs(F.A[r][k]);
+            if (r == rk) v[r] = i >= lk ? v[r] : -1.0;
+            vm = r == rk ? v[r] : fmax(vm, v[r]);
+        }
+        const double vmax = gmax(vm);
         ok = ok && (vmax > 0.0);
-        if (__any(idx != k)) {
-            swaps |= 1ull << k;
-            const int src = (i == k) ? idx : (i == idx ? k : i);
+        // rows move only if some cell's largest entry is not on the diagonal
+        const unsigned long long diag = 0x0001000100010001ull << lk;
+        const unsigned long long here = __ballot(v[rk] == vmax) & diag;
+        if (here != (__ballot(true) & diag)) {
+            F.swapped = true;
+            int idx = k;
+            bool found = false;
 #pragma unroll
-            for (int j = k; j < N; ++j) A[j] = gather(A[j], src);
-        }
-        // the pivot row: with one cell per wave read straight from the pivot
-        // lane into scalar registers; otherwise through LDS (one lane writes
-        // it, every lane of the group reads it)
-        double prow[N];
-        if constexpr (G == 64) {
-#pragma unroll
-            for (int j = k; j < N; ++j) prow[j] = bcast(A[j], k);
-        } else {
-            if (i == k) {
-#pragma unroll
-                for (int j = k; j < N; ++j) PR[j] = A[j];
+            for (int r = rk; r < R; ++r) {
+                const unsigned bits = (unsigned)(__ballot(v[r] == vmax) >> gbase()) & 0xffffu;
+                if (!found && bits) {
+                    idx = r * 16 + __builtin_ctz(bits);
+                    found = true;
+                }
             }
-            lds_sync();
+            if (!(vmax > 0.0)) idx = k;
+            const int li = idx & 15, ri = idx >> 4;
 #pragma unroll
-            for (int j = k; j < N; ++j) prow[j] = PR[j];
-            lds_sync();
+            for (int c = 0; c < NACT; ++c) {
+                double s = F.A[rk][c];
+#pragma unroll
+                for (int r = rk + 1; r < R; ++r) s = ri == r ? F.A[r][c] : s;
+                const double top = bc(F.A[rk][c], lk), low = gather(s, li);
+#pragma unroll
+                for (int r = rk; r < R; ++r) F.A[r][c] = (i == li && ri == r) ? top : F.A[r][c];
+                F.A[rk][c] = i == lk ? low : F.A[rk][c];
+            }
+            {
+                int s = F.src[rk];
+#pragma unroll
+                for (int r = rk + 1; r < R; ++r) s = ri == r ? F.src[r] : s;
+                const int top = __shfl(F.src[rk], gbase() + lk, 64), low = __shfl(s, gbase() + li, 64);
+#pragma unroll
+                for (int r = rk; r < R; ++r) F.src[r] = (i == li && ri == r) ? top : F.src[r];
+                F.src[rk] = i == lk ? low : F.src[rk];
+            }
         }
-        const double rp = chem_math::recip(prow[k]);
-        if (i == k) {
-            A[k] = rp;
-        } else if (i > k && i < N) {
-            const double l = A[k] * rp;
-            A[k] = l;
+        const double rp = chem_math::recip(bc(F.A[rk][k], lk));
+        double l[R];
 #pragma unroll
-            for (int j = k + 1; j < N; ++j) A[j] = fma(-l, prow[j], A[j]);
+        for (int r = rk; r < R; ++r) {
+            l[r] = F.A[r][k] * rp;
+            if (r == rk) l[r] = i > lk ? l[r] : 0.0;
+        }
+        F.D[rk] = i == lk ? rp : F.D[rk];
+#pragma unroll
+        for (int c = k + 1; c < NACT; ++c) {
+            const double pc = bc(F.A[rk][c], lk);
+#pragma unroll
+            for (int r = rk; r < R; ++r) F.A[r][c] = fma(-l[r], pc, F.A[r][c]);
+        }
+        // column k: the multipliers below, U above (rows of this block only)
+#pragma unroll
+        for (int r = rk; r < R; ++r) F.A[r][k] = r == rk ? (i > lk ? l[r] : F.A[r][k]) : l[r];
+    });
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int c = 0; c < NACT; ++c) {
+            const int rc = c / 16, lc = c % 16;
+            if (rc == r) {
+                F.UD[r][lc] = i < lc ? F.A[r][c] * F.D[r] : 0.0;
+                F.A[r][c] = i > lc ? F.A[r][c] : 0.0;
+            } else if (rc > r) {
+                F.A[r][c] = F.A[r][c] * F.D[r];
+            }
         }
     }
-    return swaps;
 }
 
-// Solve (LU) x = b for the group's vector b (component i in lane i).
-__device__ __forceinline__ double solve(const double (&A)[N], const double* __restrict__ PV,
-                                        unsigned long long swaps, double b)
+// b[r] <- b at position src[r]
+__device__ __forceinline__ void permute(const int (&src)[R], double (&b)[R])
 {
-    const int i = gl_local();
-    const int* piv = (const int*)(PV + N);
+    double n[R];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        if (swaps & (1ull << k)) {
-            const int pk = piv[k];
-            b = gather(b, (i == k) ? pk : (i == pk ? k : i));
+    for (int r = 0; r < R; ++r) {
+        n[r] = gather(b[0], src[r] & 15);
+#pragma unroll
+        for (int q = 1; q < R; ++q) {
+            const double g = gather(b[q], src[r] & 15);
+            n[r] = (src[r] >> 4) == q ? g : n[r];
         }
-        const double zk = bcast(b, k);
-        if (i > k && i < N) b = fma(-A[k], zk, b);
     }
 #pragma unroll
-    for (int k = N - 1; k >= 0; --k) {
-        if (i == k) b *= A[k];
-        const double zk = bcast(b, k);
-        if (i < k) b = fma(-A[k], zk, b);
-    }
-    return b;
+    for (int r = 0; r < R; ++r) b[r] = n[r];
 }
 
-// One RODAS4 step from y (component yi) with step h; false if the step
-// matrix is singular or a result is not finite.  L: the cell's scratch, PV:
-// its pivot scratch.
-__device__ __forceinline__ bool ros_step(const double* __restrict__ par, double p, double ip, double yi, double h,
-                                         double rtol, double atol, double* __restrict__ L, double* __restrict__ PV,
-                                         double& ynew, double& errn)
+// Solve M x = b for the group's vector b.
+__device__ __forceinline__ void solve(const Factors& F, double (&b)[R])
+{
+    if (F.swapped) permute(F.src, b);
+    static_for<0, NACT - 1>([&](auto kc) {
+        constexpr int k = decltype(kc)::v, rk = k / 16;
+        const double z = bc(b[rk], k % 16);
+#pragma unroll
+        for (int r = rk; r < R; ++r) b[r] = fma(-F.A[r][k], z, b[r]);
+    });
+#pragma unroll
+    for (int r = 0; r < R; ++r) b[r] *= F.D[r];
+    static_for<0, NACT - 1>([&](auto kc) {
+        constexpr int k = NACT - 1 - decltype(kc)::v, rk = k / 16;
+        const double z = bc(b[rk], k % 16);
+#pragma unroll
+        for (int r = 0; r <= rk; ++r) b[r] = fma(r == rk ? -F.UD[r][k % 16] : -F.A[r][k], z, b[r]);
+    });
+}
+
+// One RODAS4 step from y with step h; false if the step matrix is singular or
+// a result is not finite.  L: the cell's scratch.
+__device__ __forceinline__ bool ros_step(const double* __restrict__ tab, double p, double ip, const double (&y)[R],
+                                         const double (&ywi)[RI], const double (&yi)[RI], double h, double rtol,
+                                         double atol, double* __restrict__ L, double (&ynew)[R], double& errn)
 {
     const int i = gl_local();
-    double A[N];
-    double g[ROUNDS][3];
-    const double f0 = rhs<double, F_JAC>(par, p, ip, yi, L, A, 0.0, g);
+    Factors F;
+    double u[Rodas4::S - 1][R], f[R], us[R];
+    rhs<true, NACT>(tab, p, ip, y, ywi, L, f, F.A);
     const double hinv = chem_math::recip(h);
     const double ghinv = hinv * (1.0 / Rodas4::gamma);
 #pragma unroll
-    for (int j = 0; j < N; ++j) A[j] = (j == i ? ghinv : 0.0) - A[j];
-    bool ok;
-    const unsigned long long swaps = lu(A, ok, PV);
-    double u[Rodas4::S];
-    u[0] = solve(A, PV, swaps, f0);
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int s = 1; s < Rodas4::S; ++s) u[s] = 0.0;
-    double dummy[N];
+        for (int c = 0; c < NACT; ++c) F.A[r][c] = (r * 16 + i == c ? ghinv : 0.0) - F.A[r][c];
+    bool ok;
+    lu(F, ok);
+    solve(F, f);
+#pragma unroll
+    for (int s = 0; s < Rodas4::S - 1; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[s][r] = s == 0 ? f[r] : 0.0;
     // one copy of the source-term code for the five later stages (the kernel
     // stays inside the instruction cache); stage vectors stay in registers
 #pragma unroll 1
     for (int s = 1; s < Rodas4::S; ++s) {
-        double Ys = yi, acc = 0.0;
+        double Ys[R], acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            Ys[r] = y[r];
+            acc[r] = 0.0;
+        }
+        // (the tableau's rows are zero from the stage on, as are the vectors)
 #pragma unroll
         for (int j = 0; j < Rodas4::S - 1; ++j) {
-            if (j < s) {
-                Ys = fma(RA[s][j], u[j], Ys);
-                acc = fma(RC[s][j], u[j], acc);
+            const double ra = RA[s][j], rc = RC[s][j];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                Ys[r] = fma(ra, u[j][r], Ys[r]);
+                acc[r] = fma(rc, u[j][r], acc[r]);
             }
         }
-        if (s == Rodas4::S - 1) ynew = Ys;
-        const double fs = rhs<double, F_ONLY>(par, p, ip, Ys, L, dummy, 0.0, g);
-        const double us = solve(A, PV, swaps, fma(acc, hinv, fs));
 #pragma unroll
-        for (int j = 1; j < Rodas4::S; ++j)
-            if (j == s) u[j] = us;
+        for (int r = 0; r < R; ++r) ynew[r] = Ys[r];        // the last stage's: y_new = Y_6 + u_6
+        double none[R][1];
+        rhs<false, 1>(tab, p, ip, Ys, ywi, L, us, none);
+#pragma unroll
+        for (int r = 0; r < R; ++r) us[r] = fma(acc[r], hinv, us[r]);
+        solve(F, us);
+#pragma unroll
+        for (int j = 1; j < Rodas4::S - 1; ++j)
+            if (j == s)
+#pragma unroll
+                for (int r = 0; r < R; ++r) u[j][r] = us[r];
     }
-    ynew += u[Rodas4::S - 1];
-    const double sc = atol + rtol * fmax(fabs(yi), fabs(ynew));
-    const double e = u[Rodas4::S - 1] * chem_math::recip(sc);
-    errn = sqrt(gsum(i < N ? e * e : 0.0) * (1.0 / N));
-    const bool bad = gany(i < N && !finite(ynew));
-    return ok && !bad && finite(errn);
+    double e2 = 0.0;
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        ynew[r] += us[r];
+        const double sc = atol + rtol * fmax(fabs(y[r]), fabs(ynew[r]));
+        const double e = us[r] * chem_math::recip(sc);
+        const bool in = r * 16 + i < NACT;
+        e2 = in ? fma(e, e, e2) : e2;
+        bad = bad || (in && !finite(ynew[r]));
+    }
+    // species no reaction changes have no error, except that a zero scale
+    // fails the step (0 / 0) as it does in any other component
+#pragma unroll
+    for (int q = 0; q < RI; ++q) {
+        const double e = 0.0 * chem_math::recip(atol + rtol * fabs(yi[q]));
+        if (q * 16 + i < NI) e2 = fma(e, e, e2);
+    }
+    errn = sqrt(gsum(e2) * (1.0 / N));
+    return ok && !gany(bad) && finite(errn);
 }
 
-// Per-group integration state (component yi in lane i, the rest replicated).
+// Per-group integration state (the lane's components, the rest replicated).
 struct Cell {
-    double y, p, ip, t, h;
+    double y[R], yi[RI], ywi[RI];
+    double p, ip, t, h;
     int nacc, nrej, status;
     bool rej_last, done;
 };
@@ -722,7 +975,21 @@ struct Cell {
 __device__ __forceinline__ void cell_begin(Cell& c, double T, double p, const double* __restrict__ Y, double h0)
 {
     const int i = gl();
-    c.y = i == 0 ? T : (i <= NS ? Y[i - 1] : 0.0);
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int k = mech::PSPEC[r * 16 + i];
+        c.y[r] = k >= 0 ? Y[k] : 0.0;
+        if (r == 0 && i == 0) c.y[r] = T;
+        bad = bad || !finite(c.y[r]);
+    }
+#pragma unroll
+    for (int q = 0; q < RI; ++q) {
+        const int k = mech::PSPEC[R * 16 + q * 16 + i];
+        c.yi[q] = k >= 0 ? Y[k] : 0.0;
+        c.ywi[q] = c.yi[q] * mech::PW[NPT + R * 16 + q * 16 + i];
+        bad = bad || !finite(c.yi[q]);
+    }
     c.p = p;
     c.ip = 1.0 / p;
     c.t = 0.0;
@@ -730,15 +997,15 @@ __device__ __forceinline__ void cell_begin(Cell& c, double T, double p, const do
     c.nacc = 0;
     c.nrej = 0;
     c.rej_last = false;
-    const bool bad = gany(!finite(c.y)) || !(T > 0.0) || !(p > 0.0) || !finite(p);
+    bad = gany(bad) || !(T > 0.0) || !(p > 0.0) || !finite(p);
     c.status = bad ? chem::CELL_BADINPUT : chem::CELL_OK;
     c.done = bad;
 }
 
 // One attempted substep with the controller of the one-cell-per-lane form;
 // returns the step size if the step was accepted, else 0.
-__device__ __forceinline__ double cell_attempt(Cell& c, const double* __restrict__ par, const StepArgs& a,
-                                               double* __restrict__ L, double* __restrict__ PV)
+__device__ __forceinline__ double cell_attempt(Cell& c, const double* __restrict__ tab, const StepArgs& a,
+                                               double* __restrict__ L)
 {
     if (c.done) return 0.0;
     if (c.nacc + c.nrej >= a.max_substeps) {
@@ -757,10 +1024,11 @@ __device__ __forceinline__ double cell_attempt(Cell& c, const double* __restrict
         h = a.dt - c.t;
         last = true;
     }
-    double ynew, en;
-    const bool ok = ros_step(par, c.p, c.ip, c.y, h, a.rtol, a.atol, L, PV, ynew, en);
+    double ynew[R], en;
+    const bool ok = ros_step(tab, c.p, c.ip, c.y, c.ywi, c.yi, h, a.rtol, a.atol, L, ynew, en);
     if (ok && en <= 1.0) {
-        c.y = ynew;
+#pragma unroll
+        for (int r = 0; r < R; ++r) c.y[r] = ynew[r];
         c.t = last ? a.dt : c.t + h;
         double fac = 0.9 * chem::inv_root4(fmax(en, 1e-16));
         fac = fmin(6.0, fmax(0.2, fac));
@@ -777,15 +1045,29 @@ __device__ __forceinline__ double cell_attempt(Cell& c, const double* __restrict
     return 0.0;
 }
 
+// the lane's components of a state-sized vector to out[0] (T) and out_Y
+__device__ __forceinline__ void put(const double (&y)[R], const double (&yi)[RI], double* __restrict__ T,
+                                    double* __restrict__ Y)
+{
+    const int i = gl();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int k = mech::PSPEC[r * 16 + i];
+        if (k >= 0) Y[k] = y[r];
+        if (r == 0 && i == 0) *T = y[0];
+    }
+#pragma unroll
+    for (int q = 0; q < RI; ++q) {
+        const int k = mech::PSPEC[R * 16 + q * 16 + i];
+        if (k >= 0) Y[k] = yi[q];
+    }
+}
+
 __device__ __forceinline__ void cell_store(const Cell& c, double* __restrict__ T, double* __restrict__ Y, long cell,
                                            int* status, int* nacc, int* nrej)
 {
-    const int i = gl();
-    if (c.status != chem::CELL_BADINPUT) {
-        if (i == 0) T[cell] = c.y;
-        else if (i <= NS) Y[cell * NS + i - 1] = c.y;
-    }
-    if (i == 0) {   // the per-cell counters only where someone reads them (null: not asked for)
+    if (c.status != chem::CELL_BADINPUT) put(c.y, c.yi, T + cell, Y + cell * NS);
+    if (gl() == 0) {   // the per-cell counters only where someone reads them (null: not asked for)
         if (status) status[cell] = c.status;
         if (nacc) nacc[cell] = c.nacc;
         if (nrej) nrej[cell] = c.nrej;
@@ -793,206 +1075,429 @@ __device__ __forceinline__ void cell_store(const Cell& c, double* __restrict__ T
 }
 
 // ---- discrete adjoint of the frozen-step map (see the one-cell-per-lane form
-// for the algebra); every vector one component per lane ----
+// for the algebra) ----
 
-// Solve M^T x = b with the factors of lu(): U^T y = b forward, then, for
-// k = N-1 .. 0, y_k -= sum_{i>k} l_ik y_i and swap y_k, y_piv[k].  The row
-// sums a column needs are group sums.
-__device__ __forceinline__ double solve_t(const double (&A)[N], const double* __restrict__ PV,
-                                          unsigned long long swaps, double b)
+// Solve M^T x = b: the sums over rows that a column needs are group sums.
+// scr: 16 R doubles of the cell's scratch.
+__device__ __forceinline__ void solve_t(const Factors& F, double (&b)[R], double* __restrict__ scr)
 {
     const int i = gl_local();
-    const int* piv = (const int*)(PV + N);
-    double y = b;
+    // U'^T (unit lower), then the pivots
+    static_for<1, NACT>([&](auto kc) {
+        constexpr int k = decltype(kc)::v, rk = k / 16, lk = k % 16;
+        double s = F.UD[rk][lk] * b[rk];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double s = gsum(i < k ? A[k] * y : 0.0);
-        if (i == k) y = (y - s) * A[k];
+        for (int r = 0; r < rk; ++r) s = fma(F.A[r][k], b[r], s);
+        s = gsum(s);
+        b[rk] = i == lk ? b[rk] - s : b[rk];
+    });
+#pragma unroll
+    for (int r = 0; r < R; ++r) b[r] *= F.D[r];
+    // L^T
+    static_for<0, NACT - 1>([&](auto kc) {
+        constexpr int k = NACT - 2 - decltype(kc)::v, rk = k / 16, lk = k % 16;
+        double s = 0.0;
+#pragma unroll
+        for (int r = rk; r < R; ++r) s = fma(F.A[r][k], b[r], s);
+        s = gsum(s);
+        b[rk] = i == lk ? b[rk] - s : b[rk];
+    });
+    if (F.swapped) {    // x at position src is what this lane holds
+#pragma unroll
+        for (int r = 0; r < R; ++r) scr[F.src[r]] = b[r];
+        lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) b[r] = scr[r * 16 + i];
+        lds_sync();
     }
+}
+
+// what a transposed product leaves behind of S: the value, or the tangent
+__device__ __forceinline__ double take(double x) { return x; }
+__device__ __forceinline__ double take(const Dual& x) { return x.d; }
+
+// v += J(y)^T w (S = double), or D_u[J(y)^T w] with y a dual number along u;
+// vi: the same for the species no reaction changes; g: the products w . df/dq
+// d q / d(ln A, b, Ea) of the lane's reactions, or their tangents.  J is never
+// formed: every entry is assembled from the reactions' partials, so the
+// product needs each reaction's weights wY = sum nu W w and hs = sum nu H/RT
+// and two column sums colA_m = sum wY dq/dC_m, colH_m = sum hs dq/dC_m:
+//   v_{1+m} = (colA_m + Wbar (w.f_Y - SwY/rho)) / W_m + w_0 J_{0,1+m}
+//   v_0     = (wYT - SwY/T)/rho + (w.f_Y)/T + w_0 J_00
+template <class S>
+__device__ __forceinline__ void jtv(const double* __restrict__ tab, double p, double ip, const S (&y)[R],
+                                    const double (&ywi)[RI], const double (&w)[R], S* __restrict__ L,
+                                    double (&v)[R], double (&vi)[RI], double (&g)[ROUNDS][3])
+{
+    const int i = gl_local();
+    Mix<S> x;
+    Thermo<S, true> th;
+    Stream<4> list(&mech::TL[0]);
+    thermo<S, true>(tab, p, ip, y, ywi, L, x, th);
+    // neutral entries of the reaction arrays
+    if (i < 2 * MOLM) L[L_V + i * NRW + NR] = 0.0;
+    if (i < 2) L[L_XA + i * NXV + NXV - 1] = 0.0;
 #pragma unroll
-    for (int k = N - 1; k >= 0; --k) {
-        const double s = gsum(i > k && i < N ? A[k] * y : 0.0);
-        if (i == k) y -= s;
-        if (swaps & (1ull << k)) {
-            const int pk = piv[k];
-            y = gather(y, (i == k) ? pk : (i == pk ? k : i));
+    for (int r = 0; r < R; ++r) {
+        const int a = r * 16 + i;
+        if (a >= 1 && a < NACT) {
+            L[L_WW + a - 1] = mech::PW[a] * w[r];
+            L[L_CP + a - 1] = th.cpR[r];
         }
     }
-    return y;
-}
-
-// Component i of J^T w for the group's rows of J (row i in lane i).
-__device__ __forceinline__ double colsum(const double (&J)[N], double w)
-{
-    const int i = gl_local();
-    double out = 0.0;
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double s = gsum(J[k] * w);
-        out = (i == k) ? s : out;
-    }
-    return out;
-}
-
-// Component i of D_u[J^T w] from dual rows of J (tangent along u).
-__device__ __forceinline__ double colsum_tangent(const chem_math::Dual (&J)[N], double w)
-{
-    const int i = gl_local();
-    double out = 0.0;
+    for (int q = 0; q < RI; ++q)
+        if (q * 16 + i <= NI) {
+            L[L_WW + NA + q * 16 + i] = 0.0;
+            L[L_CP + NA + q * 16 + i] = 0.0;
+        }
+    lds_sync();
+    const double w0 = bc(w[0], 0);
+    const S icpm = chem_math::recip(th.cpm);
+    const S rcpinv = x.T * th.sig * ip * icpm;
+    S SwY = 0.0, HSa = 0.0, wYT = 0.0, HwT = 0.0, hw = 0.0, Wf = 0.0, cpw = 0.0, DA = 0.0, DH = 0.0;
+    S kr[ROUNDS], wYr[ROUNDS], hsr[ROUNDS];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double s = gsum(J[k].d * w);
-        out = (i == k) ? s : out;
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int j = r * G + i;
+        if (j < NR) {
+            Rate<S> o;
+            int ra[MOLR], pa[MOLP], misc;
+            if (r < mech::FULL_ROUNDS) reaction<S, true, true>(j, tab, L, x, o, ra, pa, misc);
+            else reaction<S, false, true>(j, tab, L, x, o, ra, pa, misc);
+            S wY = 0.0, cps = 0.0;
+#pragma unroll
+            for (int s = 0; s < MOLP; ++s) {
+                wY = wY + L[L_WW + pa[s]];
+                cps = cps + L[L_CP + pa[s]];
+            }
+#pragma unroll
+            for (int s = 0; s < MOLR; ++s) {
+                wY = wY - L[L_WW + ra[s]];
+                cps = cps - L[L_CP + ra[s]];
+            }
+            const S hs = o.dH;
+            SwY = fma(wY, o.s, SwY);
+            HSa = fma(hs, o.s, HSa);
+            wYT = fma(wY, o.dqT, wYT);
+            HwT = fma(hs, o.dqT, HwT);
+            hw = fma(hs, o.q, hw);
+            Wf = fma(wY, o.q, Wf);
+            cpw = fma(cps, o.q, cpw);
+            const S wsum = wY * th.irho - w0 * (mech::RU * x.T) * hs * rcpinv;
+            const S gq = wsum * o.qA;
+            g[r][0] += take(gq);
+            g[r][1] += take(gq * x.lnT);
+            g[r][2] += take(gq * (-x.iT * (1.0 / mech::RU)));
+#pragma unroll
+            for (int s = 0; s < MOLR; ++s) {
+                const S d = others<S, MOLR>(L, ra, s, o.kf);
+                L[L_V + s * NRW + j] = wY * d;
+                L[L_V + (MOLM + s) * NRW + j] = hs * d;
+            }
+            kr[r] = o.kr;
+            wYr[r] = wY;
+            hsr[r] = hs;
+            if (NTB > 0 && r < mech::FULL_ROUNDS) {
+                const int kind = misc & 7;
+                if (kind >= 1 && kind <= 4) {
+                    const int t = (misc >> 16) & 0xffff;
+                    DA = fma(wY, o.dM, DA);
+                    DH = fma(hs, o.dM, DH);
+                    for (int q = 0; q < MAXP; ++q) {
+                        const S d = tab[T_TBC + q * NTB + t] * o.dM;
+                        L[L_XA + t * MAXP + q] = wY * d;
+                        L[L_XA + NXV + t * MAXP + q] = hs * d;
+                    }
+                }
+            }
+        }
     }
-    return out;
+    lds_sync();
+    S cA[R + RI], cH[R + RI];
+#pragma unroll
+    for (int r = 0; r < R + RI; ++r) {
+        cA[r] = 0.0;
+        cH[r] = 0.0;
+    }
+    static_for<0, R + RI>([&](auto rc) {
+        constexpr int r = decltype(rc)::v;
+        list.run(mech::SRLEN[r], [&](int, int e) {
+            cA[r] = cA[r] + L[L_V + e];
+            cH[r] = cH[r] + L[L_V + MOLM * NRW + e];
+        });
+    });
+    static_for<0, R + RI>([&](auto rc) {
+        constexpr int r = decltype(rc)::v;
+        list.run(mech::SXLEN[r], [&](int, int e) {
+            cA[r] = cA[r] + L[L_XA + e];
+            cH[r] = cH[r] + L[L_XA + NXV + e];
+        });
+    });
+    lds_sync();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int j = r * G + i;
+        if (j < NR) {
+            const int* const words = (const int*)(tab + T_INT) + I_WORDS;
+            int pa[MOLP];
+#pragma unroll
+            for (int s = 0; s < MOLP; ++s) pa[s] = (words[(WR + s / 4) * NR + j] >> (8 * (s % 4))) & 255;
+#pragma unroll
+            for (int s = 0; s < MOLP; ++s) {
+                const S d = others<S, MOLP>(L, pa, s, -kr[r]);
+                L[L_V + s * NRW + j] = wYr[r] * d;
+                L[L_V + (MOLM + s) * NRW + j] = hsr[r] * d;
+            }
+        }
+    }
+    lds_sync();
+    static_for<0, R + RI>([&](auto rc) {
+        constexpr int r = decltype(rc)::v;
+        list.run(mech::SPLEN[r], [&](int, int e) {
+            cA[r] = cA[r] + L[L_V + e];
+            cH[r] = cH[r] + L[L_V + MOLM * NRW + e];
+        });
+    });
+    lds_sync();
+    SwY = gsum(SwY);
+    HSa = gsum(HSa);
+    wYT = gsum(wYT);
+    HwT = gsum(HwT);
+    hw = gsum(hw);
+    Wf = gsum(Wf) * th.irho;
+    cpw = gsum(cpw);
+    DA = gsum(DA);
+    DH = gsum(DH);
+    const S fT = -mech::RU * x.T * hw * rcpinv;
+    const S RT = mech::RU * x.T;
+    const S icp = icpm * (1.0 / mech::RU);
+    const S dcp = mech::RU * th.dcpm;
+    const S wg = th.Wbar * (Wf - th.irho * SwY);
+#pragma unroll
+    for (int r = 0; r < R + RI; ++r) {
+        const double iW = mech::PW[NPT + r * 16 + i];       // 0 where no species sits
+        const S cp = r < R ? th.cpR[r < R ? r : 0] : th.cpi[r < R ? 0 : r - R];
+        const S t = fma(th.rho, cH[r] + DH, -th.Wbar * HSa) * (-RT * rcpinv);
+        const S u = fma(cp, icp * mech::RU, -th.Wbar);
+        const S J0m = fma(-fT, u, t) * iW;
+        const S out = fma(cA[r] + DA + wg, iW, w0 * J0m);
+        if (r < R) v[r < R ? r : 0] += take(out);
+        else vi[r < R ? 0 : r - R] += take(out);
+    }
+    const S J00 = -mech::RU * (cpw + x.T * HwT - HSa) * rcpinv - fT * (dcp * icp - x.iT);
+    const S v0 = fma(th.irho, wYT - SwY * x.iT, fma(x.iT, Wf, w0 * J00));
+    if (i == 0) v[0] += take(v0);
 }
 
 // value of a stage-indexed register array at a run-time stage s (selects, so
 // the array stays in registers)
-__device__ __forceinline__ double pick(const double (&v)[Rodas4::S], int s)
-{
-    double r = v[0];
-#pragma unroll
-    for (int q = 1; q < Rodas4::S; ++q) r = (q == s) ? v[q] : r;
-    return r;
-}
-
-__device__ __forceinline__ void place(double (&v)[Rodas4::S], int s, double x)
+__device__ __forceinline__ void pick(const double (&a)[Rodas4::S][R], int s, double (&o)[R])
 {
 #pragma unroll
-    for (int q = 0; q < Rodas4::S; ++q) v[q] = (q == s) ? x : v[q];
+    for (int r = 0; r < R; ++r) {
+        o[r] = a[0][r];
+#pragma unroll
+        for (int q = 1; q < Rodas4::S; ++q) o[r] = q == s ? a[q][r] : o[r];
+    }
 }
 
-// The adjoint of one frozen RODAS4 step from y (component yi) with step h:
-// lam (the cotangent of y_new, component in lane i) becomes the cotangent of
-// y; the parameter products of the lane's reaction slots are added to g.
-// L: the cell's scratch (room for dual numbers), PV: its pivot scratch.  The
-// stage loops stay rolled (one copy of each source-term evaluation).
-__device__ __noinline__ void step_adjoint(const double* __restrict__ par, double p, double ip, double yi, double h,
-                                          double& lam, double (&g)[ROUNDS][3], double* __restrict__ L,
-                                          double* __restrict__ PV)
+__device__ __forceinline__ void place(double (&a)[Rodas4::S][R], int s, const double (&x)[R])
 {
-    using chem_math::Dual;
+#pragma unroll
+    for (int q = 0; q < Rodas4::S; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[q][r] = q == s ? x[r] : a[q][r];
+}
+
+// The adjoint of one frozen RODAS4 step from y with step h: lam (the cotangent
+// of y_new; lami for the species no reaction changes) becomes the cotangent
+// of y; the parameter products of the lane's reactions are added to g.  The
+// stage loops stay rolled (one copy of each evaluation).
+__device__ __noinline__ void step_adjoint(const double* __restrict__ tab, double p, double ip, const double (&y)[R],
+                                          const double (&ywi)[RI], double h, double (&lam)[R], double (&lami)[RI],
+                                          double (&g)[ROUNDS][3], double* __restrict__ L)
+{
     const int i = gl_local();
-    double J0[N], A[N], dummy[N];
-    const double f0 = rhs<double, F_JAC>(par, p, ip, yi, L, J0, 0.0, g);
+    Factors F;
+    double f[R];
+    rhs<true, NACT>(tab, p, ip, y, ywi, L, f, F.A);
     const double hinv = chem_math::recip(h);
     const double ghinv = hinv * (1.0 / Rodas4::gamma);
 #pragma unroll
-    for (int j = 0; j < N; ++j) A[j] = (j == i ? ghinv : 0.0) - J0[j];
-    bool ok;
-    const unsigned long long swaps = lu(A, ok, PV);
-    double u[Rodas4::S], Ys[Rodas4::S];
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int s = 0; s < Rodas4::S; ++s) u[s] = Ys[s] = 0.0;
-    Ys[0] = yi;
-    u[0] = solve(A, PV, swaps, f0);
+        for (int c = 0; c < NACT; ++c) F.A[r][c] = (r * 16 + i == c ? ghinv : 0.0) - F.A[r][c];
+    bool ok;
+    lu(F, ok);
+    double u[Rodas4::S][R], Ys[Rodas4::S][R];
+#pragma unroll
+    for (int s = 0; s < Rodas4::S; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            u[s][r] = 0.0;
+            Ys[s][r] = y[r];
+        }
+    solve(F, f);
+    place(u, 0, f);
 #pragma unroll 1
     for (int s = 1; s < Rodas4::S; ++s) {
-        double Y = yi, acc = 0.0;
+        double Y[R], acc[R], us[R], none[R][1];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            Y[r] = y[r];
+            acc[r] = 0.0;
+        }
 #pragma unroll
         for (int j = 0; j < Rodas4::S - 1; ++j) {
             if (j < s) {
-                Y = fma(RA[s][j], u[j], Y);
-                acc = fma(RC[s][j], u[j], acc);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    Y[r] = fma(RA[s][j], u[j][r], Y[r]);
+                    acc[r] = fma(RC[s][j], u[j][r], acc[r]);
+                }
             }
         }
         place(Ys, s, Y);
-        const double fs = rhs<double, F_ONLY>(par, p, ip, Y, L, dummy, 0.0, g);
-        place(u, s, solve(A, PV, swaps, fma(acc, hinv, fs)));
+        rhs<false, 1>(tab, p, ip, Y, ywi, L, us, none);
+#pragma unroll
+        for (int r = 0; r < R; ++r) us[r] = fma(acc[r], hinv, us[r]);
+        solve(F, us);
+        place(u, s, us);
     }
     // reverse over the stages
     const double mw[Rodas4::S] = {RA[5][0], RA[5][1], RA[5][2], RA[5][3], 1.0, 1.0};
-    double ub[Rodas4::S], w[Rodas4::S];
-    double yb = lam;
+    double ub[Rodas4::S][R], w[Rodas4::S][R];
 #pragma unroll
-    for (int s = 0; s < Rodas4::S; ++s) {
-        ub[s] = mw[s] * lam;
-        w[s] = 0.0;
-    }
+    for (int s = 0; s < Rodas4::S; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            ub[s][r] = mw[s] * lam[r];
+            w[s][r] = 0.0;
+        }
 #pragma unroll 1
     for (int s = Rodas4::S - 1; s >= 0; --s) {
-        const double ws = solve_t(A, PV, swaps, pick(ub, s));
+        double ws[R], Y[R], Yb[R];
+        pick(ub, s, ws);
+        solve_t(F, ws, L + L_A);
         place(w, s, ws);
-        const double Yss = pick(Ys, s);
-        double Js[N];
-        if (s == 0) {
+        pick(Ys, s, Y);
 #pragma unroll
-            for (int j = 0; j < N; ++j) Js[j] = J0[j];
-        } else {
-            rhs<double, F_JAC>(par, p, ip, Yss, L, Js, 0.0, g);
+        for (int r = 0; r < R; ++r) Yb[r] = 0.0;
+        jtv<double>(tab, p, ip, Y, ywi, ws, L, Yb, lami, g);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            lam[r] += Yb[r];
+#pragma unroll
+            for (int j = 0; j < Rodas4::S - 1; ++j)
+                if (j < s) ub[j][r] = fma(RA[s][j], Yb[r], fma(RC[s][j] * hinv, ws[r], ub[j][r]));
         }
-        const double Yb = colsum(Js, ws);
-        yb += Yb;
-        rhs<double, PARAM_VJP>(par, p, ip, Yss, L, dummy, ws, g);
-#pragma unroll
-        for (int j = 0; j < Rodas4::S - 1; ++j)
-            if (j < s) ub[j] = fma(RA[s][j], Yb, fma(RC[s][j] * hinv, ws, ub[j]));
     }
     // second-order terms at y: J(y) inside M, one dual evaluation per stage direction
-    Dual* Ld = (Dual*)L;
 #pragma unroll 1
     for (int s = 0; s < Rodas4::S; ++s) {
-        const double us = pick(u, s), ws = pick(w, s);
-        Dual Jd[N];
-        Dual gd[ROUNDS][3];
+        double us[R], ws[R];
+        pick(u, s, us);
+        pick(w, s, ws);
+        Dual yd[R];
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) gd[r][0] = gd[r][1] = gd[r][2] = 0.0;
-        rhs<Dual, F_JAC>(par, p, ip, Dual(yi, us), Ld, Jd, Dual(0.0), gd);
-        yb += colsum_tangent(Jd, ws);
-        rhs<Dual, PARAM_VJP>(par, p, ip, Dual(yi, us), Ld, Jd, Dual(ws), gd);
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            g[r][0] += gd[r][0].d;
-            g[r][1] += gd[r][1].d;
-            g[r][2] += gd[r][2].d;
-        }
+        for (int r = 0; r < R; ++r) yd[r] = Dual(y[r], us[r]);
+        jtv<Dual>(tab, p, ip, yd, ywi, ws, (Dual*)L, lam, lami, g);
     }
-    lam = yb;
+}
+
+// Groups of a workgroup: cpw of each wave hold a cell (the others have no
+// scratch and leave).  The group's place among the launch's, or -1, and its
+// scratch.
+__device__ __forceinline__ long group_of(int cpw, int words, double* __restrict__ lds, double*& L)
+{
+    const int wave = (int)threadIdx.x / 64, grp = ((int)threadIdx.x & 63) / G;
+    const int own = wave * cpw + grp;
+    L = lds + TAB_DOUBLES + own * words;
+    return grp < cpw ? (long)blockIdx.x * ((int)blockDim.x / 64 * cpw) + own : -1;
 }
 
 }  // namespace chemw
 
-// ---- plain form: one group of G lanes per cell, cells in index order ----
-extern "C" __global__ void __launch_bounds__(64, 2) chem_plain(chem::IntegrateArgs a)
+// ---- plain form: one group of 16 lanes per cell, cells in index order ----
+// A field larger than the chip holds at once is dealt through one counter
+// (a.head): a group takes the next cell when its own is done.  Dealt by the
+// grid instead, a workgroup's groups wait for its slowest cell, and a front
+// that runs along a grid line puts all the costly workgroups on the same few
+// XCDs (workgroups go to the XCDs in turn).
+extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_plain(chem::IntegrateArgs a)
 {
     using namespace chemw;
     extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    const long cell = (long)blockIdx.x * CPW + grp;
-    if (cell >= a.ncell) return;
-    double* L = lds + grp * mech::LDS_CELL;
+    load_tables(lds, a.par);
+    double* L;
+    long cell = group_of(mech::CPW, mech::LDS_CELL, lds, L);
+    if (cell < 0) return;
     Cell c;
-    cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, a.h0 ? a.h0[cell] : a.step.dt);
-    while (!c.done) cell_attempt(c, a.par, a.step, L, L + mech::L_J);
-    cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
+    c.done = true;
+    bool have = false, more = true;
+    while (true) {
+        if (!have && more) {
+            if (a.head) {
+                unsigned long long t = 0ull;
+                if (gl() == 0) t = atomicAdd(a.head, 1ull);
+                cell = (long)__shfl((long long)t, gbase(), 64);
+            }
+            have = cell < a.ncell;
+            more = a.head && have;
+            if (have) cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, a.h0 ? a.h0[cell] : a.step.dt);
+        }
+        if (__all(!have && !more)) break;
+        if (have) {
+            cell_attempt(c, lds, a.step, L);
+            if (c.done) {
+                cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
+                have = false;
+            }
+        }
+    }
 }
 
 // ---- source terms and Jacobian at given states ----
-extern "C" __global__ void __launch_bounds__(64) chem_eval(EvalArgs a)
+extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_eval(EvalArgs a)
 {
     using namespace chemw;
     extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    const long cell = (long)blockIdx.x * CPW + grp;
-    if (cell >= a.ncell) return;
-    double* L = lds + grp * mech::LDS_CELL;
+    load_tables(lds, a.par);
+    double* L;
+    const long first = group_of(mech::CPW, mech::LDS_CELL, lds, L);
+    if (first < 0) return;
     const int i = gl();
-    const double p = a.p[cell];
-    const double yi = i == 0 ? a.T[cell] : (i <= NS ? a.Y[cell * NS + i - 1] : 0.0);
-    double A[N];
-    double g[ROUNDS][3];
-    double f;
-    if (a.J) {
-        f = rhs<double, F_JAC>(a.par, p, 1.0 / p, yi, L, A, 0.0, g);
-        if (i < N) {
+    double zero[RI];
 #pragma unroll
-            for (int j = 0; j < N; ++j) a.J[(cell * N + i) * N + j] = A[j];
+    for (int q = 0; q < RI; ++q) zero[q] = 0.0;
+    // the launch holds at most the resident workgroups, which share out the cells
+    for (long cell = first; cell < a.ncell; cell += (long)gridDim.x * ((int)blockDim.x / 64 * mech::CPW)) {
+        Cell c;
+        cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 0.0);
+        double f[R];
+        if (a.J) {
+            double A[R][N];
+            rhs<true, N>(lds, c.p, c.ip, c.y, c.ywi, L, f, A);
+            double* const J = a.J + cell * N * N;
+#pragma unroll
+            for (int r = 0; r < R + RI; ++r) {
+                const int k = mech::PSPEC[r * 16 + i];
+                const int row = r == 0 && i == 0 ? 0 : 1 + k;
+                if (row > 0 || (r == 0 && i == 0)) {
+#pragma unroll
+                    for (int col = 0; col < N; ++col) {
+                        const int oc = col == 0 ? 0 : 1 + mech::COLSPEC[col - 1];
+                        J[row * N + oc] = r < R ? A[r < R ? r : 0][col] : 0.0;   // (no reaction changes the last)
+                    }
+                }
+            }
+        } else {
+            double none[R][1];
+            rhs<false, 1>(lds, c.p, c.ip, c.y, c.ywi, L, f, none);
         }
-    } else {
-        f = rhs<double, F_ONLY>(a.par, p, 1.0 / p, yi, L, A, 0.0, g);
+        put(f, zero, a.f + cell * N, a.f + cell * N + 1);
     }
-    if (i < N) a.f[cell * N + i] = f;
 }
 
 // ---- one fixed RODAS4 step of size h per cell (y_new and the error norm) ----
@@ -1009,21 +1514,20 @@ struct FixedStepArgs {
     int* ok;
 };
 
-extern "C" __global__ void __launch_bounds__(64) chem_fixed_step(FixedStepArgs a)
+extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_fixed_step(FixedStepArgs a)
 {
     using namespace chemw;
     extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    const long cell = (long)blockIdx.x * CPW + grp;
-    if (cell >= a.ncell) return;
-    double* L = lds + grp * mech::LDS_CELL;
-    const int i = gl();
-    const double p = a.p[cell];
-    const double yi = i == 0 ? a.T[cell] : (i <= NS ? a.Y[cell * NS + i - 1] : 0.0);
-    double yn, en;
-    const bool ok = ros_step(a.par, p, 1.0 / p, yi, a.h, a.rtol, a.atol, L, L + mech::L_J, yn, en);
-    if (i < N) a.ynew[cell * N + i] = yn;
-    if (i == 0) {
+    load_tables(lds, a.par);
+    double* L;
+    const long cell = group_of(mech::CPW, mech::LDS_CELL, lds, L);
+    if (cell < 0 || cell >= a.ncell) return;
+    Cell c;
+    cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, a.h);
+    double yn[R], en;
+    const bool ok = ros_step(lds, c.p, c.ip, c.y, c.ywi, c.yi, a.h, a.rtol, a.atol, L, yn, en);
+    put(yn, c.yi, a.ynew + cell * N, a.ynew + cell * N + 1);
+    if (gl() == 0) {
         a.err[cell] = en;
         a.ok[cell] = ok ? 1 : 0;
     }
@@ -1034,14 +1538,15 @@ extern "C" __global__ void __launch_bounds__(64) chem_fixed_step(FixedStepArgs a
 // next cell when its current one is done, so no group idles while cells
 // remain (the hardware already balances whole waves; this also balances the
 // groups inside a wave and spans several fields in one launch).
-extern "C" __global__ void __launch_bounds__(64, 2) chem_persistent(const PersistBlock* __restrict__ blk,
-                                                                 unsigned long long* __restrict__ heads,
-                                                                 const double* __restrict__ par)
+extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_persistent(const PersistBlock* __restrict__ blk,
+                                                                         unsigned long long* __restrict__ heads,
+                                                                         const double* __restrict__ par)
 {
     using namespace chemw;
     extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    double* L = lds + grp * mech::LDS_CELL;
+    load_tables(lds, par);
+    double* L;
+    if (group_of(mech::CPW, mech::LDS_CELL, lds, L) < 0) return;
     const StepArgs step = blk->step;
     const long total = blk->total;
     Cell c;
@@ -1064,9 +1569,9 @@ extern "C" __global__ void __launch_bounds__(64, 2) chem_persistent(const Persis
                 exhausted = true;
             }
         }
-        if (__all(exhausted)) break;
+        if (__all(exhausted && !have)) break;
         if (have) {
-            cell_attempt(c, par, step, L, L + mech::L_J);
+            cell_attempt(c, lds, step, L);
             if (c.done) {
                 const FieldDesc& fd = blk->fields[f];
                 cell_store(c, fd.T, fd.Y, local, fd.status, fd.nacc, fd.nrej);
@@ -1079,21 +1584,19 @@ extern "C" __global__ void __launch_bounds__(64, 2) chem_persistent(const Persis
 // ---- discrete adjoint: one group per cell, cells in descending cost order ----
 // The forward solve is rerun, storing every accepted step size and the state
 // every K accepted steps; then the reverse sweep recomputes each segment from
-// its checkpoint and applies the step adjoints backwards.  Per-cell parameter
-// gradients go to gpar for the fixed-order reduction.
-// Group s (of a.nslot) takes the cells in positions s, s + nslot, ... of the
-// cost order and keeps the parameter gradients of all its cells in its lanes'
-// registers (lane i holds those of its reaction slots): one row of partial
-// sums per group instead of one per cell.
-extern "C" __global__ void __launch_bounds__(64) chem_adjoint(AdjointArgs a)
+// its checkpoint and applies the step adjoints backwards.  Group s (of
+// a.nslot) takes the cells in positions s, s + nslot, ... of the cost order
+// and keeps the parameter gradients of all its cells in its lanes' registers
+// (lane i holds those of its reaction slots): one row of partial sums per
+// group instead of one per cell, for the fixed-order reduction.
+extern "C" __global__ void __launch_bounds__(256, 1) chem_adjoint(AdjointArgs a)
 {
     using namespace chemw;
     extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    const long gslot = (long)blockIdx.x * CPW + grp;
-    if (gslot >= a.nslot) return;
-    double* L = lds + grp * mech::ADJ_LDS_CELL;
-    double* PV = L + 2 * mech::LDS_CELL;
+    load_tables(lds, a.par);
+    double* L;
+    const long gslot = group_of(mech::ACPW, mech::ADJ_LDS_CELL, lds, L);
+    if (gslot < 0 || gslot >= a.nslot) return;
     const int i = gl();
     double g[ROUNDS][3];
 #pragma unroll
@@ -1108,10 +1611,12 @@ extern "C" __global__ void __launch_bounds__(64) chem_adjoint(AdjointArgs a)
         int stored = -1;
         while (!c.done) {
             if (c.nacc % a.K == 0 && c.nacc != stored && c.nacc < cap) {
-                if (i < N) ck[(c.nacc / a.K) * N + i] = c.y;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (r * 16 + i < NACT) ck[(c.nacc / a.K) * N + r * 16 + i] = c.y[r];
                 stored = c.nacc;
             }
-            const double hacc = cell_attempt(c, a.par, a.step, L, PV);
+            const double hacc = cell_attempt(c, lds, a.step, L);
             if (hacc > 0.0) {
                 if (c.nacc > cap) {
                     c.status = chem::CELL_NONFINITE;
@@ -1122,41 +1627,45 @@ extern "C" __global__ void __launch_bounds__(64) chem_adjoint(AdjointArgs a)
             }
         }
         cell_store(c, a.Tend, a.Yend, cell, a.status, a.nacc, a.nrej);
-        if (c.status == chem::CELL_BADINPUT) {
-            if (i == 0) a.Tend[cell] = a.T0[cell];
-            else if (i <= NS) a.Yend[cell * NS + i - 1] = a.Y0[cell * NS + i - 1];
-        }
+        if (c.status == chem::CELL_BADINPUT) put(c.y, c.yi, a.Tend + cell, a.Yend + cell * NS);
+        double lam[R], lami[RI];
         if (c.status != chem::CELL_OK) {
-            if (i == 0) a.gT0[cell] = __builtin_nan("");
-            else if (i <= NS) a.gY0[cell * NS + i - 1] = __builtin_nan("");
+#pragma unroll
+            for (int r = 0; r < R; ++r) lam[r] = __builtin_nan("");
+#pragma unroll
+            for (int q = 0; q < RI; ++q) lami[q] = __builtin_nan("");
+            put(lam, lami, a.gT0 + cell, a.gY0 + cell * NS);
             continue;                   // adds nothing to the parameter gradients
         }
-        double lam = i == 0 ? a.gT[cell] : (i <= NS ? a.gY[cell * NS + i - 1] : 0.0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int k = mech::PSPEC[r * 16 + i];
+            lam[r] = k >= 0 ? a.gY[cell * NS + k] : 0.0;
+            if (r == 0 && i == 0) lam[r] = a.gT[cell];
+        }
+#pragma unroll
+        for (int q = 0; q < RI; ++q) {
+            const int k = mech::PSPEC[R * 16 + q * 16 + i];
+            lami[q] = k >= 0 ? a.gY[cell * NS + k] : 0.0;
+        }
         const int na = c.nacc;
         const double p = c.p, ip = c.ip;
         for (int seg = (na - 1) / a.K; seg >= 0 && na > 0; --seg) {
             const int first = seg * a.K;
             const int last = min(na, first + a.K) - 1;
-            double ys[16];                        // the segment's states (K <= 16), component i
-            ys[0] = i < N ? ck[seg * N + i] : 0.0;
+            double ys[16][R];                     // the segment's states (K <= 16)
+#pragma unroll
+            for (int r = 0; r < R; ++r) ys[0][r] = r * 16 + i < NACT ? ck[seg * N + r * 16 + i] : 0.0;
             for (int s = first; s < last; ++s) {
-                double yn, en;
-                double yc = ys[0];
+                double yn[R], en;
+                ros_step(lds, p, ip, ys[s - first], c.ywi, c.yi, hs[s], a.step.rtol, a.step.atol, L, yn, en);
 #pragma unroll
-                for (int q = 1; q < 16; ++q) yc = (q == s - first) ? ys[q] : yc;
-                ros_step(a.par, p, ip, yc, hs[s], a.step.rtol, a.step.atol, L, PV, yn, en);
-#pragma unroll
-                for (int q = 1; q < 16; ++q) ys[q] = (q == s - first + 1) ? yn : ys[q];
+                for (int r = 0; r < R; ++r) ys[s - first + 1][r] = yn[r];
             }
-            for (int s = last; s >= first; --s) {
-                double yc = ys[0];
-#pragma unroll
-                for (int q = 1; q < 16; ++q) yc = (q == s - first) ? ys[q] : yc;
-                step_adjoint(a.par, p, ip, yc, hs[s], lam, g, L, PV);
-            }
+            for (int s = last; s >= first; --s)
+                step_adjoint(lds, p, ip, ys[s - first], c.ywi, hs[s], lam, lami, g, L);
         }
-        if (i == 0) a.gT0[cell] = lam;
-        else if (i <= NS) a.gY0[cell * NS + i - 1] = lam;
+        put(lam, lami, a.gT0 + cell, a.gY0 + cell * NS);
     }
     double* gp = a.gpar + gslot * 3 * NR;
 #pragma unroll

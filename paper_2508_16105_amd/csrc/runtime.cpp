@@ -230,6 +230,36 @@ StepArgs step_args(double dt, double rtol, double atol, const Options& o)
 
 }  // namespace
 
+// The plain kernel over a.ncell cells.  Up to what the device holds at once
+// every cell has its place in the grid; above that the resident workgroups
+// take the cells through a counter (cleared first; the per-device state's
+// queue heads, which one call at a time uses).  Both sides measured on the
+// 9-species field: see the kernel.
+namespace {
+
+int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t stream)
+{
+    int64_t lanes = m->wide ? m->layout.lanes(a.ncell) : a.ncell;
+    const unsigned shmem = m->wide ? m->layout.lds_bytes() : d.stage_lds(64);
+    const int block = m->wide ? m->layout.block() : 64;
+    if (!d.plain_blocks_per_cu) {
+        int n = 0;
+        HIPCHECK(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, d.f_plain, block, shmem), "occupancy");
+        d.plain_blocks_per_cu = std::max(1, n);
+    }
+    const int64_t resident = (int64_t)d.num_cu * d.plain_blocks_per_cu * block;
+    a.head = nullptr;
+    if (m->wide && lanes > resident) {
+        lanes = resident;
+        a.head = d.heads;
+        struct { unsigned long long* p; int n; } za{d.heads, 1};
+        if (int rc = launch_1d(d.f_zero, 1, 64, &za, sizeof za, stream, "chem_zero_u64")) return rc;
+    }
+    return launch_1d(d.f_plain, lanes, block, &a, sizeof a, stream, "chem_plain", shmem);
+}
+
+}  // namespace
+
 int run_plain(chem_mechanism* m, int64_t ncell, double* T, const double* p, double* Y, double dt,
               double rtol, double atol, const Options& o, chem_stats* stats, int32_t* status,
               int32_t* nacc, int32_t* nrej, hipStream_t stream)
@@ -243,12 +273,9 @@ int run_plain(chem_mechanism* m, int64_t ncell, double* T, const double* p, doub
     int32_t* st = status ? status : stats ? d->cells_i32 : nullptr;
     int32_t* na = nacc ? nacc : stats ? d->cells_i32 + ncell : nullptr;
     int32_t* nr = nrej ? nrej : stats ? d->cells_i32 + 2 * ncell : nullptr;
-    IntegrateArgs a{d->par, T, p, Y, (long)ncell, o.h0, st, na, nr, step_args(dt, rtol, atol, o)};
+    IntegrateArgs a{d->par, T, p, Y, (long)ncell, o.h0, st, na, nr, step_args(dt, rtol, atol, o), nullptr};
     if (stats) HIPCHECK(hipEventRecord(d->ev0, stream), "event");
-    // one lane per cell, or one group of G lanes per cell in the wave-cooperative form
-    const int64_t lanes = m->wide ? ncell * m->layout.G : ncell;
-    const unsigned shmem = m->wide ? m->layout.lds_bytes() : d->stage_lds(64);
-    if (int rc = launch_1d(d->f_plain, lanes, 64, &a, sizeof a, stream, "chem_plain", shmem)) return rc;
+    if (int rc = launch_plain(m, *d, a, stream)) return rc;
     if (!stats) return 0;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
     HIPCHECK(hipEventSynchronize(d->ev1), "event sync");
@@ -425,9 +452,9 @@ void write_tuned(const std::string& path, const LaunchConfig& c, int order, floa
 // The wave-cooperative persistent launch [reset -> persistent kernel] as a
 // graph built once per grid size (everything call-specific is in the field
 // table, whose device address is fixed).
-int launch_graph_wide(DeviceState& d, const chem_mechanism* m, int64_t waves, hipStream_t stream)
+int launch_graph_wide(DeviceState& d, const chem_mechanism* m, int64_t blocks, hipStream_t stream)
 {
-    auto it = d.wide_graphs.find(waves);
+    auto it = d.wide_graphs.find(blocks);
     if (it == d.wide_graphs.end()) {
         if (!d.capture_stream) HIPCHECK(hipStreamCreateWithFlags(&d.capture_stream, hipStreamNonBlocking), "stream");
         hipGraph_t g;
@@ -439,8 +466,8 @@ int launch_graph_wide(DeviceState& d, const chem_mechanism* m, int64_t waves, hi
         void* pcfg[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &pa, HIP_LAUNCH_PARAM_BUFFER_SIZE, &ps, HIP_LAUNCH_PARAM_END};
         hipError_t e = hipModuleLaunchKernel(d.f_reset, 1, 1, 1, 256, 1, 1, 0, d.capture_stream, nullptr, rcfg);
         if (e == hipSuccess)
-            e = hipModuleLaunchKernel(d.f_persistent, (unsigned)waves, 1, 1, 64, 1, 1, m->layout.lds_bytes(),
-                                      d.capture_stream, nullptr, pcfg);
+            e = hipModuleLaunchKernel(d.f_persistent, (unsigned)blocks, 1, 1, (unsigned)m->layout.block(), 1, 1,
+                                      m->layout.lds_bytes(), d.capture_stream, nullptr, pcfg);
         hipError_t e2 = hipStreamEndCapture(d.capture_stream, &g);
         if (e != hipSuccess) return hip_error(e, "capture wave-cooperative launch");
         if (e2 != hipSuccess) return hip_error(e2, "end capture");
@@ -448,7 +475,7 @@ int launch_graph_wide(DeviceState& d, const chem_mechanism* m, int64_t waves, hi
         hipError_t e3 = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         if (e3 != hipSuccess) return hip_error(e3, "graph instantiate");
-        it = d.wide_graphs.emplace(waves, ex).first;
+        it = d.wide_graphs.emplace(blocks, ex).first;
     }
     HIPCHECK(hipGraphLaunch(it->second, stream), "graph launch");
     return 0;
@@ -562,10 +589,9 @@ int run_persistent_wide(chem_mechanism* m, const FieldView* fv, int nfield, doub
     LaunchConfig c{64, 1, 1};
     if (int rc = write_block(*d, fields, header_for(*d, total, nfield, c, s, CHEM_ORDER_NATURAL), stream)) return rc;
     if (stats) HIPCHECK(hipEventRecord(d->ev0, stream), "event");
-    // resident waves: as many as the LDS scratch allows, at most 8 per CU
-    const unsigned per_cu = std::max<unsigned>(1u, std::min<unsigned>(8u, (unsigned)(160u * 1024u / std::max(1u, m->layout.lds_bytes()))));
-    const int64_t waves = std::min<int64_t>((int64_t)d->num_cu * per_cu, (total + m->layout.cells_per_wave() - 1) / m->layout.cells_per_wave());
-    if (int rc = launch_graph_wide(*d, m, waves, stream)) return rc;
+    // resident workgroups: as many as the registers and the LDS scratch allow
+    const int64_t blocks = std::min<int64_t>((int64_t)d->num_cu * m->layout.blocks_per_cu(), m->layout.blocks(total));
+    if (int rc = launch_graph_wide(*d, m, blocks, stream)) return rc;
     if (!stats) return 0;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
     HIPCHECK(hipEventSynchronize(d->ev1), "event sync");
@@ -704,12 +730,10 @@ int run_noalloc(chem_mechanism* m, int64_t ncell, double* T, const double* p, do
     struct { const char* blk; unsigned long long* heads; const double* par; } pa{blk, heads, d->par};
     if (m->wide) {
         if (int rc = launch_1d(d->f_reset, 256, 256, &ra, sizeof ra, stream, "chem_reset_heads")) return rc;
-        const unsigned per_cu = std::max<unsigned>(
-            1u, std::min<unsigned>(8u, (unsigned)(160u * 1024u / std::max(1u, m->layout.lds_bytes()))));
-        const int64_t waves = std::min<int64_t>((int64_t)d->num_cu * per_cu,
-                                                (ncell + m->layout.cells_per_wave() - 1) / m->layout.cells_per_wave());
-        return launch_1d(d->f_persistent, waves * 64, 64, &pa, sizeof pa, stream, "chem_persistent",
-                         m->layout.lds_bytes());
+        const int64_t blocks =
+            std::min<int64_t>((int64_t)d->num_cu * m->layout.blocks_per_cu(), m->layout.blocks(ncell));
+        return launch_1d(d->f_persistent, blocks * m->layout.block(), m->layout.block(), &pa, sizeof pa, stream,
+                         "chem_persistent", m->layout.lds_bytes());
     }
     auto launch = [&](hipFunction_t fn, unsigned grid, unsigned block, unsigned shmem, void* args, size_t size,
                       const char* what) {
@@ -895,10 +919,8 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
         HIPCHECK(hipMemcpyAsync(na_fwd, o.adjoint_nacc, sizeof(int32_t) * ncell, hipMemcpyDeviceToDevice, stream),
                  "copy the forward's step counts");
     } else if (o.h0) {
-        IntegrateArgs ia{d->par, Tw, p, Yw, (long)ncell, o.h0, st, na_fwd, nj, step};
-        const int64_t lanes = m->wide ? ncell * m->layout.G : ncell;
-        const unsigned shmem = m->wide ? m->layout.lds_bytes() : d->stage_lds(64);
-        if (int rc = launch_1d(d->f_plain, lanes, 64, &ia, sizeof ia, stream, "chem_plain", shmem)) return rc;
+        IntegrateArgs ia{d->par, Tw, p, Yw, (long)ncell, o.h0, st, na_fwd, nj, step, nullptr};
+        if (int rc = launch_plain(m, *d, ia, stream)) return rc;
     } else {   // the persistent form takes the same steps, bitwise, sooner
         FieldView fv{Tw, p, Yw, ncell, st, na_fwd, nj, nullptr, nullptr};
         Options po = o;
@@ -954,8 +976,8 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     unsigned ashmem;
     if (m->wide) {
         ashmem = m->layout.adj_lds_bytes();
-        const int64_t waves_per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (160 * 1024) / std::max(1u, ashmem)));
-        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * waves_per_cu * m->layout.cells_per_wave());
+        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * m->layout.adj_blocks_per_cu() * m->layout.awpb *
+                                             m->layout.acpw);
     } else {
         // the stage vectors (5 n doubles a lane), and during a step adjoint the
         // 3 nr parameter accumulators when they fit 80 doubles a lane (the
@@ -1022,8 +1044,9 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     AdjointArgs aa{d->par, T0, p, Y0, (long)ncell, gT, gY, gT0, gY0, gpar, (long)nslot, T_end, Y_end, off_d,
                    off_d + ncell, na_fwd, order_d, o.h0, hs, ck, st, na, nj, step, K, ngroup, gcells, stash, trail};
     HIPCHECK(hipEventRecord(d->ev0, stream), "event");
-    const int64_t alanes = m->wide ? nslot * m->layout.G : nslot;
-    if (int rc = launch_1d(d->f_adjoint, alanes, 64, &aa, sizeof aa, stream, "chem_adjoint", ashmem)) return rc;
+    const int64_t alanes = m->wide ? m->layout.adj_lanes(nslot) : nslot;
+    const int ablock = m->wide ? m->layout.adj_block() : 64;
+    if (int rc = launch_1d(d->f_adjoint, alanes, ablock, &aa, sizeof aa, stream, "chem_adjoint", ashmem)) return rc;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
     struct {
         const double* g;

@@ -34,6 +34,7 @@ struct IntegrateArgs {
     int* nacc;
     int* nrej;
     StepArgs step;
+    unsigned long long* head;  // nullable: counter the cells are dealt through
 };
 
 struct EvalArgs {
@@ -218,6 +219,7 @@ struct DeviceState {
     size_t euler_cap = 0;                // cells
     unsigned long long* euler_flags = nullptr;   // 1D driver: bad flag, max CFL (bits)
     int n = 0;                           // state size ns + 1
+    int plain_blocks_per_cu = 0;         // resident workgroups of the plain kernel (0: not asked yet)
     // LDS doubles a lane of the one-cell-per-lane kernels holds: the RODAS4
     // stage vectors u_1..u_5, or from 12 unknowns on up to 80 entries of the
     // LU factors (the device code's kLaneWords never exceeds this)
