@@ -436,17 +436,53 @@ __device__ __forceinline__ void cell_store(const Cell& c, double* __restrict__ T
 }  // namespace chem
 
 // ---- plain form: one cell per lane, cells in index order ----
+// A field larger than the chip holds at once is dealt through one counter
+// (a.head): the lanes of a wave whose cells are done take the next ones, at
+// substep boundaries and kPlainRefill at a time, as in the persistent form.
+// Dealt by the grid instead, a wave lasts as long as its slowest cell, and a
+// front that runs along a grid line puts all the costly waves on the same few
+// XCDs (workgroups go to the XCDs in turn).
+constexpr int kPlainRefill = 16;
+
 extern "C" __global__ void __launch_bounds__(64, 1) chem_plain(chem::IntegrateArgs a)
 {
     using namespace chem;
-    const long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (cell >= a.ncell) return;
     extern __shared__ double lds[];
-    Cell c;
-    cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 1, a.h0 ? a.h0[cell] : a.step.dt);
     double* const ul = lane_lds(lds);
-    while (!c.done) cell_attempt(c, a.par, a.step, ul);
-    cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
+    const int lane = threadIdx.x & 63;
+    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    bool have = false, first = true, more = true;
+    Cell c;
+    c.done = true;
+    while (true) {
+        const unsigned long long idle = __ballot(!have);
+        const int nidle = __popcll(idle);
+        if (more && (first || nidle >= kPlainRefill || nidle == 64)) {
+            if (a.head) {
+                unsigned long long old = 0;
+                if (lane == 0) old = atomicAdd(a.head, (unsigned long long)nidle);
+                old = __shfl(old, 0);
+                if (!have) cell = (long)old + __popcll(idle & below);
+                more = (long)old + nidle < a.ncell;
+            } else {
+                more = false;
+            }
+            if (!have && cell < a.ncell) {
+                cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 1, a.h0 ? a.h0[cell] : a.step.dt);
+                have = true;
+            }
+            first = false;
+        }
+        if (!__any(have)) break;
+        if (have) {
+            cell_attempt(c, a.par, a.step, ul);
+            if (c.done) {
+                cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
+                have = false;
+            }
+        }
+    }
 }
 
 

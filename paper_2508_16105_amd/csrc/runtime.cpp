@@ -249,7 +249,7 @@ int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t
     }
     const int64_t resident = (int64_t)d.num_cu * d.plain_blocks_per_cu * block;
     a.head = nullptr;
-    if (m->wide && lanes > resident) {
+    if (lanes > resident) {
         lanes = resident;
         a.head = d.heads;
         struct { unsigned long long* p; int n; } za{d.heads, 1};
