@@ -339,7 +339,7 @@ struct Emitter {
              "  cdbl* P = (cdbl*)par + z;\n"
              "  cdbl* MW = (cdbl*)&MWTAB[0] + z;\n"
              "  const S T = y[0];\n"
-             "  const S lnT = log(T);\n"
+             "  const S lnT = chem_math::ln(T);\n"
              "  const S iT = chem_math::recip(T);\n"
              "  const S T2 = T * T, T3 = T2 * T, T4 = T2 * T2;\n"
              "  S cpR[NS], HRT[NS], G[NS];\n";
@@ -370,7 +370,7 @@ struct Emitter {
              "#pragma unroll\n  for (int k = 0; k < NS; ++k) wd[k] = 0.0;\n";
         for (const auto& r : m.reactions)
             if (r.kind == RxnKind::Plog) {
-                o << "  const double lnp = log(p);\n";
+                o << "  const double lnp = chem_math::ln(p);\n";
                 break;
             }
     }
@@ -452,33 +452,34 @@ struct Emitter {
                  "    const S r0 = chem_math::exp_poly(lnr0);\n"
                  "    const S Pr = r0 * Mc;\n"
                  "    const bool floored = !(Pr >= 1e-300);\n"
-                 "    const S logPr = floored ? -300.0 : log10(Pr);\n";
+                 "    const S logPr = floored ? S(-300.0) : chem_math::lg(Pr);\n";
             if (r.kind == RxnKind::Troe) {
-                o << "    const S e3 = exp(-T * " << lit(1.0 / r.T3) << ");\n"
-                     "    const S e1 = exp(-T * " << lit(1.0 / r.T1) << ");\n";
+                o << "    const S e3 = chem_math::exp_neg(-T * " << lit(1.0 / r.T3) << ");\n"
+                     "    const S e1 = chem_math::exp_neg(-T * " << lit(1.0 / r.T1) << ");\n";
                 o << "    S Fc = " << lit(1.0 - r.alpha) << "*e3 + " << lit(r.alpha) << "*e1;\n";
                 if (jac)
                     o << "    S dFc = " << lit(-(1.0 - r.alpha) / r.T3) << "*e3 + "
                       << lit(-r.alpha / r.T1) << "*e1;\n";
                 if (r.has_T2) {
-                    o << "    const S e2 = exp(" << lit(-r.T2) << " * iT);\n"
+                    o << "    const S e2 = chem_math::exp_neg(" << lit(-r.T2) << " * iT);\n"
                          "    Fc += e2;\n";
                     if (jac) o << "    dFc += " << lit(r.T2) << "*iT*iT*e2;\n";
                 }
-                o << "    const S logFc = log10(Fc);\n"
+                o << "    const S logFc = chem_math::lg(Fc);\n"
                      "    const S tc = -0.4 - 0.67*logFc;\n"
                      "    const S tn = 0.75 - 1.27*logFc;\n"
                      "    const S tu = logPr + tc;\n"
                      "    const S tden = tn - 0.14*tu;\n"
-                     "    const S tx = tu * chem_math::recip(tden);\n"
-                     "    const S opx2 = 1.0 + tx*tx;\n"
-                     "    const S logF = logFc * chem_math::recip(opx2);\n"
-                     "    const S Fb = exp(" << lit(std::log(10.0)) << " * logF);\n";
+                     "    const S itden = chem_math::recip(tden);\n"
+                     "    const S tx = tu * itden;\n"
+                     "    const S iopx2 = chem_math::recip(1.0 + tx*tx);\n"
+                     "    const S logF = logFc * iopx2;\n"
+                     "    const S Fb = chem_math::exp_neg(" << lit(std::log(10.0)) << " * logF);\n";
                 if (jac) {
-                    o << "    const S tg = -logFc * 2.0 * tx / (opx2*opx2);\n"
-                         "    const S dF_dPr = floored ? 0.0 : tg * tn / (tden*tden);\n"
-                         "    const S dF_dFc = 1.0/opx2 + tg * (-0.67*tn + 1.27*tu) / (tden*tden);\n"
-                         "    const S dlogFc_dT = dFc / (Fc * " << lit(std::log(10.0)) << ");\n";
+                    o << "    const S tg = -logFc * 2.0 * tx * (iopx2*iopx2);\n"
+                         "    const S dF_dPr = floored ? S(0.0) : tg * tn * (itden*itden);\n"
+                         "    const S dF_dFc = iopx2 + tg * (-0.67*tn + 1.27*tu) * (itden*itden);\n"
+                         "    const S dlogFc_dT = dFc * chem_math::recip(Fc * " << lit(std::log(10.0)) << ");\n";
                 }
             } else if (r.kind == RxnKind::Sri) {
                 // F = d [a exp(-b/T) + exp(-T/c)]^X T^e with X = 1 / (1 + log10(P_r)^2)
@@ -487,12 +488,12 @@ struct Emitter {
                                                          : std::string("0.0")) << ";\n"
                      "    const S sec = chem_math::exp_poly(-T * " << lit(1.0 / c[2]) << ");\n"
                      "    const S sY = sea + sec;\n"
-                     "    const S lnsY = log(sY);\n"
+                     "    const S lnsY = chem_math::ln(sY);\n"
                      "    const S sX = chem_math::recip(1.0 + logPr * logPr);\n"
                      "    const S Fb = chem_math::exp_poly(sX * lnsY + " << lit(c[4]) << " * lnT + " << lit(std::log(c[3]))
                   << ");\n";
                 if (jac)
-                    o << "    const S dF_dPr = floored ? 0.0 : lnsY * " << lit(-2.0 / std::log(10.0))
+                    o << "    const S dF_dPr = floored ? S(0.0) : lnsY * " << lit(-2.0 / std::log(10.0))
                       << " * logPr * sX * sX;\n"
                          "    const S dF_dFc = 0.0, dlogFc_dT = 0.0;\n"
                          "    const S dlnF_T = sX * (sea * " << lit(c[1]) << " * iT * iT - sec * " << lit(1.0 / c[2])
@@ -681,12 +682,19 @@ struct Emitter {
         o << "  const S fT = f[0];\n"
              "  const S RT = " << lit(kRu) << " * T;\n"
              "  const S icp = icpm * " << lit(1.0 / kRu) << ";\n";
-        for (int mm = 0; mm < ns; ++mm) {
+        // (the columns of species no reaction changes last, and only if asked for:
+        // a step's unknowns are the others)
+        std::vector<int> cols;
+        for (int pass = 0; pass < 2; ++pass)
+            for (int mm = 0; mm < ns; ++mm)
+                if (inert[mm] == (pass == 1)) cols.push_back(mm);
+        const std::string only = "if constexpr (INERT) ";
+        for (int mm : cols) {
             std::vector<std::pair<double, std::string>> hj;
             for (int k = 0; k < ns; ++k)
                 if (jnz[k][mm])
                     hj.push_back({1.0, "HRT[" + std::to_string(k) + "]*J[" + std::to_string(1 + k) + "][" + std::to_string(1 + mm) + "]"});
-            o << "  { S HJ = " << lin_sum(hj) << ";\n"
+            o << "  " << (inert[mm] ? only : "") << "{ S HJ = " << lin_sum(hj) << ";\n"
                  "    S t = fma(rho, HJ, -Wbar*HS) * (-RT * rcpinv);\n"
                  "    S u = fma(cpR[" << mm << "], icp * " << lit(kRu) << ", -Wbar);\n"
                  "    J[0][" << 1 + mm << "] = fma(-fT, u, t) * MW[" << ns + mm << "]; }\n";
@@ -697,9 +705,9 @@ struct Emitter {
             // J_km = (1/W_m)(W_k Jc_km + Wbar g_k), g_k = f_k - W_k S_k / rho
             o << "  { const S g = fma(-MW[" << k << "], Sk[" << k << "] * irho, f[" << 1 + k << "]);\n"
                  "    const S wg = Wbar * g;\n";
-            for (int mm = 0; mm < ns; ++mm)
-                o << "    J[" << 1 + k << "][" << 1 + mm << "] = fma(J[" << 1 + k << "][" << 1 + mm << "], MW[" << k
-                  << "], wg) * MW[" << ns + mm << "];\n";
+            for (int mm : cols)
+                o << "    " << (inert[mm] ? only : "") << "J[" << 1 + k << "][" << 1 + mm << "] = fma(J[" << 1 + k << "]["
+                  << 1 + mm << "], MW[" << k << "], wg) * MW[" << ns + mm << "];\n";
             o << "    J[" << 1 + k << "][0] = fma(MW[" << k << "] * irho, J[" << 1 + k << "][0] - Sk[" << k
               << "] * iT, f[" << 1 + k << "] * iT); }\n";
         }
@@ -737,7 +745,8 @@ struct Emitter {
         rhs_tail();
         o << "}\n\n";
         // source terms and Jacobian
-        o << "template <class S>\n__device__ __forceinline__ void rhs_jac(const double* __restrict__ par, double p, "
+        o << "// INERT: with the columns of species no reaction changes\n"
+             "template <class S, bool INERT = false>\n__device__ __forceinline__ void rhs_jac(const double* __restrict__ par, double p, "
              "double ip, const S (&y)[N], S (&f)[N], S (&J)[N][N])\n{\n";
         o << "#pragma unroll\n  for (int i = 0; i < N; ++i)\n#pragma unroll\n    for (int j = 0; j < N; ++j) J[i][j] = 0.0;\n";
         prologue(true);
@@ -791,6 +800,12 @@ struct Emitter {
 };
 
 }  // namespace
+
+int active_unknowns(const MechanismData& m)
+{
+    const std::vector<bool> inert = inert_species(m);
+    return 1 + (int)std::count(inert.begin(), inert.end(), false);
+}
 
 std::string generate_mechanism_source(const MechanismData& m) { return Emitter(m).run(); }
 

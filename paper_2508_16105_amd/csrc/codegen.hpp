@@ -12,6 +12,9 @@ namespace chemmi {
 // m: straight-line code for the one-cell-per-lane kernels.
 std::string generate_mechanism_source(const MechanismData& m);
 
+// Unknowns of a step: T and the species some reaction changes.
+int active_unknowns(const MechanismData& m);
+
 // Layout of the wave-cooperative form: 16 lanes per cell, lane i owning the
 // positions r * 16 + i (T, then the species some reaction changes), and the
 // per-cell LDS scratch in doubles.

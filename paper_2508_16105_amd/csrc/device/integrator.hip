@@ -21,19 +21,19 @@ constexpr int NS = mech::NS;
 
 
 // ---- dense LU with partial pivoting, one matrix per lane ----
-// The step matrix is eliminated in the order mech::PERM: T and the species
-// some reaction changes (positions 0 .. NACT-1) first, then the species no
-// reaction changes, whose rows of M = I/(gamma h) - J hold the diagonal alone.
-// Their entries in the first NACT columns are zero, so they never become
-// pivots there and take no row updates; when their own columns come, only
-// such rows remain below the diagonal.  Skipping them is exact: this is dense
-// LU with partial pivoting of the symmetrically permuted matrix, with the
-// structural zeros of those rows left out.  Row interchanges are made with
-// selects (the pivot row differs per lane), on the trailing columns only, and
-// skipped when no lane of the wave needs one; piv[a] records the position
-// swapped into position a at step a (LINPACK order) and bit a of the returned
-// wave-uniform mask says whether any lane swapped at step a.  The diagonal of
-// U is stored as its reciprocal.
+// The unknowns of a step are T and the species some reaction changes, in the
+// order mech::PERM (positions 0 .. NACT-1).  A species no reaction changes has
+// a zero source term and a zero row in the Jacobian, so its row of M =
+// I/(gamma h) - J is the diagonal alone, all its stage vectors are exactly
+// zero, and its column of M meets only those zeros: leaving such species out
+// is exact, bit for bit.  (9 species: 330 multiply-adds a factorisation dense,
+// 240 with their rows left out, 204 without their columns; a tenth of the
+// solves' and stage combinations' work, and 10 doubles of registers.)  Row
+// interchanges are made with selects (the pivot row differs per lane), on the
+// trailing columns only, and skipped when no lane of the wave needs one; piv[a]
+// records the position swapped into position a at step a (LINPACK order) and
+// bit a of the returned wave-uniform mask says whether any lane swapped at
+// step a.  The diagonal of U is stored as its reciprocal.
 constexpr int NACT = mech::NACT;
 
 __device__ __forceinline__ constexpr int P(int a) { return mech::PERM[a]; }
@@ -43,22 +43,22 @@ __device__ __forceinline__ constexpr int P(int a) { return mech::PERM[a]; }
 // per lane, lane-interleaved: word w of lane l at w * 64 + l.  The 64 lanes
 // of a wave touch 64 consecutive doubles (no bank conflicts) and every word
 // sits at a compile-time offset from the lane's base, whatever the workgroup
-// size.  The words hold the RODAS4 stage vectors u_1..u_5 (u_s component k
-// at word s N + k), or, when the step matrix's factors do not fit the lane's
+// size.  The words hold the RODAS4 stage vectors u_1..u_5 (u_s position a
+// at word s NACT + a), or, when the step matrix's factors do not fit the lane's
 // registers (kFactorsInLds), the first factor entries in the order the solves
 // read them, the stage vectors then going to private memory.
 constexpr int kLaneStride = 64;
-// entries of the LU factors the solves read: L below the diagonal of the
-// first NACT positions, and per position a its diagonal and min(a, NACT) of U
-constexpr int kFactorEntries = NACT * (NACT - 1) / 2 + N + (NACT * (NACT - 1)) / 2 + (N - NACT) * NACT;
-// From 12 unknowns the factors no longer fit beside the source-term temporaries
-// and spill to private memory (measured at 14: 1.4 KB a lane), where every
+// entries of the LU factors the solves read
+constexpr int kFactorEntries = NACT * NACT;
+// From 11 unknowns the factors no longer fit beside the source-term temporaries
+// and spill to private memory (measured at 12: 1.4 KB a lane), where every
 // solve waits on them; below, they stay in accumulation registers, whose two
-// moves per read cost less than an LDS load in the solve's chain (m9).
-constexpr bool kFactorsInLds = N >= 12;
+// moves per read cost less than an LDS load in the solve's chain (measured at
+// 9).
+constexpr bool kFactorsInLds = NACT >= 11;
 constexpr int kLdsBudget = 80;     // doubles a lane: 160 KB over four 64-lane waves
 constexpr int kFactorsLds = kFactorsInLds ? (kFactorEntries < kLdsBudget ? kFactorEntries : kLdsBudget) : 0;
-constexpr int kLaneWords = kFactorsInLds ? kFactorsLds : 5 * N;
+constexpr int kLaneWords = kFactorsInLds ? kFactorsLds : 5 * NACT;
 
 __device__ __forceinline__ double* lane_lds(double* lds)
 {
@@ -81,11 +81,11 @@ __host__ __device__ constexpr FactorSlots factor_slots(int count)
             if (s < count) m.slot[mech::PERM[c]][mech::PERM[a]] = s;
             ++s;
         }
-    for (int a = N - 1; a >= 0; --a) {             // back substitution: U by columns
+    for (int a = NACT - 1; a >= 0; --a) {          // back substitution: U by columns
         const int k = mech::PERM[a];
         if (s < count) m.slot[k][k] = s;
         ++s;
-        for (int c = 0; c < (a < NACT ? a : NACT); ++c) {
+        for (int c = 0; c < a; ++c) {
             if (s < count) m.slot[mech::PERM[c]][k] = s;
             ++s;
         }
@@ -130,7 +130,7 @@ __device__ __forceinline__ unsigned lu_factor(double (&A)[N][N], int (&piv)[N], 
                 const bool s = (p == b);
                 const int i = P(b);
 #pragma unroll
-                for (int c = a; c < N; ++c) {
+                for (int c = a; c < NACT; ++c) {
                     const int j = P(c);
                     const double akj = A[k][j], aij = A[i][j];
                     A[k][j] = s ? aij : akj;
@@ -146,18 +146,11 @@ __device__ __forceinline__ unsigned lu_factor(double (&A)[N][N], int (&piv)[N], 
             const double l = A[i][k] * rp;
             A[i][k] = l;
 #pragma unroll
-            for (int c = a + 1; c < N; ++c) {
+            for (int c = a + 1; c < NACT; ++c) {
                 const int j = P(c);
                 A[i][j] = fma(-l, A[k][j], A[i][j]);
             }
         }
-    }
-#pragma unroll
-    for (int a = NACT; a < N; ++a) {     // rows with the diagonal alone
-        const int k = P(a);
-        piv[a] = a;
-        ok = ok && (fabs(A[k][k]) > 0.0);
-        A[k][k] = chem_math::recip(A[k][k]);
     }
     return swaps;
 }
@@ -208,11 +201,11 @@ __device__ __forceinline__ void lu_solve(const double (&A)[N][N], const int (&pi
         }
     }
 #pragma unroll
-    for (int a = N - 1; a >= 0; --a) {
+    for (int a = NACT - 1; a >= 0; --a) {
         const int k = P(a);
         b[k] *= factor<FL>(A, fl, k, k);
 #pragma unroll
-        for (int c = 0; c < (a < NACT ? a : NACT); ++c) {
+        for (int c = 0; c < a; ++c) {
             const int r = P(c);
             b[r] = fma(-factor<FL>(A, fl, r, k), b[k], b[r]);
         }
@@ -220,15 +213,15 @@ __device__ __forceinline__ void lu_solve(const double (&A)[N][N], const int (&pi
 }
 
 
-// What one step leaves for its adjoint, per lane and step: the factors of M
-// (N x N, as lu_factor leaves them), the pivot positions, the swap mask, and
-// the stage vectors u_1..u_6.
+// What one step leaves for its adjoint, per lane and step, by position: the
+// factors of M (as lu_factor leaves them), the pivot positions, the swap mask,
+// and the stage vectors u_1..u_6.
 struct StashLayout {
-    static constexpr int WORDS = N * N + N + 1 + Rodas4::S * N;
-    __device__ static constexpr int lu(int i, int j) { return i * N + j; }
-    __device__ static constexpr int piv(int a) { return N * N + a; }
-    __device__ static constexpr int swaps() { return N * N + N; }
-    __device__ static constexpr int u(int s, int k) { return N * N + N + 1 + s * N + k; }
+    static constexpr int WORDS = NACT * NACT + NACT + 1 + Rodas4::S * NACT;
+    __device__ static constexpr int lu(int a, int b) { return a * NACT + b; }
+    __device__ static constexpr int piv(int a) { return NACT * NACT + a; }
+    __device__ static constexpr int swaps() { return NACT * NACT + NACT; }
+    __device__ static constexpr int u(int s, int a) { return NACT * NACT + NACT + 1 + s * NACT + a; }
 };
 
 // One RODAS4 step from y with step h.  Returns false if the step matrix is
@@ -249,16 +242,17 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
     const double hinv = chem_math::recip(h);
     const double ghinv = hinv * (1.0 / Rodas4::gamma);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
+    for (int a = 0; a < NACT; ++a) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) M[i][j] = -M[i][j];
-        M[i][i] += ghinv;
+        for (int b = 0; b < NACT; ++b) M[P(a)][P(b)] = -M[P(a)][P(b)];
+        M[P(a)][P(a)] += ghinv;
     }
     int piv[N];
     bool ok;
     // the swap mask is the same in every active lane (lu_factor builds it from
     // __any), so it is read into a scalar register once
     const unsigned swaps = __builtin_amdgcn_readfirstlane(lu_factor(M, piv, ok));
+    if (NACT < N) ok = ok && (fabs(ghinv) > 0.0);     // the other rows' diagonal
     if constexpr (kFactorsInLds) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
@@ -269,11 +263,11 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
     if constexpr (STASH) {
         if (stash) {
 #pragma unroll
-        for (int i = 0; i < N; ++i)
+        for (int a = 0; a < NACT; ++a)
 #pragma unroll
-            for (int j = 0; j < N; ++j) stash[StashLayout::lu(i, j)] = M[i][j];
+            for (int b = 0; b < NACT; ++b) stash[StashLayout::lu(a, b)] = M[P(a)][P(b)];
 #pragma unroll
-        for (int a = 0; a < N; ++a) stash[StashLayout::piv(a)] = (double)piv[a];
+        for (int a = 0; a < NACT; ++a) stash[StashLayout::piv(a)] = (double)piv[a];
         stash[StashLayout::swaps()] = (double)swaps;
         }
     }
@@ -281,35 +275,37 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
     // the stage vectors when the factors take the LDS words: private memory
     // (the indices pass through an empty asm so the array is not promoted to
     // registers, which the factors need)
-    double us[kFactorsInLds ? Rodas4::S - 1 : 1][N];
+    double us[kFactorsInLds ? Rodas4::S - 1 : 1][NACT];
     lu_solve<kFactorsInLds>(M, piv, opaque_uniform(swaps), f, ul);
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        if constexpr (kFactorsInLds) us[opaque_index(0)][k] = f[k];
-        else ul[k * kLaneStride] = f[k];
+    for (int a = 0; a < NACT; ++a) {
+        if constexpr (kFactorsInLds) us[opaque_index(0)][a] = f[P(a)];
+        else ul[a * kLaneStride] = f[P(a)];
     }
     if constexpr (STASH) {
         if (stash)
 #pragma unroll
-            for (int k = 0; k < N; ++k) stash[StashLayout::u(0, k)] = f[k];
+            for (int a = 0; a < NACT; ++a) stash[StashLayout::u(0, a)] = f[P(a)];
     }
     double u[N];
 #pragma unroll
     for (int s = 1; s < Rodas4::S; ++s) {
-        double Ys[N], acc[N];
+        double Ys[N], acc[NACT];
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-            double v = y[k], w = 0.0;
+        for (int a = NACT; a < N; ++a) Ys[P(a)] = y[P(a)];
+#pragma unroll
+        for (int a = 0; a < NACT; ++a) {
+            double v = y[P(a)], w = 0.0;
 #pragma unroll
             for (int j = 0; j < s; ++j) {
                 double uj;
-                if constexpr (kFactorsInLds) uj = us[opaque_index(j)][k];
-                else uj = ul[(j * N + k) * kLaneStride];
+                if constexpr (kFactorsInLds) uj = us[opaque_index(j)][a];
+                else uj = ul[(j * NACT + a) * kLaneStride];
                 v = fma(RA[s][j], uj, v);
                 w = fma(RC[s][j], uj, w);
             }
-            Ys[k] = v;
-            acc[k] = w;
+            Ys[P(a)] = v;
+            acc[a] = w;
         }
         if (s == Rodas4::S - 1) {
 #pragma unroll
@@ -317,25 +313,25 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
         }
         mech::rhs(par, p, ip, Ys, u);
 #pragma unroll
-        for (int k = 0; k < N; ++k) u[k] = fma(acc[k], hinv, u[k]);
+        for (int a = 0; a < NACT; ++a) u[P(a)] = fma(acc[a], hinv, u[P(a)]);
         lu_solve<kFactorsInLds>(M, piv, opaque_uniform(swaps), u, ul);
         if (s < Rodas4::S - 1) {
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
-                if constexpr (kFactorsInLds) us[opaque_index(s)][k] = u[k];
-                else ul[(s * N + k) * kLaneStride] = u[k];
+            for (int a = 0; a < NACT; ++a) {
+                if constexpr (kFactorsInLds) us[opaque_index(s)][a] = u[P(a)];
+                else ul[(s * NACT + a) * kLaneStride] = u[P(a)];
             }
         }
         if constexpr (STASH) {
             if (stash)
 #pragma unroll
-                for (int k = 0; k < N; ++k) stash[StashLayout::u(s, k)] = u[k];
+                for (int a = 0; a < NACT; ++a) stash[StashLayout::u(s, a)] = u[P(a)];
         }
     }
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        ynew[k] += u[k];
+        ynew[k] += u[k];      // (u of a species no reaction changes is its zero source term)
         const double sc = atol + rtol * fmax(fabs(y[k]), fabs(ynew[k]));
         const double e = u[k] * chem_math::recip(sc);
         acc = fma(e, e, acc);
@@ -436,43 +432,53 @@ __device__ __forceinline__ void cell_store(const Cell& c, double* __restrict__ T
 }  // namespace chem
 
 // ---- plain form: one cell per lane, cells in index order ----
+extern "C" __global__ void __launch_bounds__(64, 1) chem_plain(chem::IntegrateArgs a)
+{
+    using namespace chem;
+    const long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (cell >= a.ncell) return;
+    extern __shared__ double lds[];
+    Cell c;
+    cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 1, a.h0 ? a.h0[cell] : a.step.dt);
+    double* const ul = lane_lds(lds);
+    while (!c.done) cell_attempt(c, a.par, a.step, ul);
+    cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
+}
+
 // A field larger than the chip holds at once is dealt through one counter
 // (a.head): the lanes of a wave whose cells are done take the next ones, at
 // substep boundaries and kPlainRefill at a time, as in the persistent form.
 // Dealt by the grid instead, a wave lasts as long as its slowest cell, and a
 // front that runs along a grid line puts all the costly waves on the same few
-// XCDs (workgroups go to the XCDs in turn).
+// XCDs (workgroups go to the XCDs in turn): 200,003 cells of the 9-species
+// field 69 ms by the grid, 25 ms dealt.  A kernel of its own, as the refill
+// costs the other registers and a few microseconds.
 constexpr int kPlainRefill = 16;
 
-extern "C" __global__ void __launch_bounds__(64, 1) chem_plain(chem::IntegrateArgs a)
+extern "C" __global__ void __launch_bounds__(64, 1) chem_plain_dealt(chem::IntegrateArgs a)
 {
     using namespace chem;
     extern __shared__ double lds[];
     double* const ul = lane_lds(lds);
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    long cell = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    bool have = false, first = true, more = true;
+    long cell = 0;
+    bool have = false, more = true;
     Cell c;
     c.done = true;
     while (true) {
         const unsigned long long idle = __ballot(!have);
         const int nidle = __popcll(idle);
-        if (more && (first || nidle >= kPlainRefill || nidle == 64)) {
-            if (a.head) {
-                unsigned long long old = 0;
-                if (lane == 0) old = atomicAdd(a.head, (unsigned long long)nidle);
-                old = __shfl(old, 0);
-                if (!have) cell = (long)old + __popcll(idle & below);
-                more = (long)old + nidle < a.ncell;
-            } else {
-                more = false;
+        if (more && nidle >= kPlainRefill) {
+            unsigned long long old = 0;
+            if (lane == 0) old = atomicAdd(a.head, (unsigned long long)nidle);
+            old = __shfl(old, 0);
+            more = (long)old + nidle < a.ncell;
+            if (!have) {
+                cell = (long)old + __popcll(idle & below);
+                have = cell < a.ncell;
+                if (have) cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 1, a.h0 ? a.h0[cell] : a.step.dt);
             }
-            if (!have && cell < a.ncell) {
-                cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 1, a.h0 ? a.h0[cell] : a.step.dt);
-                have = true;
-            }
-            first = false;
         }
         if (!__any(have)) break;
         if (have) {
@@ -499,7 +505,7 @@ extern "C" __global__ void __launch_bounds__(64, 1) chem_eval(EvalArgs a)
     const double p = a.p[cell];
     if (a.J) {
         double J[N][N];
-        mech::rhs_jac(a.par, p, 1.0 / p, y, f, J);
+        mech::rhs_jac<double, true>(a.par, p, 1.0 / p, y, f, J);
 #pragma unroll
         for (int i = 0; i < N; ++i)
 #pragma unroll
@@ -764,20 +770,19 @@ namespace chem {
 __device__ __forceinline__ void lu_solve_t(const double (&A)[N][N], const int (&piv)[N], unsigned swaps,
                                            double (&b)[N])
 {
-    // U^T (only the first NACT rows of U have entries off the diagonal)
+    // U^T
 #pragma unroll
-    for (int a = 0; a < N; ++a) {
+    for (int a = 0; a < NACT; ++a) {
         const int i = P(a);
         double v = b[i];
 #pragma unroll
-        for (int c = 0; c < (a < NACT ? a : NACT); ++c) {
+        for (int c = 0; c < a; ++c) {
             const int j = P(c);
             v = fma(-A[j][i], b[j], v);
         }
         b[i] = v * A[i][i];
     }
-    // L^T and the interchanges in reverse (L has entries below the diagonal in
-    // the first NACT rows and columns only)
+    // L^T and the interchanges in reverse
 #pragma unroll
     for (int a = NACT - 1; a >= 0; --a) {
         const int k = P(a);
@@ -830,13 +835,17 @@ __device__ __noinline__ void step_adjoint(const double* __restrict__ par, double
     unsigned swaps;
     const double hinv = chem_math::recip(h);
     double u[Rodas4::S][N], Ys[Rodas4::S][N];
+    // (the stage vectors of species no reaction changes are zero; their
+    // components of w enter nothing, so they are left at zero too)
+    for (int s = 0; s < Rodas4::S; ++s)
+        for (int k = 0; k < N; ++k) u[s][k] = 0.0;
     if constexpr (FROM_STASH) {
-        for (int i = 0; i < N; ++i)
-            for (int j = 0; j < N; ++j) M[i][j] = stash[StashLayout::lu(i, j)];
-        for (int a = 0; a < N; ++a) piv[a] = (int)stash[StashLayout::piv(a)];
+        for (int a = 0; a < NACT; ++a)
+            for (int b = 0; b < NACT; ++b) M[P(a)][P(b)] = stash[StashLayout::lu(a, b)];
+        for (int a = 0; a < NACT; ++a) piv[a] = (int)stash[StashLayout::piv(a)];
         swaps = (unsigned)stash[StashLayout::swaps()];
         for (int s = 0; s < Rodas4::S; ++s)
-            for (int k = 0; k < N; ++k) u[s][k] = stash[StashLayout::u(s, k)];
+            for (int a = 0; a < NACT; ++a) u[s][P(a)] = stash[StashLayout::u(s, a)];
         for (int k = 0; k < N; ++k) Ys[0][k] = y[k];
         for (int s = 1; s < Rodas4::S; ++s)
             for (int k = 0; k < N; ++k) {
@@ -848,9 +857,9 @@ __device__ __noinline__ void step_adjoint(const double* __restrict__ par, double
         double f[N];
         mech::rhs_jac(par, p, ip, y, f, M);
         const double ghinv = hinv * (1.0 / Rodas4::gamma);
-        for (int i = 0; i < N; ++i) {
-            for (int j = 0; j < N; ++j) M[i][j] = -M[i][j];
-            M[i][i] += ghinv;
+        for (int a = 0; a < NACT; ++a) {
+            for (int b = 0; b < NACT; ++b) M[P(a)][P(b)] = -M[P(a)][P(b)];
+            M[P(a)][P(a)] += ghinv;
         }
         bool ok;
         swaps = lu_factor(M, piv, ok);
@@ -895,7 +904,8 @@ __device__ __noinline__ void step_adjoint(const double* __restrict__ par, double
     }
     const double gsc = jd <= 0 ? 1.0 : 0.0;
     for (int s = Rodas4::S - 1; s >= 0; --s) {
-        for (int k = 0; k < N; ++k) w[s][k] = ub[s][k];
+        for (int k = 0; k < N; ++k) w[s][k] = 0.0;
+        for (int a = 0; a < NACT; ++a) w[s][P(a)] = ub[s][P(a)];
         lu_solve_t(M, piv, swaps, w[s]);
         double Yb[N];
         mech::jtv_param<double, kAdjParamStride>(par, p, ip, Ys[s], w[s], Yb, qA, qb, qE, gsc);

@@ -65,6 +65,48 @@ __device__ __forceinline__ double recip(double x)
     return fma(r, e, r);
 }
 
+// exp(x) where x is not large; very negative arguments (a Troe constant of
+// 1e-50 K) are held where the polynomial's reduced argument is still exact.
+__device__ __forceinline__ double exp_neg(double x) { return exp_poly(fmax(x, -800.0)); }
+
+// ln(x).  x = 2^e m with m in [sqrt(1/2), sqrt(2)), s = (m - 1) / (m + 1) and
+// ln m = 2 atanh(s) = 2 s + 2 s z P(z), z = s^2, P the degree-6 polynomial that
+// interpolates (atanh(s)/s - 1)/z at the Chebyshev nodes of the range
+// (interpolation error 5e-18 of the result), ln 2 in two parts.  Within 2 ulp.
+// The library's log carries the whole evaluation in two doubles (some 90
+// instructions, against 30): its last half bit is far below the rounding of
+// b ln T - Ea/RT that it enters, and with one to three of them per source
+// evaluation they were a tenth of the 13-species one.  Zero, negative
+// arguments, infinity and NaN give NaN (the library's -inf and inf make the
+// stage that meets them fail just the same).  SUB: x may be subnormal.
+template <bool SUB = false>
+__device__ __forceinline__ double ln(double x)
+{
+    const bool small = SUB && x < 2.2250738585072014e-308;
+    const double xs = small ? x * 18014398509481984.0 : x;         // 2^54
+    const unsigned long long ix = (unsigned long long)__double_as_longlong(xs);
+    const unsigned long long t = ix - 0x3fe6a09e00000000ull;        // the bits of sqrt(1/2)
+    const double e = (double)((int)((long long)t >> 52) - (small ? 54 : 0));
+    const double m = __longlong_as_double((long long)(ix - (t & 0xfff0000000000000ull)));
+    const double f = m - 1.0, d = m + 1.0;
+    const double r = recip(d);
+    double s = f * r;
+    s = fma(r, fma(-s, d, f), s);
+    const double z = s * s;
+    double q = fma(0.0730822484252193, z, 0.07665860800277999);
+    q = fma(q, z, 0.09091444562630861);
+    q = fma(q, z, 0.1111110556739754);
+    q = fma(q, z, 0.14285714312987743);
+    q = fma(q, z, 0.19999999999949752);
+    q = fma(q, z, 0.3333333333333335);
+    const double s2 = s + s;
+    const double u = fma(s2, z * q, s2);
+    const double y = fma(e, 0.6931471805599453, fma(e, 2.3190468138462996e-17, u));
+    return x > 0.0 && x <= 1.7976931348623157e308 ? y : __builtin_nan("");
+}
+// log10(x)
+__device__ __forceinline__ double lg(double x) { return ln<true>(x) * 0.4342944819032518; }
+
 }  // namespace chem_math
 
 // ---- forward-mode dual numbers (value, derivative along one direction) ----
@@ -133,6 +175,13 @@ __device__ __forceinline__ Dual recip(Dual x)
     const double r = recip(x.v);
     return {r, -(r * r) * x.d};
 }
+__device__ __forceinline__ Dual exp_neg(Dual x)
+{
+    const double e = exp_neg(x.v);
+    return {e, e * x.d};
+}
+__device__ __forceinline__ Dual ln(Dual x) { return {ln(x.v), x.d * recip(x.v)}; }
+__device__ __forceinline__ Dual lg(Dual x) { return {lg(x.v), x.d * recip(x.v * 2.302585092994045684)}; }
 __device__ __forceinline__ Dual log(Dual x) { return {::log(x.v), x.d / x.v}; }
 __device__ __forceinline__ Dual log10(Dual x) { return {::log10(x.v), x.d / (x.v * 2.302585092994045684)}; }
 

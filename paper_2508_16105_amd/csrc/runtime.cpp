@@ -84,6 +84,7 @@ int device_state(chem_mechanism* m, hipStream_t stream, DeviceState** out)
         d.arch = prop.gcnArchName;
         d.lds_per_block = prop.sharedMemPerBlock;
         d.n = m->data.ns() + 1;
+        d.nact = active_unknowns(m->data);
         HIPCHECK(hipModuleLoadData(&d.module, m->code.data()), "hipModuleLoadData");
         int rc = 0;
         rc = rc ? rc : load_function(d.module, "chem_plain", &d.f_plain);
@@ -100,7 +101,9 @@ int device_state(chem_mechanism* m, hipStream_t stream, DeviceState** out)
         rc = rc ? rc : load_function(d.module, "chem_euler_update", &d.f_euler_update);
         rc = rc ? rc : load_function(d.module, "chem_euler_init", &d.f_euler_init);
         rc = rc ? rc : load_function(d.module, "chem_fixed_step", &d.f_fixed);
+        d.f_dealt = d.f_plain;   // (the wave-cooperative plain kernel does both)
         if (!m->wide) {   // one-cell-per-lane module only
+            rc = rc ? rc : load_function(d.module, "chem_plain_dealt", &d.f_dealt);
             rc = rc ? rc : load_function(d.module, "chem_gather_sample", &d.f_gather);
             rc = rc ? rc : load_function(d.module, "chem_order_key", &d.f_okey);
             rc = rc ? rc : load_function(d.module, "chem_order_scan", &d.f_oscan);
@@ -233,8 +236,7 @@ StepArgs step_args(double dt, double rtol, double atol, const Options& o)
 // The plain kernel over a.ncell cells.  Up to what the device holds at once
 // every cell has its place in the grid; above that the resident workgroups
 // take the cells through a counter (cleared first; the per-device state's
-// queue heads, which one call at a time uses).  Both sides measured on the
-// 9-species field: see the kernel.
+// queue heads, which one call at a time uses).
 namespace {
 
 int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t stream)
@@ -244,7 +246,7 @@ int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t
     const int block = m->wide ? m->layout.block() : 64;
     if (!d.plain_blocks_per_cu) {
         int n = 0;
-        HIPCHECK(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, d.f_plain, block, shmem), "occupancy");
+        HIPCHECK(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, d.f_dealt, block, shmem), "occupancy");
         d.plain_blocks_per_cu = std::max(1, n);
     }
     const int64_t resident = (int64_t)d.num_cu * d.plain_blocks_per_cu * block;
@@ -255,7 +257,7 @@ int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t
         struct { unsigned long long* p; int n; } za{d.heads, 1};
         if (int rc = launch_1d(d.f_zero, 1, 64, &za, sizeof za, stream, "chem_zero_u64")) return rc;
     }
-    return launch_1d(d.f_plain, lanes, block, &a, sizeof a, stream, "chem_plain", shmem);
+    return launch_1d(a.head ? d.f_dealt : d.f_plain, lanes, block, &a, sizeof a, stream, "chem_plain", shmem);
 }
 
 }  // namespace
@@ -1021,7 +1023,7 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     double* stash = nullptr;
     if (!m->wide && K > 1) {
         const char* e = std::getenv("CHEM_ADJOINT_STASH");
-        const size_t words = (size_t)n * n + n + 1 + 6 * (size_t)n;
+        const size_t na = (size_t)d->nact, words = na * na + na + 1 + 6 * na;   // StashLayout::WORDS
         const size_t bytes = (size_t)nslot * K * words * sizeof(double);
         size_t freeb = 0, totalb = 0;
         HIPCHECK(hipMemGetInfo(&freeb, &totalb), "device memory info");
@@ -1034,7 +1036,7 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     double* trail = nullptr;
     if (!m->wide && K == 1) {
         const char* e = std::getenv("CHEM_ADJOINT_STASH");
-        const size_t words = (size_t)n * n + n + 1 + 6 * (size_t)n;
+        const size_t na = (size_t)d->nact, words = na * na + na + 1 + 6 * na;   // StashLayout::WORDS
         const size_t slots = (size_t)th + (size_t)ncell;
         size_t freeb = 0, totalb = 0;
         HIPCHECK(hipMemGetInfo(&freeb, &totalb), "device memory info");

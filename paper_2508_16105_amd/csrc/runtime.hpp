@@ -185,7 +185,8 @@ struct DeviceState {
                   f_stats = nullptr, f_persistent = nullptr, f_reset = nullptr, f_gather = nullptr,
                   f_okey = nullptr, f_oscan = nullptr, f_oscatter = nullptr, f_adjoint = nullptr,
                   f_rparams = nullptr, f_src_begin = nullptr, f_src_end = nullptr, f_euler_prim = nullptr,
-                  f_euler_update = nullptr, f_euler_init = nullptr;
+                  f_euler_update = nullptr, f_euler_init = nullptr, f_adj_size = nullptr,
+                  f_dealt = nullptr;
     double* par = nullptr;               // 3 * nr device doubles
     uint64_t par_version = 0;
     unsigned long long* stats = nullptr; // 4 counters
@@ -220,10 +221,11 @@ struct DeviceState {
     unsigned long long* euler_flags = nullptr;   // 1D driver: bad flag, max CFL (bits)
     int n = 0;                           // state size ns + 1
     int plain_blocks_per_cu = 0;         // resident workgroups of the plain kernel (0: not asked yet)
+    int nact = 0;                        // unknowns of a step (active_unknowns)
     // LDS doubles a lane of the one-cell-per-lane kernels holds: the RODAS4
-    // stage vectors u_1..u_5, or from 12 unknowns on up to 80 entries of the
+    // stage vectors u_1..u_5, or from 11 unknowns on up to 80 entries of the
     // LU factors (the device code's kLaneWords never exceeds this)
-    int lane_words() const { return n >= 12 ? 80 : 5 * n; }
+    int lane_words() const { return nact >= 11 ? 80 : 5 * nact; }
     unsigned stage_lds(int block) const { return (unsigned)(block * lane_words() * sizeof(double)); }
 };
 
