@@ -265,13 +265,13 @@ def step_fixed(mech: Mechanism, T, p, Y, h, rtol=1e-8, atol=1e-12, stream=None):
 
 
 def integrate_adjoint(mech: Mechanism, T0, p, Y0, dt, rtol, atol, gT, gY, *, stats=True,
-                      stream=None, checkpoint_every=0, allow_failed=False, forward_nacc=None, **opts):
+                      stream=None, checkpoint_every=0, allow_failed=False, forward_nacc=None, end_state=True, **opts):
     """Discrete adjoint of the frozen-step map.  Returns
     (gT0, gY0, g_lnA, g_b, g_Ea, T_end, Y_end, stats).  Failed cells (with
     allow_failed) get NaN gT0/gY0 and add nothing to the parameter gradients.
     forward_nacc: the int32 per-cell accepted steps of a forward integration
     of the same input (integrate's nacc), which spares the adjoint its own
-    sizing pass."""
+    sizing pass.  end_state=False: T_end and Y_end are not wanted (None)."""
     torch = _torch()
     n = T0.shape[0]
     for t, nm, sh in ((T0, "T0", (n,)), (p, "p", (n,)), (Y0, "Y0", (n, mech.ns)),
@@ -281,8 +281,8 @@ def integrate_adjoint(mech: Mechanism, T0, p, Y0, dt, rtol, atol, gT, gY, *, sta
     gT0 = torch.empty(n, dtype=torch.float64, device=dev)
     gY0 = torch.empty((n, mech.ns), dtype=torch.float64, device=dev)
     ga, gb, ge = (torch.empty(mech.nr, dtype=torch.float64, device=dev) for _ in range(3))
-    Te = torch.empty(n, dtype=torch.float64, device=dev)
-    Ye = torch.empty((n, mech.ns), dtype=torch.float64, device=dev)
+    Te = torch.empty(n, dtype=torch.float64, device=dev) if end_state else None
+    Ye = torch.empty((n, mech.ns), dtype=torch.float64, device=dev) if end_state else None
     s = _lib.Stats() if stats else None
     if forward_nacc is not None:
         _check_tensor(forward_nacc, "forward_nacc", (n,), dtype=torch.int32)
@@ -327,7 +327,7 @@ def _make_autograd():
             gYe = torch.zeros_like(Y) if gYe is None else gYe.contiguous().to(torch.float64)
             gT0, gY0, ga, gb, ge, _, _, _ = integrate_adjoint(mech, T, p, Y, ctx.dt, ctx.rtol,
                                                               ctx.atol, gTe, gYe, stats=False,
-                                                              forward_nacc=ctx.nacc)
+                                                              forward_nacc=ctx.nacc, end_state=False)
             return None, gT0, None, gY0, ga, gb, ge, None, None, None
 
     return ChemIntegrate

@@ -35,6 +35,7 @@ def embed_device_source():
     out = "// generated from device/*.hip by build.py; do not edit\n"
     for var, name in (("kMathSource", "math.hip"), ("kCommonSource", "common.hip"),
                       ("kIntegratorSource", "integrator.hip"), ("kWideSource", "wide.hip"),
+                      ("kWideAdjointSource", "wide_adjoint.hip"),
                       ("kEulerSource", "euler.hip")):
         src = (CSRC / "device" / name).read_text()
         assert f"){delim}\"" not in src

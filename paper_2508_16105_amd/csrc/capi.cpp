@@ -131,7 +131,7 @@ int finish_load(std::unique_ptr<chem_mechanism> m, chem_mechanism** out)
         // mechanisms above 9 species, which spill, it raised the spill
         // (13 species: 1,392 -> 1,604 B per lane) and the run time (+18 %),
         // so those keep the clamped conversion
-        m->source = device_source(generate_mechanism_source(m->data), false, m->data.ns() + 1 <= 10);
+        m->source = device_source(generate_mechanism_source(m->data), DeviceForm::Lane, m->data.ns() + 1 <= 10);
     } else {
         m->layout = wide_layout(m->data);
         if (m->layout.G == 0)
@@ -139,7 +139,10 @@ int finish_load(std::unique_ptr<chem_mechanism> m, chem_mechanism** out)
                                                      "coefficient over 3 on a reaction side, |dnu| over 4, or over "
                                                      "511 third-body or falloff reactions, or over 511 PLOG reactions)");
         m->wide = true;
-        m->source = device_source(generate_wide_source(m->data, m->layout), true, true);
+        m->source = device_source(generate_wide_source(m->data, m->layout), DeviceForm::Wide, true);
+        m->rows = row_layout(m->data);
+        const std::string adjoint = device_source(generate_row_source(m->data, m->rows), DeviceForm::WideAdjoint, true);
+        if (int rc = build_code_object(adjoint, m->adjoint_code, err)) return set_error(rc, err);
     }
     if (int rc = build_code_object(m->source, m->code, err, &m->cache_file)) return set_error(rc, err);
     // with a gfx950 device current, load the code there now, so that the
@@ -509,7 +512,7 @@ int chem_integrate_adjoint(const chem_mechanism* mc, int64_t ncell, const double
         Te = (double*)own;
         Ye = Te + ncell;
     }
-    int rc = run_adjoint(m, ncell, T0, p, Y0, dt, rtol, atol, gT, gY, gT0, gY0, g_lnA, g_b, g_Ea, Te, Ye, o,
+    int rc = run_adjoint(m, ncell, T0, p, Y0, dt, rtol, atol, gT, gY, gT0, gY0, g_lnA, g_b, g_Ea, Te, Ye, o, T_end != nullptr,
                          stats, (hipStream_t)stream);
     if (own) {
         (void)hipStreamSynchronize((hipStream_t)stream);

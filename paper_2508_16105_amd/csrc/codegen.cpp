@@ -867,25 +867,18 @@ WideLayout wide_layout(const MechanismData& m)
     for (int j = 0; j < nr; ++j)
         if (m.reactions[j].reversible && !kc.product_form[j]) w.lnkc = true;
     // the scratch of a cell, as the device code lays it out
-    const int sp = ns + 1, nrw = nr + 1, mol = std::max(w.molr, w.molp);
+    const int sp = ns + 1, nrw = nr + 1;
     const int l_a = (w.lnkc ? 5 : 4) * sp;
     const int fwd = l_a + std::max(16 * w.r, std::max(5, w.molr + w.molp) * nrw + w.ntb * (1 + w.maxp));
-    const int rev = 2 * (l_a + 2 * sp + 2 * mol * nrw + 2 * (w.ntb * w.maxp + 1));    // dual numbers
     // cells 16 doubles apart modulo the 64 banks, so two cells' rows do not collide
     auto pad = [](int n) { return n + (48 - n % 32) % 32; };
     w.lds_cell = pad(fwd);
-    w.adj_lds_cell = pad(std::max(fwd, rev));
     const int words = (w.molr + 3) / 4 + (w.molp + 3) / 4 + 1, npt = 16 * (w.r + w.ri);
     w.table = 3 * nr + 38 * npt + (11 + w.maxp) * w.ntb + (words * nr + w.maxp * w.ntb + 1) / 2;
     // a workgroup is four waves of four cells that share the tables; fewer waves,
     // then fewer cells a wave, where that does not fit the 160 KB of LDS
-    auto shape = [&](int cell, int& wpb, int& cpw) {
-        wpb = cpw = 4;
-        while (wpb * cpw > 1 && (size_t)(w.table + wpb * cpw * cell) * sizeof(double) > 160 * 1024)
-            (wpb > 1 ? wpb : cpw) /= 2;
-    };
-    shape(w.lds_cell, w.wpb, w.cpw);
-    shape(w.adj_lds_cell, w.awpb, w.acpw);
+    while (w.wpb * w.cpw > 1 && (size_t)(w.table + w.wpb * w.cpw * w.lds_cell) * sizeof(double) > 160 * 1024)
+        (w.wpb > 1 ? w.wpb : w.cpw) /= 2;
     return w;
 }
 
@@ -937,9 +930,8 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
       << "constexpr int MOLR = " << w.molr << ", MOLP = " << w.molp << ", MAXDNU = " << maxdnu << ";\n"
       << "constexpr int NTB = " << w.ntb << ", MAXP = " << w.maxp << ";\n"
       << "constexpr int FULL_ROUNDS = " << full_rounds << ";   // leading rounds with slots other than elementary\n"
-      << "constexpr int LDS_CELL = " << w.lds_cell << ", ADJ_LDS_CELL = " << w.adj_lds_cell
-      << ";   // doubles of scratch per cell\n"
-      << "constexpr int CPW = " << w.cpw << ", ACPW = " << w.acpw << ";   // cells per wave\n"
+      << "constexpr int LDS_CELL = " << w.lds_cell << ";   // doubles of scratch per cell\n"
+      << "constexpr int CPW = " << w.cpw << ";   // cells per wave\n"
       << "constexpr int WPS = " << w.waves_per_simd() << ";   // waves per SIMD the registers are shared by\n"
       << "constexpr double RU = " << lit(kRu) << ";\n"
       << "constexpr double RU_PATM = " << lit(kRu / kPatm) << ", PATM_RU = " << lit(kPatm / kRu) << ";\n"
@@ -1108,7 +1100,7 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
         for (size_t t = 0; t < n; ++t)
             for (int i = 0; i < 16; ++i) l.data.push_back(t < lanes[i].size() ? lanes[i][t] : padding);
     };
-    Lists wl, dl, dgl, srl, sxl, spl;
+    Lists wl, dl, dgl;
     for (int r = 0; r < w.r; ++r) {
         std::vector<std::vector<int>> lw(16), ld(16);
         for (int i = 0; i < 16; ++i) {
@@ -1182,44 +1174,18 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
         }
         if (part == 0) jgact = (int)grow.size();
     }
-    for (int r = 0; r < w.r + w.ri; ++r) {
-        std::vector<std::vector<int>> lr(16), lx(16), lp(16);
-        for (int i = 0; i < 16; ++i) {
-            const int sp0 = pspec[16 * r + i];
-            if (sp0 < 0) continue;
-            const int k = inv[sp0];
-            for (int s = 0; s < nr; ++s) {
-                for (size_t q = 0; q < rs[s].size(); ++q)
-                    if (rs[s][q] == k) lr[i].push_back((int)q * nrw + s);
-                if (m.reactions[order[s]].reversible)
-                    for (size_t q = 0; q < ps[s].size(); ++q)
-                        if (ps[s][q] == k) lp[i].push_back((int)q * nrw + s);
-            }
-            for (int t = 0; t < w.ntb; ++t)
-                for (int q = 0; q < w.maxp; ++q)
-                    if (tsp[(size_t)q * w.ntb + t] == k && tc[(size_t)q * w.ntb + t] != 0.0) lx[i].push_back(t * w.maxp + q);
-        }
-        add(srl, lr, zero);
-        add(spl, lp, zero);
-        add(sxl, lx, w.ntb * w.maxp);
+    // (the lists follow one another in the order the evaluation walks them; two
+    // spare rows at the end, as words are loaded two rows ahead)
+    std::vector<int> rl;
+    for (const auto& q : {std::make_pair("W", &wl), std::make_pair("D", &dl), std::make_pair("DG", &dgl)}) {
+        ints(std::string("constexpr int ") + q.first + "LEN", q.second->len);
+        rl.insert(rl.end(), q.second->data.begin(), q.second->data.end());
     }
-    // (a table's lists follow one another in the order the evaluation walks
-    // them; two spare rows at the end, as words are loaded two rows ahead)
-    auto table = [&](const std::string& nm, std::initializer_list<std::pair<const char*, const Lists*>> parts) {
-        std::vector<int> data;
-        for (const auto& q : parts) {
-            ints(std::string("constexpr int ") + q.first + "LEN", q.second->len);
-            data.insert(data.end(), q.second->data.begin(), q.second->data.end());
-        }
-        data.insert(data.end(), 8 * 16, 0);
-        ints(ci + nm, data);
-    };
+    rl.insert(rl.end(), 8 * 16, 0);
     o << "// by row: production rates (reaction slot, net coefficient); third-body part of a\n"
          "// Jacobian row (d q / d [M] of the slots that change the species); the species'\n"
          "// own column of it\n";
-    table("RL", {{"W", &wl}, {"D", &dl}, {"DG", &dgl}});
-    o << "// transposed product, by column: reactant slots, third-body corrections, product slots\n";
-    table("TL", {{"SR", &srl}, {"SX", &sxl}, {"SP", &spl}});
+    ints(ci + "RL", rl);
     o << "// Jacobian rows, other columns: partials of the slots and third-body corrections,\n"
          "// in groups of columns\n"
       << "constexpr int JGW = " << jgw << ", JGACT = " << jgact << ", JGALL = " << grow.size() << ";\n";
@@ -1228,6 +1194,266 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
     ints("constexpr int JGCOL", gcol);
     jdata.insert(jdata.end(), 2 * jgw * 16, 0);
     ints(ci + "JL", jdata);
+    o << "}  // namespace mech\n";
+    return o.str();
+}
+
+// ---- the wave-cooperative adjoint: one matrix row per lane ----
+
+RowLayout row_layout(const MechanismData& m)
+{
+    RowLayout w;
+    const int ns = m.ns(), nr = m.nr(), n = ns + 1;
+    if (n > 64) {
+        w.G = 0;
+        return w;
+    }
+    w.G = 16;
+    while (w.G < n) w.G *= 2;
+    w.maxt = 1;
+    for (const auto& r : m.reactions) w.maxt = std::max<int>(w.maxt, (int)std::max(r.reac.size(), r.prod.size()));
+    if (w.maxt > 3) {
+        w.G = 0;
+        return w;
+    }
+    for (const auto& r : m.reactions) {   // the packed reaction table's field widths
+        for (const auto* side : {&r.reac, &r.prod})
+            for (const auto& t : *side)
+                if (t.nu > 3) w.G = 0;
+        if (r.dnu < -4 || r.dnu > 3) w.G = 0;
+    }
+    int n_eff = 0, n_plog = 0;
+    for (const auto& r : m.reactions) {
+        if (r.kind == RxnKind::Plog) ++n_plog;
+        else if (r.kind != RxnKind::Elementary) ++n_eff;
+    }
+    if (n_eff > 511 || n_plog > 511 || nr > 65535 || w.G == 0) {
+        w.G = 0;
+        return w;
+    }
+    w.nslot = 2 * w.maxt;
+    w.pw = w.nslot + 2;
+    w.jw = (ns + 1) % 2 ? ns + 1 : ns + 2;
+    w.l_y = 0;
+    w.l_c = w.l_y + n;
+    w.l_g = w.l_c + ns;
+    w.l_h = w.l_g + ns;
+    w.l_q = w.l_h + ns;
+    w.l_p = w.l_q + nr;
+    w.l_j = w.l_p + nr * w.pw;
+    w.l_t0 = w.l_j + ns * w.jw;
+    w.l_w = w.l_t0 + ns;
+    w.lds_cell = w.l_w + n;
+    w.adj_lds_cell = 2 * w.lds_cell + 2 * n;
+    return w;
+}
+
+std::string generate_row_source(const MechanismData& m, const RowLayout& w)
+{
+    Emitter e(m);
+    std::ostringstream& o = e.o;
+    const int ns = m.ns(), nr = m.nr();
+    o << "// generated mechanism tables (wave-cooperative adjoint): " << m.name << " (" << ns << " species, " << nr
+      << " reactions)\n"
+      << "namespace mech {\n"
+      << "constexpr int NS = " << ns << ";\n"
+      << "constexpr int NR = " << nr << ";\n"
+      << "constexpr int N = NS + 1;\n"
+      << "constexpr int G = " << w.G << ";            // lanes per cell\n"
+      << "constexpr int MAXT = " << w.maxt << ";         // most terms on a reaction side\n"
+      << "constexpr int NSLOT = " << w.nslot << ", PW = " << w.pw << ", JW = " << w.jw << ";\n"
+      << "constexpr int L_Y = " << w.l_y << ", L_C = " << w.l_c << ", L_G = " << w.l_g << ", L_H = " << w.l_h
+      << ", L_Q = " << w.l_q << ", L_P = " << w.l_p << ", L_J = " << w.l_j << ", L_T0 = " << w.l_t0
+      << ", L_W = " << w.l_w << ";\n"
+      << "constexpr int LDS_CELL = " << w.lds_cell << ";  // doubles of LDS scratch per cell\n"
+      << "constexpr int ADJ_LDS_CELL = " << w.adj_lds_cell << ";  // per cell in the adjoint\n"
+      << "constexpr double RU = " << lit(kRu) << ";\n"
+      << "constexpr double LN_PATM_R = " << lit(std::log(kPatm / kRu)) << ";\n"
+      << "constexpr double LN10 = " << lit(std::log(10.0)) << ";\n";
+    e.thermo_table();
+    o << "__constant__ double TMID[NS] = {";
+    for (int k = 0; k < ns; ++k) o << lit(m.species[k].tmid) << (k + 1 < ns ? ", " : "};\n");
+    // reactions in evaluation order: grouped by kind so a round of lanes mostly
+    // takes one branch
+    std::vector<int> order;
+    for (int kind = 0; kind < 6; ++kind)
+        for (int j = 0; j < nr; ++j)
+            if ((int)m.reactions[j].kind == kind) order.push_back(j);
+    std::vector<int> slot_of(nr);
+    for (int s = 0; s < nr; ++s) slot_of[order[s]] = s;
+    // per slot: its EFF row (third body and falloff) or its PLOG table (PLOG)
+    std::vector<int> effrow(nr, -1);
+    int neff = 0, nplog = 0;
+    for (int s = 0; s < nr; ++s) {
+        const RxnKind k = m.reactions[order[s]].kind;
+        if (k == RxnKind::Plog) effrow[s] = nplog++;
+        else if (k != RxnKind::Elementary) effrow[s] = neff++;
+    }
+    auto ints = [&](const char* name, const std::vector<int>& v) {
+        o << "__constant__ int " << name << "[" << std::max<size_t>(v.size(), 1) << "] = {";
+        if (v.empty()) o << "0";
+        for (size_t i = 0; i < v.size(); ++i) o << v[i] << (i + 1 < v.size() ? ", " : "");
+        o << "};\n";
+    };
+    auto dbls = [&](const char* name, const std::vector<double>& v) {
+        o << "__constant__ double " << name << "[" << std::max<size_t>(v.size(), 1) << "] = {";
+        if (v.empty()) o << "0.0";
+        for (size_t i = 0; i < v.size(); ++i) o << lit(v[i]) << (i + 1 < v.size() ? ", " : "");
+        o << "};\n";
+    };
+    // per slot: original index; species of the MAXT reactant then MAXT product
+    // slots (-1: unused)
+    std::vector<int> orig, sp;
+    std::vector<double> low, troe, eff, plog;
+    std::vector<int> plog_off(1, 0);
+    for (int s = 0; s < nr; ++s) {
+        const auto& r = m.reactions[order[s]];
+        orig.push_back(order[s]);
+        for (int t = 0; t < w.maxt; ++t) sp.push_back(t < (int)r.reac.size() ? r.reac[t].sp : -1);
+        for (int t = 0; t < w.maxt; ++t) sp.push_back(t < (int)r.prod.size() ? r.prod[t].sp : -1);
+        low.insert(low.end(), {r.lnA0, r.b0, r.EaR0});
+        const bool tr = r.kind == RxnKind::Troe;
+        if (r.kind == RxnKind::Sri)
+            troe.insert(troe.end(), {r.sri[0], -r.sri[1], 1.0 / r.sri[2], r.sri[1], std::log(r.sri[3]), r.sri[4],
+                                     0.0, 0.0});
+        else
+            troe.insert(troe.end(), {tr ? 1.0 - r.alpha : 0.0, tr ? r.alpha : 0.0, tr ? 1.0 / r.T3 : 0.0,
+                                     tr ? 1.0 / r.T1 : 0.0, tr && r.has_T2 ? r.T2 : 0.0,
+                                     tr ? -(1.0 - r.alpha) / r.T3 : 0.0, tr ? -r.alpha / r.T1 : 0.0,
+                                     tr && r.has_T2 ? 1.0 : 0.0});
+        if (r.kind == RxnKind::Plog) {
+            for (const auto& e : r.plog) plog.insert(plog.end(), {e.lnp, e.lnA, e.b, e.EaR});
+            plog_off.push_back((int)(plog.size() / 4));
+        } else if (effrow[s] >= 0) {
+            for (int k = 0; k < ns; ++k) eff.push_back(r.eff[k]);
+        }
+    }
+    // packed per slot, for one load per reaction round: species slots (8 bits
+    // each: species index + 1 in the low 6 bits, coefficient in the top 2;
+    // 0 = unused) in two words, then kind | irreversible << 3 | (dnu + 4) << 4 |
+    // (EFF row or PLOG table + 1) << 7 | orig << 16
+    {
+        std::vector<int> pack;
+        for (int s = 0; s < nr; ++s) {
+            const auto& r = m.reactions[order[s]];
+            unsigned long long slots = 0;
+            for (int t = 0; t < 2 * w.maxt; ++t) {
+                const bool isr = t < w.maxt;
+                const auto& side = isr ? r.reac : r.prod;
+                const int q = isr ? t : t - w.maxt;
+                unsigned v = 0;
+                if (q < (int)side.size()) v = (unsigned)(side[q].sp + 1) | ((unsigned)side[q].nu << 6);
+                slots |= (unsigned long long)v << (8 * t);
+            }
+            pack.push_back((int)(unsigned)(slots & 0xffffffffull));
+            pack.push_back((int)(unsigned)(slots >> 32));
+            pack.push_back((int)((unsigned)r.kind | ((r.reversible ? 0u : 1u) << 3) | ((unsigned)(r.dnu + 4) << 4) |
+                                 ((unsigned)(effrow[s] + 1) << 7) | ((unsigned)order[s] << 16)));
+        }
+        o << "// per slot: species slots (two words, 8 bits each: index + 1 | nu << 6), then\n"
+             "// kind | irreversible << 3 | (dnu + 4) << 4 | (EFF row or PLOG table + 1) << 7 |\n"
+             "// original index << 16\n";
+        ints("RX_PACK", pack);
+    }
+    o << "// reactions in evaluation order (slot s): original index (kind, species\n"
+         "// slots and coefficients are in RX_PACK)\n";
+    ints("RX_ORIG", orig);
+    o << "// low-pressure limit (ln A0 SI, b0, Ea0/R); Troe: 1-alpha, alpha, 1/T***,\n"
+         "// 1/T*, T**, -(1-alpha)/T***, -alpha/T*, [T** given]; SRI: a, -b, 1/c, b, ln d, e\n";
+    dbls("RX_LOW", low);
+    dbls("RX_TROE", troe);
+    {
+        bool sri = false, irrev = false;
+        for (const auto& r : m.reactions) {
+            sri = sri || r.kind == RxnKind::Sri;
+            irrev = irrev || !r.reversible;
+        }
+        o << "// reaction forms present (the kernels leave out the code of the absent ones)\n"
+             "constexpr bool HAS_PLOG = " << (nplog > 0 ? "true" : "false") << ";\n"
+             "constexpr bool HAS_SRI = " << (sri ? "true" : "false") << ";\n"
+             "constexpr bool HAS_IRREV = " << (irrev ? "true" : "false") << ";\n";
+    }
+    o << "// PLOG tables: entries RX_PLOG_OFF[t] .. RX_PLOG_OFF[t+1] of (ln p, ln A SI, b, Ea/R)\n";
+    ints("RX_PLOG_OFF", plog_off);
+    dbls("RX_PLOG", plog);
+    o << "// third-body efficiencies, one dense row per non-elementary reaction\n";
+    dbls("EFF", eff);
+    // species -> reactions that change it (slot, net coefficient)
+    std::vector<int> off(1, 0), srx, snu;
+    for (int k = 0; k < ns; ++k) {
+        for (int s = 0; s < nr; ++s) {
+            const auto& r = m.reactions[order[s]];
+            int v = 0;
+            for (auto& t : r.reac) if (t.sp == k) v -= t.nu;
+            for (auto& t : r.prod) if (t.sp == k) v += t.nu;
+            if (v) {
+                srx.push_back(s);
+                snu.push_back(v);
+            }
+        }
+        while ((srx.size() - off.back()) % 4) {   // padded to a multiple of 4 (coefficient 0)
+            srx.push_back(0);
+            snu.push_back(0);
+        }
+        off.push_back((int)srx.size());
+    }
+    o << "// species k: the reactions that change it, SP_RX[SP_OFF[k] .. SP_OFF[k+1]),\n"
+         "// with net coefficients SP_NU (padded to a multiple of 4 by coefficient 0)\n";
+    ints("SP_OFF", off);
+    ints("SP_RX", srx);
+    ints("SP_NU", snu);
+    // the same entries packed for the Jacobian rows, so one round of loads gives
+    // everything an entry needs: slot | (net coefficient & 255) << 16, then the
+    // species of the reaction's slots 0-3 and 4-5 as bytes (index + 1, 0 unused)
+    {
+        std::vector<int> jp;
+        for (size_t e = 0; e < srx.size(); ++e) {
+            const int slot = srx[e];
+            jp.push_back((int)((unsigned)slot | (((unsigned)snu[e] & 255u) << 16)));
+            unsigned b[2] = {0u, 0u};
+            for (int t = 0; t < w.nslot; ++t) {
+                const int spc = sp[slot * w.nslot + t];
+                b[t / 4] |= (unsigned)(spc + 1) << (8 * (t % 4));
+            }
+            jp.push_back((int)b[0]);
+            jp.push_back((int)b[1]);
+        }
+        o << "// per SP entry: slot | (net coefficient & 255) << 16, slot species 0-3, 4-5 (bytes, index + 1)\n";
+        ints("SP_JPACK", jp);
+    }
+    // third-body and falloff reactions t (EFF row t): their slot, and the net
+    // coefficient of every species in them (the dense third-body part of the
+    // Jacobian rows)
+    std::vector<int> tbslot;
+    std::vector<double> nutb;
+    for (int s = 0; s < nr; ++s)
+        if (effrow[s] >= 0 && m.reactions[order[s]].kind != RxnKind::Plog) tbslot.push_back(s);
+    for (int k = 0; k < ns; ++k)
+        for (int s : tbslot) {
+            const auto& r = m.reactions[order[s]];
+            int v = 0;
+            for (auto& t : r.reac) if (t.sp == k) v -= t.nu;
+            for (auto& t : r.prod) if (t.sp == k) v += t.nu;
+            nutb.push_back((double)v);
+        }
+    o << "constexpr int NTB = " << tbslot.size() << ";\n"
+         "static_assert(NTB == 0 || sizeof(EFF) == sizeof(double) * NTB * NS, \"one EFF row per third-body "
+         "reaction\");\n"
+         "// third-body or falloff reaction t: its slot (EFF row t); the net coefficient of\n"
+         "// species k in it as a 4-bit field (coefficient + 8), eight per word:\n"
+         "// NU_TB4[k * NTBW + t / 8] >> (4 (t % 8))\n";
+    ints("TB_SLOT", tbslot);
+    {
+        const int ntb = (int)tbslot.size(), ntbw = std::max(1, (ntb + 7) / 8);
+        std::vector<int> packed((size_t)ns * ntbw, 0);
+        for (int k = 0; k < ns; ++k)
+            for (int t = 0; t < ntb; ++t) {
+                const int v = (int)nutb[(size_t)k * ntb + t];
+                packed[(size_t)k * ntbw + t / 8] |= (int)((unsigned)(v + 8) << (4 * (t % 8)));
+            }
+        o << "constexpr int NTBW = " << ntbw << ";\n";
+        ints("NU_TB4", packed);
+    }
     o << "}  // namespace mech\n";
     return o.str();
 }

@@ -19,8 +19,8 @@
 // A species no reaction changes has a zero source term and a zero row in the
 // Jacobian, so all its stage vectors are exactly zero and its column of the
 // step matrix never meets anything but zeros: the forward step is the
-// NACT x NACT system.  Such species enter the mixture sums, the third-body
-// concentrations and, in the adjoint, the outputs.
+// NACT x NACT system.  Such species enter the mixture sums and the third-body
+// concentrations.
 //
 // Per source-term evaluation:
 //   - species thermo (NASA-7) and equilibrium factors e^{+-G} in the lanes of
@@ -29,8 +29,7 @@
 //     of the group ending with the same bits;
 //   - reactions 16 at a time (lane i: slot q * 16 + i), those with third-body,
 //     falloff or PLOG terms first, so that only the leading rounds run that code;
-//   - production rates, Jacobian rows and transposed products gathered by each
-//     lane from the cell's LDS through per-position lists padded to the
+//   - production rates and Jacobian rows gathered by each lane from the cell's LDS through per-position lists padded to the
 //     longest of the 16 lanes, so every loop has a compile-time length and
 //     the sums have a fixed order (reproducible results).
 //
@@ -45,7 +44,6 @@ using chem::RC;
 using chem::Rodas4;
 using chem::StepArgs;
 using chem::finite;
-using chem_math::Dual;
 constexpr int N = mech::N, NS = mech::NS, NR = mech::NR, NA = mech::NA, NI = mech::NI;
 constexpr int NACT = mech::NACT, R = mech::R, RI = mech::RI, NPT = mech::NPT;
 constexpr int G = 16;
@@ -75,18 +73,13 @@ constexpr int T_TBC = T_TROE + 8 * NTB;
 constexpr int T_INT = T_TBC + MAXP * NTB;                 // in doubles
 constexpr int I_WORDS = 0, I_TBSP = NWORDS * NR, N_INT = NWORDS * NR + MAXP * NTB;
 constexpr int TAB_DOUBLES = T_INT + (N_INT + 1) / 2;
-// per cell (in scalars of the evaluation's type): concentrations, e^{G},
-// e^{-G}, H/RT, then G itself where some reaction needs it, W_k w_k and cp/R
-// (transposed product), then the reaction arrays
+// per cell: concentrations, e^{G}, e^{-G}, H/RT, then G itself where some
+// reaction needs it, then the reaction arrays
 constexpr int L_C = 0, L_GP = SP, L_GM = 2 * SP, L_H = 3 * SP;
 constexpr int L_G = 4 * SP;
 constexpr int L_A = (mech::HAS_LNKC ? 5 : 4) * SP;
 constexpr int NARR = MOLR + MOLP > 5 ? MOLR + MOLP : 5;
 constexpr int L_X = L_A + NARR * NRW;        // third-body terms: NTB, then NTB * MAXP partner corrections
-constexpr int L_WW = L_A, L_CP = L_A + SP;
-constexpr int L_V = L_A + 2 * SP;            // transposed product: MOLM arrays for A, MOLM for H, corrections
-constexpr int L_XA = L_V + 2 * MOLM * NRW;
-constexpr int NXV = NTB * MAXP + 1;
 
 __device__ __forceinline__ int gl() { return (int)(threadIdx.x & 15u); }
 __device__ __forceinline__ int gbase() { return (int)(threadIdx.x & 48u); }
@@ -144,7 +137,6 @@ __device__ __forceinline__ double bc(double x, int k)
     default: return dpp<0x15F>(x);
     }
 }
-__device__ __forceinline__ Dual bc(Dual x, int k) { return Dual(bc(x.v, k), bc(x.d, k)); }
 
 // value of x in lane `src` of this group; src may differ per lane
 __device__ __forceinline__ double gather(double x, int src) { return __shfl(x, gbase() + src, 64); }
@@ -169,7 +161,6 @@ __device__ __forceinline__ double gmax(double x)
 {
     return greduce(x, [](double a, double b) { return fmax(a, b); });
 }
-__device__ __forceinline__ Dual gsum(Dual x) { return Dual(gsum(x.v), gsum(x.d)); }
 
 // true in every lane of the group if `bad` holds in any lane of it
 __device__ __forceinline__ bool gany(bool bad)
@@ -207,9 +198,8 @@ __device__ __forceinline__ void load_tables(double* __restrict__ tab, const doub
 }
 
 // the temperature-dependent scalars of one evaluation, the same in every lane
-template <class S>
 struct Mix {
-    S T, lnT, iT, lnPRT, ctot, rtp, prt;
+    double T, lnT, iT, lnPRT, ctot, rtp, prt;
     double p;
 };
 
@@ -218,16 +208,15 @@ struct Mix {
 // of the two sides; dqT = d q / d T at fixed C; dM the coefficient of the
 // third-body efficiencies in d q / d C; s = sum_m d q / d C_m C_m; qA = d q /
 // d ln A of the main rate; dH = sum nu H/RT.
-template <class S>
 struct Rate {
-    S q, kf, kr, dqT, dM, s, qA, dH;
+    double q, kf, kr, dqT, dM, s, qA, dH;
 };
 
 // FULL: the round may hold slots other than elementary ones.
 // DERIV: derivatives are wanted.
-template <class S, bool FULL, bool DERIV>
-__device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, const S* __restrict__ L,
-                                         const Mix<S>& x, Rate<S>& o, int (&ra)[MOLR], int (&pa)[MOLP], int& misc)
+template <bool FULL, bool DERIV>
+__device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, const double* __restrict__ L,
+                                         const Mix& x, Rate& o, int (&ra)[MOLR], int (&pa)[MOLP], int& misc)
 {
     const int* const words = (const int*)(tab + T_INT) + I_WORDS;
     const double lnA = tab[T_PAR + j], pb = tab[T_PAR + NR + j], pe = tab[T_PAR + 2 * NR + j];
@@ -239,14 +228,14 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
     for (int s = 0; s < MOLR; ++s) ra[s] = (w[s / 4] >> (8 * (s % 4))) & 255;
 #pragma unroll
     for (int s = 0; s < MOLP; ++s) pa[s] = (w[WR + s / 4] >> (8 * (s % 4))) & 255;
-    S pf = L[L_C + ra[0]], pr = L[L_C + pa[0]];
+    double pf = L[L_C + ra[0]], pr = L[L_C + pa[0]];
 #pragma unroll
     for (int s = 1; s < MOLR; ++s) pf = pf * L[L_C + ra[s]];
 #pragma unroll
     for (int s = 1; s < MOLP; ++s) pr = pr * L[L_C + pa[s]];
     // 1/K_c = prod_reac e^{G} prod_prod e^{-G} (RT/P_atm)^dnu, the factors
     // multiplied reactant, product, reactant, ... as the range check took them
-    S ikc = L[L_GP + ra[0]] * L[L_GM + pa[0]];
+    double ikc = L[L_GP + ra[0]] * L[L_GM + pa[0]];
 #pragma unroll
     for (int s = 1; s < MOLM; ++s) {
         if (s < MOLR) ikc = ikc * L[L_GP + ra[s < MOLR ? s : 0]];
@@ -255,11 +244,11 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
     const int dnu = ((misc >> 5) & 7) - 4;
 #pragma unroll
     for (int q = 1; q <= mech::MAXDNU; ++q) {
-        const S f = dnu > 0 ? x.rtp : x.prt;
+        const double f = dnu > 0 ? x.rtp : x.prt;
         ikc = (dnu >= q || dnu <= -q) ? ikc * f : ikc;
     }
     if (mech::HAS_LNKC && !((misc >> 4) & 1)) {
-        S lnKc = (double)dnu * x.lnPRT;
+        double lnKc = (double)dnu * x.lnPRT;
 #pragma unroll
         for (int s = 0; s < MOLR; ++s) lnKc = lnKc - L[L_G + ra[s]];
 #pragma unroll
@@ -267,7 +256,7 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
         ikc = chem_math::exp_poly(-lnKc);
     }
     if (mech::HAS_IRREV && ((misc >> 3) & 1)) ikc = 0.0;
-    S lnk = x.lnT * pb;
+    double lnk = x.lnT * pb;
     lnk = fma(-x.iT, pe, lnk);
     lnk = lnk + lnA;
     const int kind = FULL ? misc & 7 : 0;
@@ -275,7 +264,7 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
     if (FULL && mech::HAS_PLOG && kind == 5) {
         // the Arrhenius set at this pressure: linear in ln p between the
         // tabulated pressures, the end sets outside them
-        const double lnp = log(x.p);
+        const double lnp = chem_math::ln(x.p);
         const int t = (misc >> 16) & 0xffff;
         const int e0 = mech::RX_PLOG_OFF[t], e1 = mech::RX_PLOG_OFF[t + 1] - 1;
         const double* E = mech::RX_PLOG;
@@ -295,8 +284,8 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
         eb += plb;
         ee += ple;
     }
-    S kf = chem_math::exp_poly(lnk);
-    S fac = 1.0, Mc = 0.0, dkdM = 0.0, qAf = 1.0, dlnkf = 0.0;
+    double kf = chem_math::exp_poly(lnk);
+    double fac = 1.0, Mc = 0.0, dkdM = 0.0, qAf = 1.0, dlnkf = 0.0;
     if (DERIV) dlnkf = (eb + ee * x.iT) * x.iT;
     if (FULL && NTB > 0 && kind >= 1 && kind <= 4) {
         const int t = (misc >> 16) & 0xffff;
@@ -308,56 +297,56 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
         if (kind >= 2) {
             // P_r = k0 [M] / k_inf, one exponential for the ratio
             const double* lo = tab + T_LOW + t;
-            const S lnr0 = lo[0] + lo[NTB] * x.lnT - lo[2 * NTB] * x.iT - lnk;
-            const S r0 = chem_math::exp_poly(lnr0);
-            const S Pr = r0 * Mc;
-            const bool floored = !(chem_math::value(Pr) >= 1e-300);
-            const S logPr = floored ? S(-300.0) : log10(Pr);
-            S Fb = 1.0, dF_dPr = 0.0, dlnF_T = 0.0;
+            const double lnr0 = lo[0] + lo[NTB] * x.lnT - lo[2 * NTB] * x.iT - lnk;
+            const double r0 = chem_math::exp_poly(lnr0);
+            const double Pr = r0 * Mc;
+            const bool floored = !(Pr >= 1e-300);
+            const double logPr = floored ? -300.0 : chem_math::lg(Pr);
+            double Fb = 1.0, dF_dPr = 0.0, dlnF_T = 0.0;
             if (kind == 3) {
                 const double* tr = tab + T_TROE + t;
-                const S e3 = chem_math::exp_poly(-x.T * tr[2 * NTB]);
-                const S e1 = chem_math::exp_poly(-x.T * tr[3 * NTB]);
-                S Fc = tr[0] * e3 + tr[1 * NTB] * e1;
-                S dFc = tr[5 * NTB] * e3 + tr[6 * NTB] * e1;
+                const double e3 = chem_math::exp_neg(-x.T * tr[2 * NTB]);
+                const double e1 = chem_math::exp_neg(-x.T * tr[3 * NTB]);
+                double Fc = tr[0] * e3 + tr[1 * NTB] * e1;
+                double dFc = tr[5 * NTB] * e3 + tr[6 * NTB] * e1;
                 if (tr[7 * NTB] != 0.0) {
-                    const S e2 = chem_math::exp_poly(-tr[4 * NTB] * x.iT);
+                    const double e2 = chem_math::exp_neg(-tr[4 * NTB] * x.iT);
                     Fc += e2;
                     dFc += tr[4 * NTB] * x.iT * x.iT * e2;
                 }
-                const S logFc = log10(Fc);
-                const S tc = -0.4 - 0.67 * logFc;
-                const S tn = 0.75 - 1.27 * logFc;
-                const S tu = logPr + tc;
-                const S itd = chem_math::recip(tn - 0.14 * tu);
-                const S tx = tu * itd;
-                const S iop = chem_math::recip(1.0 + tx * tx);
-                const S logF = logFc * iop;
-                Fb = chem_math::exp_poly(mech::LN10 * logF);
+                const double logFc = chem_math::lg(Fc);
+                const double tc = -0.4 - 0.67 * logFc;
+                const double tn = 0.75 - 1.27 * logFc;
+                const double tu = logPr + tc;
+                const double itd = chem_math::recip(tn - 0.14 * tu);
+                const double tx = tu * itd;
+                const double iop = chem_math::recip(1.0 + tx * tx);
+                const double logF = logFc * iop;
+                Fb = chem_math::exp_neg(mech::LN10 * logF);
                 if (DERIV) {
-                    const S tg = -logFc * 2.0 * tx * (iop * iop);
+                    const double tg = -logFc * 2.0 * tx * (iop * iop);
                     if (!floored) dF_dPr = tg * tn * (itd * itd);
-                    const S dF_dFc = iop + tg * (-0.67 * tn + 1.27 * tu) * (itd * itd);
+                    const double dF_dFc = iop + tg * (-0.67 * tn + 1.27 * tu) * (itd * itd);
                     dlnF_T = mech::LN10 * dF_dFc * (dFc * chem_math::recip(Fc * mech::LN10));
                 }
             } else if (mech::HAS_SRI && kind == 4) {
                 // SRI: F = d [a exp(-b/T) + exp(-T/c)]^X T^e, X = 1 / (1 + log10(P_r)^2);
                 // row: a, -b, 1/c, b, ln d, e
                 const double* sr = tab + T_TROE + t;
-                const S sea = sr[0] * chem_math::exp_poly(sr[1 * NTB] * x.iT);
-                const S sec = chem_math::exp_poly(-x.T * sr[2 * NTB]);
-                const S sY = sea + sec;
-                const S lnsY = log(sY);
-                const S sX = chem_math::recip(1.0 + logPr * logPr);
+                const double sea = sr[0] * chem_math::exp_neg(sr[1 * NTB] * x.iT);
+                const double sec = chem_math::exp_neg(-x.T * sr[2 * NTB]);
+                const double sY = sea + sec;
+                const double lnsY = chem_math::ln(sY);
+                const double sX = chem_math::recip(1.0 + logPr * logPr);
                 Fb = chem_math::exp_poly(sX * lnsY + sr[5 * NTB] * x.lnT + sr[4 * NTB]);
                 if (DERIV) {
                     if (!floored) dF_dPr = lnsY * (-2.0 / mech::LN10) * logPr * sX * sX;
                     dlnF_T = sX * (sea * sr[3 * NTB] * x.iT * x.iT - sec * sr[2 * NTB]) / sY + sr[5 * NTB] * x.iT;
                 }
             }
-            const S ipr1 = chem_math::recip(1.0 + Pr);
+            const double ipr1 = chem_math::recip(1.0 + Pr);
             if (DERIV) {
-                const S dlnk0 = (lo[NTB] + lo[2 * NTB] * x.iT) * x.iT;
+                const double dlnk0 = (lo[NTB] + lo[2 * NTB] * x.iT) * x.iT;
                 dlnkf = dlnkf + (ipr1 + dF_dPr) * (dlnk0 - dlnkf) + dlnF_T;
                 dkdM = kf * r0 * Fb * (ipr1 * ipr1 + dF_dPr * ipr1);
                 qAf = Pr * ipr1 - dF_dPr;
@@ -365,20 +354,20 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
             kf = kf * Pr * ipr1 * Fb;
         }
     }
-    const S net = fma(-ikc, pr, pf);
-    const S kfn = kf * net;
+    const double net = fma(-ikc, pr, pf);
+    const double kfn = kf * net;
     o.q = FULL ? fac * kfn : kfn;
     if (DERIV) {
         o.kf = FULL ? fac * kf : kf;
         o.kr = o.kf * ikc;
-        const S fwd = o.kf * pf, rev = o.kr * pr;
-        S dH = 0.0;
+        const double fwd = o.kf * pf, rev = o.kr * pr;
+        double dH = 0.0;
 #pragma unroll
         for (int s = 0; s < MOLP; ++s) dH = dH + L[L_H + pa[s]];
 #pragma unroll
         for (int s = 0; s < MOLR; ++s) dH = dH - L[L_H + ra[s]];
         o.dH = dH;
-        const S dlnKc = (dH - (double)dnu) * x.iT;
+        const double dlnKc = (dH - (double)dnu) * x.iT;
         o.dqT = dlnkf * fwd - (dlnkf - dlnKc) * rev;
         o.s = (double)((misc >> 8) & 15) * fwd - (double)((misc >> 12) & 15) * rev;
         o.dM = 0.0;
@@ -392,8 +381,8 @@ __device__ __forceinline__ void reaction(int j, const double* __restrict__ tab, 
 }
 
 // product of the concentrations of a side's slots but s (times c)
-template <class S, int MOL>
-__device__ __forceinline__ S others(const S* __restrict__ L, const int (&a)[MOL], int s, S c)
+template <int MOL>
+__device__ __forceinline__ double others(const double* __restrict__ L, const int (&a)[MOL], int s, double c)
 {
 #pragma unroll
     for (int t = 0; t < MOL; ++t)
@@ -404,26 +393,25 @@ __device__ __forceinline__ S others(const S* __restrict__ L, const int (&a)[MOL]
 // Species thermo, mixture sums and the species arrays in LDS: the part of an
 // evaluation before the reactions.  y: the lane's components; ywi: Y/W of its
 // species that no reaction changes.
-template <class S, bool DERIV>
+template <bool DERIV>
 struct Thermo {
-    S cpR[R], HRT[R], yw[R], dcpR[DERIV ? R : 1];
-    S cpi[RI];
-    S rho, irho, Wbar, sig, cpm, dcpm;
+    double cpR[R], HRT[R], yw[R], dcpR[DERIV ? R : 1];
+    double cpi[RI];
+    double rho, irho, Wbar, sig, cpm, dcpm;
 };
 
-template <class S, bool DERIV>
-__device__ __forceinline__ void thermo(const double* __restrict__ tab, double p, double ip, const S (&y)[R], const double (&ywi)[RI],
-                                       S* __restrict__ L, Mix<S>& x, Thermo<S, DERIV>& th)
+template <bool DERIV>
+__device__ __forceinline__ void thermo(const double* __restrict__ tab, double p, double ip, const double (&y)[R], const double (&ywi)[RI],
+                                       double* __restrict__ L, Mix& x, Thermo<DERIV>& th)
 {
     const int i = gl_local();
-    const S T = bc(y[0], 0);
+    const double T = bc(y[0], 0);
     x.T = T;
     x.p = p;
-    x.lnT = log(T);
+    x.lnT = chem_math::ln(T);
     x.iT = chem_math::recip(T);
-    const S T2 = T * T, T3 = T2 * T, T4 = T2 * T2;
-    const double Tv = chem_math::value(T);
-    S sig = 0.0;
+    const double T2 = T * T, T3 = T2 * T, T4 = T2 * T2;
+    double sig = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int a = r * 16 + i;
@@ -441,13 +429,13 @@ __device__ __forceinline__ void thermo(const double* __restrict__ tab, double p,
     x.lnPRT = mech::LN_PATM_R - x.lnT;
     x.rtp = T * mech::RU_PATM;
     x.prt = x.iT * mech::PATM_RU;
-    S cpm = 0.0, dcpm = 0.0;
+    double cpm = 0.0, dcpm = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int a = r * 16 + i;
-        const double* c = tab + T_TH + (Tv < mech::PTMID[a] ? 0 : NPT) + a;
+        const double* c = tab + T_TH + (T < mech::PTMID[a] ? 0 : NPT) + a;
         constexpr int st = 2 * NPT;
-        S v = T4 * c[4 * st];
+        double v = T4 * c[4 * st];
         v = fma(T3, c[3 * st], v);
         v = fma(T2, c[2 * st], v);
         v = fma(T, c[1 * st], v);
@@ -464,7 +452,7 @@ __device__ __forceinline__ void thermo(const double* __restrict__ tab, double p,
         v = fma(T, c[10 * st], v);
         v = fma(x.lnT, c[0], v);
         v = fma(-x.iT, c[9 * st], v);
-        const S Gk = v + c[14 * st];
+        const double Gk = v + c[14 * st];
         if (DERIV) {
             v = T3 * c[18 * st];
             v = fma(T2, c[17 * st], v);
@@ -474,7 +462,7 @@ __device__ __forceinline__ void thermo(const double* __restrict__ tab, double p,
         }
         cpm = fma(th.cpR[r], th.yw[r], cpm);
         if (a >= 1 && a < NACT) {
-            const S gp = chem_math::exp_poly(Gk);
+            const double gp = chem_math::exp_poly(Gk);
             L[L_C + a - 1] = th.rho * th.yw[r];
             L[L_GP + a - 1] = gp;
             L[L_GM + a - 1] = chem_math::recip(gp);
@@ -488,9 +476,9 @@ __device__ __forceinline__ void thermo(const double* __restrict__ tab, double p,
     for (int q = 0; q < RI; ++q) {
         const int m = q * 16 + i;
         const int a = R * 16 + m;
-        const double* c = tab + T_TH + (Tv < mech::PTMID[a] ? 0 : NPT) + a;
+        const double* c = tab + T_TH + (T < mech::PTMID[a] ? 0 : NPT) + a;
         constexpr int st = 2 * NPT;
-        S v = T4 * c[4 * st];
+        double v = T4 * c[4 * st];
         v = fma(T3, c[3 * st], v);
         v = fma(T2, c[2 * st], v);
         v = fma(T, c[1 * st], v);
@@ -503,7 +491,7 @@ __device__ __forceinline__ void thermo(const double* __restrict__ tab, double p,
             dcpm = fma(v + c[15 * st], ywi[q], dcpm);
         }
         if (m <= NI) {
-            L[L_C + NA + m] = m < NI ? th.rho * ywi[q] : S(1.0);
+            L[L_C + NA + m] = m < NI ? th.rho * ywi[q] : 1.0;
             L[L_GP + NA + m] = 1.0;
             L[L_GM + NA + m] = 1.0;
             L[L_H + NA + m] = 0.0;
@@ -576,14 +564,14 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
                                     double (&A)[R][NC])
 {
     const int i = gl_local();
-    Mix<double> x;
-    Thermo<double, JAC> th;
+    Mix x;
+    Thermo<JAC> th;
     if (i < NARR) L[L_A + i * NRW + NR] = 0.0;
     Stream<4> list(&mech::RL[0]);
-    thermo<double, JAC>(tab, p, ip, y, ywi, L, x, th);
+    thermo<JAC>(tab, p, ip, y, ywi, L, x, th);
     lds_sync();
     double* const Q = L + L_A;
-    auto store = [&](int j, const Rate<double>& o) {
+    auto store = [&](int j, const Rate& o) {
         Q[j] = o.q;
         if (JAC) {
             Q[NRW + j] = o.dqT;
@@ -595,9 +583,9 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
 #pragma unroll 1
     for (int j = i; j < 16 * mech::FULL_ROUNDS; j += 16) {
         if (j < NR) {
-            Rate<double> o;
+            Rate o;
             int ra[MOLR], pa[MOLP], misc;
-            reaction<double, true, JAC>(j, tab, L, x, o, ra, pa, misc);
+            reaction<true, JAC>(j, tab, L, x, o, ra, pa, misc);
             store(j, o);
             const int kind = misc & 7;
             if (JAC && NTB > 0 && kind >= 1 && kind <= 4) {
@@ -609,9 +597,9 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
     }
 #pragma unroll 2
     for (int j = 16 * mech::FULL_ROUNDS + i; j < NR; j += 16) {
-        Rate<double> o;
+        Rate o;
         int ra[MOLR], pa[MOLP], misc;
-        reaction<double, false, JAC>(j, tab, L, x, o, ra, pa, misc);
+        reaction<false, JAC>(j, tab, L, x, o, ra, pa, misc);
         store(j, o);
     }
     lds_sync();
@@ -655,9 +643,9 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
             for (int s = 0; s < MOLP; ++s) pa[s] = (words[(WR + s / 4) * NR + j] >> (8 * (s % 4))) & 255;
             const double kf = Q[3 * NRW + j], kr = Q[4 * NRW + j];
 #pragma unroll
-            for (int s = 0; s < MOLR; ++s) Q[s * NRW + j] = others<double, MOLR>(L, ra, s, kf);
+            for (int s = 0; s < MOLR; ++s) Q[s * NRW + j] = others<MOLR>(L, ra, s, kf);
 #pragma unroll
-            for (int s = 0; s < MOLP; ++s) Q[(MOLR + s) * NRW + j] = others<double, MOLP>(L, pa, s, -kr);
+            for (int s = 0; s < MOLP; ++s) Q[(MOLR + s) * NRW + j] = others<MOLP>(L, pa, s, -kr);
         }
         lds_sync();
         // concentration Jacobian Jc_km = d wdot_k / d C_m: the third-body part
@@ -1074,338 +1062,6 @@ __device__ __forceinline__ void cell_store(const Cell& c, double* __restrict__ T
     }
 }
 
-// ---- discrete adjoint of the frozen-step map (see the one-cell-per-lane form
-// for the algebra) ----
-
-// Solve M^T x = b: the sums over rows that a column needs are group sums.
-// scr: 16 R doubles of the cell's scratch.
-__device__ __forceinline__ void solve_t(const Factors& F, double (&b)[R], double* __restrict__ scr)
-{
-    const int i = gl_local();
-    // U'^T (unit lower), then the pivots
-    static_for<1, NACT>([&](auto kc) {
-        constexpr int k = decltype(kc)::v, rk = k / 16, lk = k % 16;
-        double s = F.UD[rk][lk] * b[rk];
-#pragma unroll
-        for (int r = 0; r < rk; ++r) s = fma(F.A[r][k], b[r], s);
-        s = gsum(s);
-        b[rk] = i == lk ? b[rk] - s : b[rk];
-    });
-#pragma unroll
-    for (int r = 0; r < R; ++r) b[r] *= F.D[r];
-    // L^T
-    static_for<0, NACT - 1>([&](auto kc) {
-        constexpr int k = NACT - 2 - decltype(kc)::v, rk = k / 16, lk = k % 16;
-        double s = 0.0;
-#pragma unroll
-        for (int r = rk; r < R; ++r) s = fma(F.A[r][k], b[r], s);
-        s = gsum(s);
-        b[rk] = i == lk ? b[rk] - s : b[rk];
-    });
-    if (F.swapped) {    // x at position src is what this lane holds
-#pragma unroll
-        for (int r = 0; r < R; ++r) scr[F.src[r]] = b[r];
-        lds_sync();
-#pragma unroll
-        for (int r = 0; r < R; ++r) b[r] = scr[r * 16 + i];
-        lds_sync();
-    }
-}
-
-// what a transposed product leaves behind of S: the value, or the tangent
-__device__ __forceinline__ double take(double x) { return x; }
-__device__ __forceinline__ double take(const Dual& x) { return x.d; }
-
-// v += J(y)^T w (S = double), or D_u[J(y)^T w] with y a dual number along u;
-// vi: the same for the species no reaction changes; g: the products w . df/dq
-// d q / d(ln A, b, Ea) of the lane's reactions, or their tangents.  J is never
-// formed: every entry is assembled from the reactions' partials, so the
-// product needs each reaction's weights wY = sum nu W w and hs = sum nu H/RT
-// and two column sums colA_m = sum wY dq/dC_m, colH_m = sum hs dq/dC_m:
-//   v_{1+m} = (colA_m + Wbar (w.f_Y - SwY/rho)) / W_m + w_0 J_{0,1+m}
-//   v_0     = (wYT - SwY/T)/rho + (w.f_Y)/T + w_0 J_00
-template <class S>
-__device__ __forceinline__ void jtv(const double* __restrict__ tab, double p, double ip, const S (&y)[R],
-                                    const double (&ywi)[RI], const double (&w)[R], S* __restrict__ L,
-                                    double (&v)[R], double (&vi)[RI], double (&g)[ROUNDS][3])
-{
-    const int i = gl_local();
-    Mix<S> x;
-    Thermo<S, true> th;
-    Stream<4> list(&mech::TL[0]);
-    thermo<S, true>(tab, p, ip, y, ywi, L, x, th);
-    // neutral entries of the reaction arrays
-    if (i < 2 * MOLM) L[L_V + i * NRW + NR] = 0.0;
-    if (i < 2) L[L_XA + i * NXV + NXV - 1] = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int a = r * 16 + i;
-        if (a >= 1 && a < NACT) {
-            L[L_WW + a - 1] = mech::PW[a] * w[r];
-            L[L_CP + a - 1] = th.cpR[r];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < RI; ++q)
-        if (q * 16 + i <= NI) {
-            L[L_WW + NA + q * 16 + i] = 0.0;
-            L[L_CP + NA + q * 16 + i] = 0.0;
-        }
-    lds_sync();
-    const double w0 = bc(w[0], 0);
-    const S icpm = chem_math::recip(th.cpm);
-    const S rcpinv = x.T * th.sig * ip * icpm;
-    S SwY = 0.0, HSa = 0.0, wYT = 0.0, HwT = 0.0, hw = 0.0, Wf = 0.0, cpw = 0.0, DA = 0.0, DH = 0.0;
-    S kr[ROUNDS], wYr[ROUNDS], hsr[ROUNDS];
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int j = r * G + i;
-        if (j < NR) {
-            Rate<S> o;
-            int ra[MOLR], pa[MOLP], misc;
-            if (r < mech::FULL_ROUNDS) reaction<S, true, true>(j, tab, L, x, o, ra, pa, misc);
-            else reaction<S, false, true>(j, tab, L, x, o, ra, pa, misc);
-            S wY = 0.0, cps = 0.0;
-#pragma unroll
-            for (int s = 0; s < MOLP; ++s) {
-                wY = wY + L[L_WW + pa[s]];
-                cps = cps + L[L_CP + pa[s]];
-            }
-#pragma unroll
-            for (int s = 0; s < MOLR; ++s) {
-                wY = wY - L[L_WW + ra[s]];
-                cps = cps - L[L_CP + ra[s]];
-            }
-            const S hs = o.dH;
-            SwY = fma(wY, o.s, SwY);
-            HSa = fma(hs, o.s, HSa);
-            wYT = fma(wY, o.dqT, wYT);
-            HwT = fma(hs, o.dqT, HwT);
-            hw = fma(hs, o.q, hw);
-            Wf = fma(wY, o.q, Wf);
-            cpw = fma(cps, o.q, cpw);
-            const S wsum = wY * th.irho - w0 * (mech::RU * x.T) * hs * rcpinv;
-            const S gq = wsum * o.qA;
-            g[r][0] += take(gq);
-            g[r][1] += take(gq * x.lnT);
-            g[r][2] += take(gq * (-x.iT * (1.0 / mech::RU)));
-#pragma unroll
-            for (int s = 0; s < MOLR; ++s) {
-                const S d = others<S, MOLR>(L, ra, s, o.kf);
-                L[L_V + s * NRW + j] = wY * d;
-                L[L_V + (MOLM + s) * NRW + j] = hs * d;
-            }
-            kr[r] = o.kr;
-            wYr[r] = wY;
-            hsr[r] = hs;
-            if (NTB > 0 && r < mech::FULL_ROUNDS) {
-                const int kind = misc & 7;
-                if (kind >= 1 && kind <= 4) {
-                    const int t = (misc >> 16) & 0xffff;
-                    DA = fma(wY, o.dM, DA);
-                    DH = fma(hs, o.dM, DH);
-                    for (int q = 0; q < MAXP; ++q) {
-                        const S d = tab[T_TBC + q * NTB + t] * o.dM;
-                        L[L_XA + t * MAXP + q] = wY * d;
-                        L[L_XA + NXV + t * MAXP + q] = hs * d;
-                    }
-                }
-            }
-        }
-    }
-    lds_sync();
-    S cA[R + RI], cH[R + RI];
-#pragma unroll
-    for (int r = 0; r < R + RI; ++r) {
-        cA[r] = 0.0;
-        cH[r] = 0.0;
-    }
-    static_for<0, R + RI>([&](auto rc) {
-        constexpr int r = decltype(rc)::v;
-        list.run(mech::SRLEN[r], [&](int, int e) {
-            cA[r] = cA[r] + L[L_V + e];
-            cH[r] = cH[r] + L[L_V + MOLM * NRW + e];
-        });
-    });
-    static_for<0, R + RI>([&](auto rc) {
-        constexpr int r = decltype(rc)::v;
-        list.run(mech::SXLEN[r], [&](int, int e) {
-            cA[r] = cA[r] + L[L_XA + e];
-            cH[r] = cH[r] + L[L_XA + NXV + e];
-        });
-    });
-    lds_sync();
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int j = r * G + i;
-        if (j < NR) {
-            const int* const words = (const int*)(tab + T_INT) + I_WORDS;
-            int pa[MOLP];
-#pragma unroll
-            for (int s = 0; s < MOLP; ++s) pa[s] = (words[(WR + s / 4) * NR + j] >> (8 * (s % 4))) & 255;
-#pragma unroll
-            for (int s = 0; s < MOLP; ++s) {
-                const S d = others<S, MOLP>(L, pa, s, -kr[r]);
-                L[L_V + s * NRW + j] = wYr[r] * d;
-                L[L_V + (MOLM + s) * NRW + j] = hsr[r] * d;
-            }
-        }
-    }
-    lds_sync();
-    static_for<0, R + RI>([&](auto rc) {
-        constexpr int r = decltype(rc)::v;
-        list.run(mech::SPLEN[r], [&](int, int e) {
-            cA[r] = cA[r] + L[L_V + e];
-            cH[r] = cH[r] + L[L_V + MOLM * NRW + e];
-        });
-    });
-    lds_sync();
-    SwY = gsum(SwY);
-    HSa = gsum(HSa);
-    wYT = gsum(wYT);
-    HwT = gsum(HwT);
-    hw = gsum(hw);
-    Wf = gsum(Wf) * th.irho;
-    cpw = gsum(cpw);
-    DA = gsum(DA);
-    DH = gsum(DH);
-    const S fT = -mech::RU * x.T * hw * rcpinv;
-    const S RT = mech::RU * x.T;
-    const S icp = icpm * (1.0 / mech::RU);
-    const S dcp = mech::RU * th.dcpm;
-    const S wg = th.Wbar * (Wf - th.irho * SwY);
-#pragma unroll
-    for (int r = 0; r < R + RI; ++r) {
-        const double iW = mech::PW[NPT + r * 16 + i];       // 0 where no species sits
-        const S cp = r < R ? th.cpR[r < R ? r : 0] : th.cpi[r < R ? 0 : r - R];
-        const S t = fma(th.rho, cH[r] + DH, -th.Wbar * HSa) * (-RT * rcpinv);
-        const S u = fma(cp, icp * mech::RU, -th.Wbar);
-        const S J0m = fma(-fT, u, t) * iW;
-        const S out = fma(cA[r] + DA + wg, iW, w0 * J0m);
-        if (r < R) v[r < R ? r : 0] += take(out);
-        else vi[r < R ? 0 : r - R] += take(out);
-    }
-    const S J00 = -mech::RU * (cpw + x.T * HwT - HSa) * rcpinv - fT * (dcp * icp - x.iT);
-    const S v0 = fma(th.irho, wYT - SwY * x.iT, fma(x.iT, Wf, w0 * J00));
-    if (i == 0) v[0] += take(v0);
-}
-
-// value of a stage-indexed register array at a run-time stage s (selects, so
-// the array stays in registers)
-__device__ __forceinline__ void pick(const double (&a)[Rodas4::S][R], int s, double (&o)[R])
-{
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        o[r] = a[0][r];
-#pragma unroll
-        for (int q = 1; q < Rodas4::S; ++q) o[r] = q == s ? a[q][r] : o[r];
-    }
-}
-
-__device__ __forceinline__ void place(double (&a)[Rodas4::S][R], int s, const double (&x)[R])
-{
-#pragma unroll
-    for (int q = 0; q < Rodas4::S; ++q)
-#pragma unroll
-        for (int r = 0; r < R; ++r) a[q][r] = q == s ? x[r] : a[q][r];
-}
-
-// The adjoint of one frozen RODAS4 step from y with step h: lam (the cotangent
-// of y_new; lami for the species no reaction changes) becomes the cotangent
-// of y; the parameter products of the lane's reactions are added to g.  The
-// stage loops stay rolled (one copy of each evaluation).
-__device__ __noinline__ void step_adjoint(const double* __restrict__ tab, double p, double ip, const double (&y)[R],
-                                          const double (&ywi)[RI], double h, double (&lam)[R], double (&lami)[RI],
-                                          double (&g)[ROUNDS][3], double* __restrict__ L)
-{
-    const int i = gl_local();
-    Factors F;
-    double f[R];
-    rhs<true, NACT>(tab, p, ip, y, ywi, L, f, F.A);
-    const double hinv = chem_math::recip(h);
-    const double ghinv = hinv * (1.0 / Rodas4::gamma);
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < NACT; ++c) F.A[r][c] = (r * 16 + i == c ? ghinv : 0.0) - F.A[r][c];
-    bool ok;
-    lu(F, ok);
-    double u[Rodas4::S][R], Ys[Rodas4::S][R];
-#pragma unroll
-    for (int s = 0; s < Rodas4::S; ++s)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            u[s][r] = 0.0;
-            Ys[s][r] = y[r];
-        }
-    solve(F, f);
-    place(u, 0, f);
-#pragma unroll 1
-    for (int s = 1; s < Rodas4::S; ++s) {
-        double Y[R], acc[R], us[R], none[R][1];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            Y[r] = y[r];
-            acc[r] = 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < Rodas4::S - 1; ++j) {
-            if (j < s) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    Y[r] = fma(RA[s][j], u[j][r], Y[r]);
-                    acc[r] = fma(RC[s][j], u[j][r], acc[r]);
-                }
-            }
-        }
-        place(Ys, s, Y);
-        rhs<false, 1>(tab, p, ip, Y, ywi, L, us, none);
-#pragma unroll
-        for (int r = 0; r < R; ++r) us[r] = fma(acc[r], hinv, us[r]);
-        solve(F, us);
-        place(u, s, us);
-    }
-    // reverse over the stages
-    const double mw[Rodas4::S] = {RA[5][0], RA[5][1], RA[5][2], RA[5][3], 1.0, 1.0};
-    double ub[Rodas4::S][R], w[Rodas4::S][R];
-#pragma unroll
-    for (int s = 0; s < Rodas4::S; ++s)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            ub[s][r] = mw[s] * lam[r];
-            w[s][r] = 0.0;
-        }
-#pragma unroll 1
-    for (int s = Rodas4::S - 1; s >= 0; --s) {
-        double ws[R], Y[R], Yb[R];
-        pick(ub, s, ws);
-        solve_t(F, ws, L + L_A);
-        place(w, s, ws);
-        pick(Ys, s, Y);
-#pragma unroll
-        for (int r = 0; r < R; ++r) Yb[r] = 0.0;
-        jtv<double>(tab, p, ip, Y, ywi, ws, L, Yb, lami, g);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            lam[r] += Yb[r];
-#pragma unroll
-            for (int j = 0; j < Rodas4::S - 1; ++j)
-                if (j < s) ub[j][r] = fma(RA[s][j], Yb[r], fma(RC[s][j] * hinv, ws[r], ub[j][r]));
-        }
-    }
-    // second-order terms at y: J(y) inside M, one dual evaluation per stage direction
-#pragma unroll 1
-    for (int s = 0; s < Rodas4::S; ++s) {
-        double us[R], ws[R];
-        pick(u, s, us);
-        pick(w, s, ws);
-        Dual yd[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) yd[r] = Dual(y[r], us[r]);
-        jtv<Dual>(tab, p, ip, yd, ywi, ws, (Dual*)L, lam, lami, g);
-    }
-}
-
 // Groups of a workgroup: cpw of each wave hold a cell (the others have no
 // scratch and leave).  The group's place among the launch's, or -1, and its
 // scratch.
@@ -1577,105 +1233,6 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_persistent(con
                 cell_store(c, fd.T, fd.Y, local, fd.status, fd.nacc, fd.nrej);
                 have = false;
             }
-        }
-    }
-}
-
-// ---- discrete adjoint: one group per cell, cells in descending cost order ----
-// The forward solve is rerun, storing every accepted step size and the state
-// every K accepted steps; then the reverse sweep recomputes each segment from
-// its checkpoint and applies the step adjoints backwards.  Group s (of
-// a.nslot) takes the cells in positions s, s + nslot, ... of the cost order
-// and keeps the parameter gradients of all its cells in its lanes' registers
-// (lane i holds those of its reaction slots): one row of partial sums per
-// group instead of one per cell, for the fixed-order reduction.
-extern "C" __global__ void __launch_bounds__(256, 1) chem_adjoint(AdjointArgs a)
-{
-    using namespace chemw;
-    extern __shared__ double lds[];
-    load_tables(lds, a.par);
-    double* L;
-    const long gslot = group_of(mech::ACPW, mech::ADJ_LDS_CELL, lds, L);
-    if (gslot < 0 || gslot >= a.nslot) return;
-    const int i = gl();
-    double g[ROUNDS][3];
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) g[r][0] = g[r][1] = g[r][2] = 0.0;
-    for (long slot = gslot; slot < a.ncell; slot += a.nslot) {
-        const long cell = a.order[slot];
-        Cell c;
-        cell_begin(c, a.T0[cell], a.p[cell], a.Y0 + cell * NS, a.h0 ? a.h0[cell] : a.step.dt);
-        double* hs = a.hs + a.off_h[cell];
-        double* ck = a.ck + a.off_ck[cell] * N;
-        const int cap = a.nacc_fwd[cell];
-        int stored = -1;
-        while (!c.done) {
-            if (c.nacc % a.K == 0 && c.nacc != stored && c.nacc < cap) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (r * 16 + i < NACT) ck[(c.nacc / a.K) * N + r * 16 + i] = c.y[r];
-                stored = c.nacc;
-            }
-            const double hacc = cell_attempt(c, lds, a.step, L);
-            if (hacc > 0.0) {
-                if (c.nacc > cap) {
-                    c.status = chem::CELL_NONFINITE;
-                    c.done = true;
-                    break;
-                }
-                if (i == 0) hs[c.nacc - 1] = hacc;
-            }
-        }
-        cell_store(c, a.Tend, a.Yend, cell, a.status, a.nacc, a.nrej);
-        if (c.status == chem::CELL_BADINPUT) put(c.y, c.yi, a.Tend + cell, a.Yend + cell * NS);
-        double lam[R], lami[RI];
-        if (c.status != chem::CELL_OK) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) lam[r] = __builtin_nan("");
-#pragma unroll
-            for (int q = 0; q < RI; ++q) lami[q] = __builtin_nan("");
-            put(lam, lami, a.gT0 + cell, a.gY0 + cell * NS);
-            continue;                   // adds nothing to the parameter gradients
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int k = mech::PSPEC[r * 16 + i];
-            lam[r] = k >= 0 ? a.gY[cell * NS + k] : 0.0;
-            if (r == 0 && i == 0) lam[r] = a.gT[cell];
-        }
-#pragma unroll
-        for (int q = 0; q < RI; ++q) {
-            const int k = mech::PSPEC[R * 16 + q * 16 + i];
-            lami[q] = k >= 0 ? a.gY[cell * NS + k] : 0.0;
-        }
-        const int na = c.nacc;
-        const double p = c.p, ip = c.ip;
-        for (int seg = (na - 1) / a.K; seg >= 0 && na > 0; --seg) {
-            const int first = seg * a.K;
-            const int last = min(na, first + a.K) - 1;
-            double ys[16][R];                     // the segment's states (K <= 16)
-#pragma unroll
-            for (int r = 0; r < R; ++r) ys[0][r] = r * 16 + i < NACT ? ck[seg * N + r * 16 + i] : 0.0;
-            for (int s = first; s < last; ++s) {
-                double yn[R], en;
-                ros_step(lds, p, ip, ys[s - first], c.ywi, c.yi, hs[s], a.step.rtol, a.step.atol, L, yn, en);
-#pragma unroll
-                for (int r = 0; r < R; ++r) ys[s - first + 1][r] = yn[r];
-            }
-            for (int s = last; s >= first; --s)
-                step_adjoint(lds, p, ip, ys[s - first], c.ywi, hs[s], lam, lami, g, L);
-        }
-        put(lam, lami, a.gT0 + cell, a.gY0 + cell * NS);
-    }
-    double* gp = a.gpar + gslot * 3 * NR;
-#pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        const int j = r * G + i;
-        if (j < NR) {
-            const int oj = mech::RX_ORIG[j];
-            gp[oj] = g[r][0];
-            gp[NR + oj] = g[r][1];
-            gp[2 * NR + oj] = g[r][2];
         }
     }
 }

@@ -19,14 +19,17 @@
 
 namespace chemmi {
 
-#include "_device_source.inc"   // kMathSource, kCommonSource, kIntegratorSource, kWideSource, kEulerSource
+#include "_device_source.inc"   // kMathSource, kCommonSource, kIntegratorSource, kWideSource, kWideAdjointSource, kEulerSource
 
-std::string device_source(const std::string& mechanism_code, bool wide, bool exp_saturating)
+std::string device_source(const std::string& mechanism_code, DeviceForm form, bool exp_saturating)
 {
     const std::string config = std::string("namespace chem_config {\nconstexpr bool kExpSaturatingConvert = ") +
                                (exp_saturating ? "true" : "false") + ";\n}\n";
-    return config + std::string(kMathSource) + "\n" + mechanism_code + "\n" + std::string(kCommonSource) + "\n" +
-           std::string(wide ? kWideSource : kIntegratorSource) + "\n" + std::string(kEulerSource);
+    const std::string shared = config + std::string(kMathSource) + "\n" + mechanism_code + "\n" +
+                               std::string(kCommonSource) + "\n";
+    if (form == DeviceForm::WideAdjoint) return shared + std::string(kWideAdjointSource);
+    return shared + std::string(form == DeviceForm::Wide ? kWideSource : kIntegratorSource) + "\n" +
+           std::string(kEulerSource);
 }
 
 const std::vector<std::string>& compile_options()

@@ -93,7 +93,11 @@ int device_state(chem_mechanism* m, hipStream_t stream, DeviceState** out)
         rc = rc ? rc : load_function(d.module, "chem_reduce_stats", &d.f_stats);
         rc = rc ? rc : load_function(d.module, "chem_persistent", &d.f_persistent);
         rc = rc ? rc : load_function(d.module, "chem_reset_heads", &d.f_reset);
-        rc = rc ? rc : load_function(d.module, "chem_adjoint", &d.f_adjoint);
+        if (m->wide) {
+            HIPCHECK(hipModuleLoadData(&d.adjoint_module, m->adjoint_code.data()), "hipModuleLoadData");
+            rc = rc ? rc : load_function(d.adjoint_module, "chem_adjoint_size", &d.f_adj_size);
+        }
+        rc = rc ? rc : load_function(m->wide ? d.adjoint_module : d.module, "chem_adjoint", &d.f_adjoint);
         rc = rc ? rc : load_function(d.module, "chem_reduce_params", &d.f_rparams);
         rc = rc ? rc : load_function(d.module, "chem_source_begin", &d.f_src_begin);
         rc = rc ? rc : load_function(d.module, "chem_source_end", &d.f_src_end);
@@ -188,6 +192,7 @@ void release_device_state(chem_mechanism* m)
         if (d.ev0) (void)hipEventDestroy(d.ev0);
         if (d.ev1) (void)hipEventDestroy(d.ev1);
         if (d.done) (void)hipEventDestroy(d.done);
+        if (d.adjoint_module) (void)hipModuleUnload(d.adjoint_module);
         if (d.module) (void)hipModuleUnload(d.module);
     }
     m->devices.clear();
@@ -887,15 +892,24 @@ int run_euler1d(chem_mechanism* m, int64_t ncell, double dx, double dt, const do
     return rc;
 }
 
+namespace {
+
+int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, const double* T0, const double* p,
+                 const double* Y0, const double* gT, const double* gY, double* gT0, double* gY0, double* g_lnA,
+                 double* g_b, double* g_Ea, double* T_end, double* Y_end, const Options& o, int K, const StepArgs& step,
+                 int32_t* i32, const std::vector<int32_t>& nacc_h, chem_stats* stats, hipStream_t stream);
+
+}  // namespace
+
 int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double* p, const double* Y0,
                 double dt, double rtol, double atol, const double* gT, const double* gY, double* gT0,
                 double* gY0, double* g_lnA, double* g_b, double* g_Ea, double* T_end, double* Y_end,
-                const Options& o, chem_stats* stats, hipStream_t stream)
+                const Options& o, bool end_wanted, chem_stats* stats, hipStream_t stream)
 {
     DeviceState* d;
     if (int rc = device_state(m, stream, &d)) return rc;
-    const int ns = m->data.ns(), n = ns + 1, nr = m->data.nr();
-    int K = o.checkpoint_every;
+    const int ns = m->data.ns(), nr = m->data.nr();
+    const int K = o.checkpoint_every;
     if (K < 0 || K > 16) return set_error(CHEM_E_INVAL, "checkpoint_every must be 1..16");
     if (ncell == 0) {   // parameter gradients are zero; nothing else to do
         struct {
@@ -917,22 +931,84 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     HIPCHECK(hipMemcpyAsync(Tw, T0, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T0");
     HIPCHECK(hipMemcpyAsync(Yw, Y0, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y0");
     const StepArgs step = step_args(dt, rtol, atol, o);
-    if (o.adjoint_nacc) {   // the caller's forward already counted the steps
+    if (o.adjoint_nacc)   // the caller's forward already counted the steps
         HIPCHECK(hipMemcpyAsync(na_fwd, o.adjoint_nacc, sizeof(int32_t) * ncell, hipMemcpyDeviceToDevice, stream),
                  "copy the forward's step counts");
-    } else if (o.h0) {
-        IntegrateArgs ia{d->par, Tw, p, Yw, (long)ncell, o.h0, st, na_fwd, nj, step, nullptr};
-        if (int rc = launch_plain(m, *d, ia, stream)) return rc;
-    } else {   // the persistent form takes the same steps, bitwise, sooner
-        FieldView fv{Tw, p, Yw, ncell, st, na_fwd, nj, nullptr, nullptr};
-        Options po = o;
-        po.form = CHEM_FORM_PERSISTENT;
-        if (int rc = run_persistent(m, &fv, 1, dt, rtol, atol, po, nullptr, stream)) return rc;
+    // (the wave-cooperative adjoint's own rerun rounds differently from the
+    // forward kernels, whose end state the caller gets: see below)
+    const bool forward = !o.adjoint_nacc || (m->wide && end_wanted);
+    if (forward) {
+        int32_t* counts = o.adjoint_nacc ? na : na_fwd;
+        if (o.h0) {
+            IntegrateArgs ia{d->par, Tw, p, Yw, (long)ncell, o.h0, st, counts, nj, step, nullptr};
+            if (int rc = launch_plain(m, *d, ia, stream)) return rc;
+        } else {   // the persistent form takes the same steps, bitwise, sooner
+            FieldView fv{Tw, p, Yw, ncell, st, counts, nj, nullptr, nullptr};
+            Options po = o;
+            po.form = CHEM_FORM_PERSISTENT;
+            if (int rc = run_persistent(m, &fv, 1, dt, rtol, atol, po, nullptr, stream)) return rc;
+        }
     }
     std::vector<int32_t> nacc_h(ncell);
     HIPCHECK(hipMemcpyAsync(nacc_h.data(), na_fwd, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
              "copy step counts");
     HIPCHECK(hipStreamSynchronize(stream), "sync sizing pass");
+    if (m->wide) {
+        // the rerun may take a step more or less than the forward kernels where
+        // an error estimate sits at the acceptance limit: two and 1 in 32 spare
+        for (auto& c : nacc_h)
+            if (c > 0) c += 2 + c / 32;
+        HIPCHECK(hipMemcpyAsync(na_fwd, nacc_h.data(), sizeof(int32_t) * ncell, hipMemcpyHostToDevice, stream),
+                 "copy step limits");
+    }
+    auto pass = [&] {
+        return adjoint_pass(m, *d, s, ncell, T0, p, Y0, gT, gY, gT0, gY0, g_lnA, g_b, g_Ea, T_end, Y_end, o, K, step,
+                            i32, nacc_h, stats, stream);
+    };
+    int rc = pass();
+    if (rc == CHEM_E_CELL_FAILED && m->wide && !o.adjoint_nacc) {
+        // a cell that outran the spare steps as well: the rerun's own counts
+        std::vector<int32_t> status_h(ncell);
+        HIPCHECK(hipMemcpyAsync(status_h.data(), st, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
+                 "copy status");
+        HIPCHECK(hipStreamSynchronize(stream), "sync status");
+        if (std::count(status_h.begin(), status_h.end(), (int32_t)CHEM_CELL_NONFINITE)) {
+            double *Ts, *Ys;
+            if (int rc2 = s.alloc(&Ts, ncell, "adjoint T")) return rc2;
+            if (int rc2 = s.alloc(&Ys, (size_t)ncell * ns, "adjoint Y")) return rc2;
+            HIPCHECK(hipMemcpyAsync(Ts, T0, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T0");
+            HIPCHECK(hipMemcpyAsync(Ys, Y0, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y0");
+            IntegrateArgs ia{d->par, Ts, p, Ys, (long)ncell, o.h0, st, na_fwd, nj, step, nullptr};
+            if (int rc2 = launch_1d(d->f_adj_size, ncell * m->rows.G, 64, &ia, sizeof ia, stream, "chem_adjoint_size",
+                                    m->rows.lds_bytes()))
+                return rc2;
+            HIPCHECK(hipMemcpyAsync(nacc_h.data(), na_fwd, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
+                     "copy step counts");
+            HIPCHECK(hipStreamSynchronize(stream), "sync sizing pass");
+            rc = pass();
+        }
+    }
+    if (!m->wide || !forward || (rc && rc != CHEM_E_CELL_FAILED)) return rc;
+    // the end state is the forward kernels' (bitwise chem_integrate's), not the
+    // rerun's
+    HIPCHECK(hipMemcpyAsync(T_end, Tw, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T");
+    HIPCHECK(hipMemcpyAsync(Y_end, Yw, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y");
+    return rc;
+}
+
+namespace {
+
+// The adjoint proper: arenas for nacc_h accepted steps a cell, the kernel, and
+// the parameter reduction.  i32: the call's counters (status, the steps on the
+// device, accepted, rejected).
+int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, const double* T0, const double* p,
+                 const double* Y0, const double* gT, const double* gY, double* gT0, double* gY0, double* g_lnA,
+                 double* g_b, double* g_Ea, double* T_end, double* Y_end, const Options& o, int K, const StepArgs& step,
+                 int32_t* i32, const std::vector<int32_t>& nacc_h, chem_stats* stats, hipStream_t stream)
+{
+    DeviceState* d = &ds;
+    const int n = m->data.ns() + 1, nr = m->data.nr();
+    int32_t *st = i32, *na_fwd = i32 + ncell, *na = i32 + 2 * ncell, *nj = i32 + 3 * ncell;
     if (K == 0) {
         // the densest checkpoints whose arena fits a quarter of the free device
         // memory: every step stored means no recomputation in the reverse sweep
@@ -977,9 +1053,9 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     int64_t nslot;
     unsigned ashmem;
     if (m->wide) {
-        ashmem = m->layout.adj_lds_bytes();
-        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * m->layout.adj_blocks_per_cu() * m->layout.awpb *
-                                             m->layout.acpw);
+        ashmem = m->rows.adj_lds_bytes();
+        const int64_t waves_per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (160 * 1024) / std::max(1u, ashmem)));
+        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * waves_per_cu * m->rows.cells_per_wave());
     } else {
         // the stage vectors (5 n doubles a lane), and during a step adjoint the
         // 3 nr parameter accumulators when they fit 80 doubles a lane (the
@@ -1046,9 +1122,8 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     AdjointArgs aa{d->par, T0, p, Y0, (long)ncell, gT, gY, gT0, gY0, gpar, (long)nslot, T_end, Y_end, off_d,
                    off_d + ncell, na_fwd, order_d, o.h0, hs, ck, st, na, nj, step, K, ngroup, gcells, stash, trail};
     HIPCHECK(hipEventRecord(d->ev0, stream), "event");
-    const int64_t alanes = m->wide ? m->layout.adj_lanes(nslot) : nslot;
-    const int ablock = m->wide ? m->layout.adj_block() : 64;
-    if (int rc = launch_1d(d->f_adjoint, alanes, ablock, &aa, sizeof aa, stream, "chem_adjoint", ashmem)) return rc;
+    const int64_t alanes = m->wide ? nslot * m->rows.G : nslot;
+    if (int rc = launch_1d(d->f_adjoint, alanes, 64, &aa, sizeof aa, stream, "chem_adjoint", ashmem)) return rc;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
     struct {
         const double* g;
@@ -1065,5 +1140,7 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     chem_stats local{};
     return collect_stats(*d, st, na, nj, ncell, ms, stats ? stats : &local, stream);
 }
+
+}  // namespace
 
 }  // namespace chemmi

@@ -180,7 +180,7 @@ struct LaunchConfig {
 struct DeviceState {
     int device = -1;
     int num_cu = 256;
-    hipModule_t module = nullptr;
+    hipModule_t module = nullptr, adjoint_module = nullptr;   // (the wave-cooperative adjoint's)
     hipFunction_t f_plain = nullptr, f_eval = nullptr, f_fixed = nullptr, f_zero = nullptr,
                   f_stats = nullptr, f_persistent = nullptr, f_reset = nullptr, f_gather = nullptr,
                   f_okey = nullptr, f_oscan = nullptr, f_oscatter = nullptr, f_adjoint = nullptr,
@@ -235,6 +235,8 @@ struct chem_mechanism {
     chemmi::MechanismData data;
     bool wide = false;                   // wave-cooperative kernels (else one cell per lane)
     chemmi::WideLayout layout;           // of the wave-cooperative form
+    chemmi::RowLayout rows;              // of its adjoint
+    std::vector<char> adjoint_code;      // the adjoint's code object (wave-cooperative form)
     std::vector<double> params;          // lnA[nr], b[nr], Ea/R[nr]
     uint64_t params_version = 1;
     std::string source;
@@ -300,10 +302,10 @@ int run_source(chem_mechanism* m, int64_t ncell, double* T, const double* p, dou
                double* wdot, double* qdot, hipStream_t stream);
 
 // Discrete adjoint (see chem_integrate_adjoint); the arrays are as there, with
-// T_end/Y_end non-null.
+// T_end/Y_end non-null (scratch of the call unless end_wanted).
 int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double* p, const double* Y0,
                 double dt, double rtol, double atol, const double* gT, const double* gY, double* gT0,
                 double* gY0, double* g_lnA, double* g_b, double* g_Ea, double* T_end, double* Y_end,
-                const Options& o, chem_stats* stats, hipStream_t stream);
+                const Options& o, bool end_wanted, chem_stats* stats, hipStream_t stream);
 
 }  // namespace chemmi
