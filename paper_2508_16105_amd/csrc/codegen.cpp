@@ -917,6 +917,10 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
     const int full_rounds = (nfull + 15) / 16;
     const bool has_plog = std::any_of(m.reactions.begin(), m.reactions.end(),
                                       [](const ReactionData& r) { return r.kind == RxnKind::Plog; });
+    const bool has_troe = std::any_of(m.reactions.begin(), m.reactions.end(),
+                                  [](const ReactionData& r) { return r.kind == RxnKind::Troe; });
+    const bool one_tmid = std::all_of(m.species.begin(), m.species.end(),
+                                      [&](const auto& s) { return s.tmid == m.species[0].tmid; });
     auto yn = [](bool b) { return b ? "true" : "false"; };
     o << "// generated mechanism tables (wave-cooperative form): " << m.name << " (" << ns << " species, " << nr
       << " reactions)\n"
@@ -939,7 +943,9 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
       << "constexpr double LN10 = " << lit(std::log(10.0)) << ";\n"
       << "// reaction forms present (the kernels leave out the code of the absent ones)\n"
          "constexpr bool HAS_PLOG = " << yn(has_plog) << ", HAS_SRI = " << yn(sri) << ", HAS_IRREV = " << yn(irrev)
-      << ", HAS_LNKC = " << yn(w.lnkc) << ";\n";
+      << ", HAS_LNKC = " << yn(w.lnkc) << ", HAS_TROE = " << yn(has_troe) << ";\n"
+      << "constexpr bool ONE_TMID = " << yn(one_tmid) << ";   // one temperature parts every species' ranges\n"
+      << "constexpr double TMID = " << lit(m.species[0].tmid) << ";\n";
     e.thermo_table();
     auto ints = [&](const std::string& decl, const std::vector<int>& v) {
         o << decl << "[" << std::max<size_t>(v.size(), 1) << "] = {";
@@ -1185,7 +1191,17 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
     o << "// by row: production rates (reaction slot, net coefficient); third-body part of a\n"
          "// Jacobian row (d q / d [M] of the slots that change the species); the species'\n"
          "// own column of it\n";
-    ints(ci + "RL", rl);
+    // the words of a row that a lane takes lie together, so it reads four at once
+    auto by_lane = [](const std::vector<int>& v, int lists) {
+        std::vector<int> w(v.size());
+        for (size_t k = 0; k < v.size(); ++k) {
+            const size_t row = k / (16 * lists), q = k / 16 % lists, lane = k % 16;
+            w[(row * 16 + lane) * lists + q] = v[k];
+        }
+        return w;
+    };
+    const std::string aligned = "__constant__ __attribute__((aligned(16))) int ";
+    ints(aligned + "RL", by_lane(rl, 4));
     o << "// Jacobian rows, other columns: partials of the slots and third-body corrections,\n"
          "// in groups of columns\n"
       << "constexpr int JGW = " << jgw << ", JGACT = " << jgact << ", JGALL = " << grow.size() << ";\n";
@@ -1193,7 +1209,7 @@ std::string generate_wide_source(const MechanismData& m, const WideLayout& w)
     ints("constexpr int JGLEN", glen);
     ints("constexpr int JGCOL", gcol);
     jdata.insert(jdata.end(), 2 * jgw * 16, 0);
-    ints(ci + "JL", jdata);
+    ints(aligned + "JL", by_lane(jdata, jgw));
     o << "}  // namespace mech\n";
     return o.str();
 }
