@@ -1321,6 +1321,13 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_fixed_step(Fix
     cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, a.h);
     double yn[R], en;
     const bool ok = ros_step(lds, c.p, c.ip, c.y, c.ywi, c.yi, a.h, a.rtol, a.atol, L, yn, en);
+    // where the step fails, the species no reaction changes fail with the others
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) bad = bad || (r * 16 + gl() < NACT && !finite(yn[r]));
+    if (gany(bad))
+#pragma unroll
+        for (int q = 0; q < RI; ++q) c.yi[q] = __builtin_nan("");
     put(yn, c.yi, a.ynew + cell * N, a.ynew + cell * N + 1);
     if (gl() == 0) {
         a.err[cell] = en;

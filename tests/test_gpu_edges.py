@@ -1,0 +1,106 @@
+"""Sizes at which the kernels' splits have their edges.
+
+Wave-cooperative form (16 lanes a cell, 4 cells a wave, 4 waves a workgroup):
+cell counts around each of these, mechanisms with one and two matrix rows a
+lane, with and without every form of rate.  A cell's result does not depend on
+the cells beside it, so prefixes are compared bitwise, the longest with the
+oracle at the tolerances of the other parity tests (|dT| <= 1e-6 T, |dY| <= 1e-8
+at rtol 1e-8).
+
+Plain launches above the lanes the chip holds at once deal cells to idle lanes:
+bitwise the launches that fit, and the persistent form."""
+import os
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from workloads import mech_path, mech_text  # noqa: E402
+from workloads.states import uniform_cells  # noqa: E402
+
+RTOL, ATOL = 1e-8, 1e-12
+
+
+@pytest.fixture(scope="module")
+def chem():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2508_16105_amd as chem
+    return chem
+
+
+def _g(a):
+    return torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda:0")
+
+
+def _load(chem, name, lane_max=None):
+    old = os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
+    try:
+        if lane_max is not None:
+            os.environ["CHEM_LANE_MAX_SPECIES"] = str(lane_max)
+        return chem.Mechanism(mech_path(name))
+    finally:
+        os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
+        if old is not None:
+            os.environ["CHEM_LANE_MAX_SPECIES"] = old
+
+
+@pytest.mark.parametrize("name", ["m9", "m13x", "m16", "m32", "m32x"])
+def test_wave_cooperative_cell_counts(chem, oracle_lib, name):
+    gm, om = _load(chem, name, 0), oracle_lib.Mechanism(mech_path(name))
+    n, dt = 65, 1e-8
+    T, p, Y = uniform_cells(mech_text(name), n, 91)
+    a = [_g(v) for v in (T, p, Y)]
+    Tw, Yw, _ = chem.integrate(gm, *a, dt, RTOL, ATOL)
+    f, J = chem.eval_source(gm, *a, jacobian=True)
+    g = chem.eval_source(gm, *a, jacobian=False)[0]
+    h = chem.step_fixed(gm, *a, 1e-10, RTOL, ATOL)
+    To, Yo, _, _, _ = om.integrate(T, p, Y, dt, RTOL, ATOL)
+    assert np.all(np.abs(Tw.cpu().numpy() - To) <= 1e-6 * To)
+    assert np.all(np.abs(Yw.cpu().numpy() - Yo) <= 1e-8)
+    for k in (1, 3, 4, 5, 15, 16, 17, 63, 64, 65):
+        b = [v[:k].contiguous() for v in a]
+        for form in (chem.FORM_PLAIN, chem.FORM_PERSISTENT):
+            Tk, Yk, _ = chem.integrate(gm, *b, dt, RTOL, ATOL, form=form)
+            assert torch.equal(Tk, Tw[:k]) and torch.equal(Yk, Yw[:k]), (k, form)
+        fk, Jk = chem.eval_source(gm, *b, jacobian=True)
+        assert torch.equal(fk, f[:k]) and torch.equal(Jk, J[:k]), k
+        assert torch.equal(chem.eval_source(gm, *b, jacobian=False)[0], g[:k]), k
+        # (a step of this size fails in some cells: NaN, in the same ones)
+        for x, y in zip(chem.step_fixed(gm, *b, 1e-10, RTOL, ATOL), h):
+            assert torch.allclose(x, y[:k], rtol=0, atol=0, equal_nan=True), k
+
+
+@pytest.mark.parametrize("name,resident,first", [("m9", 65536, False), ("m9", 65536, True), ("m16", 8192, False)])
+@pytest.mark.parametrize("extra", [1, 64, 777])
+def test_dealt_plain_launch_is_bitwise_the_static_one(chem, name, resident, first, extra):
+    gm = _load(chem, name)
+    n = resident + extra
+    T, p, Y = uniform_cells(mech_text(name), n, 17)
+    a = [_g(v) for v in (T, p, Y)]
+    h0 = _g(np.geomspace(1e-13, 1e-9, n)) if first else None
+    run = lambda s, **kw: chem.integrate(gm, *(v[s].contiguous() for v in a), 2e-9, RTOL, ATOL, return_counts=True,
+                                         **({} if h0 is None else {"h0": h0[s].contiguous()}), **kw)
+    whole = run(slice(0, n))
+    parts = [run(slice(s, min(n, s + resident // 2))) for s in range(0, n, resident // 2)]
+    for k in (0, 1, 3, 4, 5):
+        assert torch.equal(whole[k], torch.cat([q[k] for q in parts])), k
+    if h0 is None:
+        other = run(slice(0, n), form=chem.FORM_PERSISTENT)
+        assert torch.equal(whole[0], other[0]) and torch.equal(whole[1], other[1])
+
+
+@pytest.mark.parametrize("name,lane_max", [("m9", 0), ("m16", None), ("m32", None)])
+def test_a_failed_single_step_has_no_finite_component(chem, name, lane_max):
+    """Wave-cooperative form: also in the species no reaction changes, which are
+    not part of the linear system; the cells beside it are untouched."""
+    gm = _load(chem, name, lane_max)
+    T, p, Y = uniform_cells(mech_text(name), 6, 5)
+    good = [v.cpu() for v in chem.step_fixed(gm, _g(T), _g(p), _g(Y), 1e-13, RTOL, ATOL)]
+    assert bool((good[2] == 1).all()) and bool(torch.isfinite(good[0]).all())
+    T[3] = -1.0                                   # ln T is NaN
+    yn, en, ok = (v.cpu() for v in chem.step_fixed(gm, _g(T), _g(p), _g(Y), 1e-13, RTOL, ATOL))
+    assert ok.tolist() == [1, 1, 1, 0, 1, 1] and bool(torch.isnan(yn[3]).all()) and bool(torch.isnan(en[3]))
+    rest = [0, 1, 2, 4, 5]
+    assert torch.equal(yn[rest], good[0][rest]) and torch.equal(en[rest], good[1][rest])
