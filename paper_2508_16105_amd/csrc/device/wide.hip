@@ -1263,17 +1263,30 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_eval(EvalArgs 
     const long first = group_of(mech::CPW, mech::LDS_CELL, lds, L);
     if (first < 0) return;
     const int i = gl();
-    double zero[RI];
-#pragma unroll
-    for (int q = 0; q < RI; ++q) zero[q] = 0.0;
     // the launch holds at most the resident workgroups, which share out the cells
     for (long cell = first; cell < a.ncell; cell += (long)gridDim.x * ((int)blockDim.x / 64 * mech::CPW)) {
         Cell c;
         cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, 0.0);
         double f[R];
+        // what the species no reaction changes get: zero, or NaN in a state (a
+        // Jacobian) that is not finite, as in every other component
+        double zero[RI], z = fma(0.0, c.ip, 0.0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) z = fma(0.0, c.y[r], z);
+#pragma unroll
+        for (int q = 0; q < RI; ++q) z = fma(0.0, c.yi[q], z);
+        z = gsum(z);
+#pragma unroll
+        for (int q = 0; q < RI; ++q) zero[q] = z;
         if (a.J) {
             double A[R][N];
             rhs<true, N>(lds, c.p, c.ip, c.y, c.ywi, L, f, A);
+            double za = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int col = 0; col < N; ++col) za = fma(0.0, A[r][col], za);
+            za = gsum(za);
             double* const J = a.J + cell * N * N;
 #pragma unroll
             for (int r = 0; r < R + RI; ++r) {
@@ -1283,7 +1296,7 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_eval(EvalArgs 
 #pragma unroll
                     for (int col = 0; col < N; ++col) {
                         const int oc = col == 0 ? 0 : 1 + mech::COLSPEC[col - 1];
-                        J[row * N + oc] = r < R ? A[r < R ? r : 0][col] : 0.0;   // (no reaction changes the last)
+                        J[row * N + oc] = r < R ? A[r < R ? r : 0][col] : za;
                     }
                 }
             }

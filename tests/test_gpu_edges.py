@@ -104,3 +104,23 @@ def test_a_failed_single_step_has_no_finite_component(chem, name, lane_max):
     assert ok.tolist() == [1, 1, 1, 0, 1, 1] and bool(torch.isnan(yn[3]).all()) and bool(torch.isnan(en[3]))
     rest = [0, 1, 2, 4, 5]
     assert torch.equal(yn[rest], good[0][rest]) and torch.equal(en[rest], good[1][rest])
+
+
+@pytest.mark.parametrize("name,lane_max", [("m9", 0), ("m16", None), ("m32", None)])
+@pytest.mark.parametrize("what", ["T", "p", "Y"])
+def test_source_terms_of_a_state_that_is_not_finite(chem, name, lane_max, what):
+    """Wave-cooperative form: NaN in every source term and Jacobian entry, also
+    of the species no reaction changes; the cells beside it are untouched."""
+    gm = _load(chem, name, lane_max)
+    T, p, Y = uniform_cells(mech_text(name), 6, 5)
+    f0, J0 = (v.cpu() for v in chem.eval_source(gm, _g(T), _g(p), _g(Y), jacobian=True))
+    assert bool(torch.isfinite(f0).all()) and bool(torch.isfinite(J0).all())
+    if what == "Y":
+        Y[3, 0] = np.nan
+    else:
+        (T if what == "T" else p)[3] = np.nan
+    f, J = (v.cpu() for v in chem.eval_source(gm, _g(T), _g(p), _g(Y), jacobian=True))
+    g = chem.eval_source(gm, _g(T), _g(p), _g(Y), jacobian=False)[0].cpu()
+    assert bool(torch.isnan(f[3]).all()) and bool(torch.isnan(J[3]).all()) and bool(torch.isnan(g[3]).all())
+    rest = [0, 1, 2, 4, 5]
+    assert torch.equal(f[rest], f0[rest]) and torch.equal(J[rest], J0[rest])
