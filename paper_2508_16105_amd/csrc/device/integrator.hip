@@ -231,7 +231,18 @@ struct StashLayout {
 // With STASH the step also leaves what its adjoint needs in `stash` (see
 // StashLayout; nothing if it is null): the factors of M, the pivots, the swap
 // mask and u_1..u_6, bitwise the values the adjoint would recompute.
-template <bool STASH>
+// ROLL: the five stages as a loop.  Unrolled, the 13-species step is 230 KB of
+// code, 3.5 times the instruction cache that two CUs share; as a loop 121 KB:
+// 115 against 129 ms on a 100,000-cell field, 31 against 33 ms on 4,096
+// reactors, 139 against 142 ms on 400,000 cells in seven fields.  The
+// unrolled kernel is also one the compiler gets wrong: after a step that fails
+// from its first source term on (all mass fractions zero) its next step size
+// came out below any limit.  Nine species (113 KB unrolled) gain nothing (28.7
+// and 29.0 ms on 1M cells), and a kernel that makes one step fetches its code
+// once either way and loses the overlap of the stages (13 species, 124 against
+// 112 us), so those unroll.
+constexpr bool kRollStages = kFactorsInLds;
+template <bool STASH, bool ROLL>
 __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, double p, double ip,
                                               const double (&y)[N], double h, double rtol,
                                               double atol, double (&ynew)[N], double& errn,
@@ -287,33 +298,32 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
 #pragma unroll
             for (int a = 0; a < NACT; ++a) stash[StashLayout::u(0, a)] = f[P(a)];
     }
-    double u[N];
+    double u[N], Ys[N];
 #pragma unroll
-    for (int s = 1; s < Rodas4::S; ++s) {
-        double Ys[N], acc[NACT];
-#pragma unroll
-        for (int a = NACT; a < N; ++a) Ys[P(a)] = y[P(a)];
+    for (int a = NACT; a < N; ++a) Ys[P(a)] = y[P(a)];
+    double sum[NACT];
+    auto begin = [&] {
 #pragma unroll
         for (int a = 0; a < NACT; ++a) {
-            double v = y[P(a)], w = 0.0;
-#pragma unroll
-            for (int j = 0; j < s; ++j) {
-                double uj;
-                if constexpr (kFactorsInLds) uj = us[opaque_index(j)][a];
-                else uj = ul[(j * NACT + a) * kLaneStride];
-                v = fma(RA[s][j], uj, v);
-                w = fma(RC[s][j], uj, w);
-            }
-            Ys[P(a)] = v;
-            acc[a] = w;
+            Ys[P(a)] = y[P(a)];
+            sum[a] = 0.0;
         }
-        if (s == Rodas4::S - 1) {
+    };
+    auto add = [&](int s, int j) {
+        const double ra = RA[s][j], rc = RC[s][j];
 #pragma unroll
-            for (int k = 0; k < N; ++k) ynew[k] = Ys[k];     // stiffly accurate: y_new = Y_6 + u_6
+        for (int a = 0; a < NACT; ++a) {
+            double uj;
+            if constexpr (kFactorsInLds) uj = us[opaque_index(j)][a];
+            else uj = ul[(j * NACT + a) * kLaneStride];
+            Ys[P(a)] = fma(ra, uj, Ys[P(a)]);
+            sum[a] = fma(rc, uj, sum[a]);
         }
+    };
+    auto end = [&](int s) {
         mech::rhs(par, p, ip, Ys, u);
 #pragma unroll
-        for (int a = 0; a < NACT; ++a) u[P(a)] = fma(acc[a], hinv, u[P(a)]);
+        for (int a = 0; a < NACT; ++a) u[P(a)] = fma(sum[a], hinv, u[P(a)]);
         lu_solve<kFactorsInLds>(M, piv, opaque_uniform(swaps), u, ul);
         if (s < Rodas4::S - 1) {
 #pragma unroll
@@ -327,7 +337,26 @@ __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, do
 #pragma unroll
                 for (int a = 0; a < NACT; ++a) stash[StashLayout::u(s, a)] = u[P(a)];
         }
+    };
+    if constexpr (ROLL) {
+#pragma unroll 1
+        for (int s = 1; s < Rodas4::S; ++s) {
+            begin();
+#pragma unroll 1
+            for (int j = 0; j < s; ++j) add(s, j);
+            end(s);
+        }
+    } else {
+#pragma unroll
+        for (int s = 1; s < Rodas4::S; ++s) {
+            begin();
+#pragma unroll
+            for (int j = 0; j < s; ++j) add(s, j);
+            end(s);
+        }
     }
+#pragma unroll
+    for (int k = 0; k < N; ++k) ynew[k] = Ys[k];     // stiffly accurate: y_new = Y_6 + u_6
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -346,7 +375,7 @@ __device__ __forceinline__ bool ros_step(const double* __restrict__ par, double 
                                          double atol, double (&ynew)[N], double& errn,
                                          double* __restrict__ ul)
 {
-    return ros_step_impl<false>(par, p, ip, y, h, rtol, atol, ynew, errn, ul, nullptr);
+    return ros_step_impl<false, false>(par, p, ip, y, h, rtol, atol, ynew, errn, ul, nullptr);
 }
 
 // Per-lane integration state.
@@ -394,7 +423,7 @@ __device__ __forceinline__ double cell_attempt(Cell& c, const double* __restrict
     double h = c.h;
     if (h >= a.dt - c.t) { h = a.dt - c.t; last = true; }
     double ynew[N], en;
-    const bool ok = ros_step_impl<STASH>(par, c.p, c.ip, c.y, h, a.rtol, a.atol, ynew, en, ul, stash);
+    const bool ok = ros_step_impl<STASH, kRollStages>(par, c.p, c.ip, c.y, h, a.rtol, a.atol, ynew, en, ul, stash);
     if (ok && en <= 1.0) {
 #pragma unroll
         for (int k = 0; k < N; ++k) c.y[k] = ynew[k];
@@ -811,7 +840,7 @@ __device__ __forceinline__ void lu_solve_t(const double (&A)[N][N], const int (&
 // in its group (direction jd; lanes 6 and 7 evaluate a zero direction); only
 // lanes with jd <= 0 add the first-order parameter products.
 // FROM_STASH: the factors, pivots and stage vectors of the step come from
-// what ros_step_impl<true> left for it (the same values, bitwise), and only
+// what ros_step_impl<true, ...> left for it (the same values, bitwise), and only
 // the stage states are formed again from them.
 // gA, gb, gE: the lane's parameter-gradient accumulators (private memory).
 // While the step runs they are held in the lane's LDS words instead, when the
@@ -1055,7 +1084,7 @@ extern "C" __global__ void __launch_bounds__(64, 1) chem_adjoint(AdjointArgs a)
                 double* st = a.stash + lane * (long)a.K * StashLayout::WORDS;
                 for (int i = first; i <= last; ++i) {
                     double yn[N], en;
-                    ros_step_impl<true>(a.par, p, ip, ys[i - first], hs[i], a.step.rtol, a.step.atol, yn, en, ul,
+                    ros_step_impl<true, kRollStages>(a.par, p, ip, ys[i - first], hs[i], a.step.rtol, a.step.atol, yn, en, ul,
                                         st + (i - first) * StashLayout::WORDS);
                     if (i < last)
                         for (int k = 0; k < N; ++k) ys[i - first + 1][k] = yn[k];

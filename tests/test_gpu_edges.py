@@ -124,3 +124,26 @@ def test_source_terms_of_a_state_that_is_not_finite(chem, name, lane_max, what):
     assert bool(torch.isnan(f[3]).all()) and bool(torch.isnan(J[3]).all()) and bool(torch.isnan(g[3]).all())
     rest = [0, 1, 2, 4, 5]
     assert torch.equal(f[rest], f0[rest]) and torch.equal(J[rest], J0[rest])
+
+
+@pytest.mark.parametrize("name,lane_max", [("m9", None), ("m9", 0), ("m13", None), ("m13", 0), ("m16", None)])
+@pytest.mark.parametrize("state", ["no mass", "too hot"])
+def test_steps_that_fail_shrink_to_the_smallest(chem, name, lane_max, state):
+    """Every trial step of such a cell holds NaN, so each takes 0.2 of the size
+    before: 0.2^29 is the first below the default limit of 1e-20.  Its
+    neighbours end as without it."""
+    gm = _load(chem, name, lane_max)
+    T, p, Y = uniform_cells(mech_text(name), 9, 5)
+    out = []
+    for k in (0, 1):
+        Tw, Yw = _g(T), _g(Y)
+        st, na, nr = (torch.zeros(9, dtype=torch.int32, device="cuda:0") for _ in range(3))
+        chem.integrate_noalloc(gm, Tw, _g(p), Yw, 1e-9, RTOL, ATOL, status=st, nacc=na, nrej=nr)
+        out.append([v.cpu() for v in (Tw, Yw, st, na, nr)])
+        if state == "no mass":
+            Y[4] = 0.0
+        else:
+            T[4] = 1e6
+    assert out[1][2].tolist() == [0, 0, 0, 0, 2, 0, 0, 0, 0] and out[1][3][4] == 0 and out[1][4][4] == 29
+    rest = [0, 1, 2, 3, 5, 6, 7, 8]
+    assert all(torch.equal(x[rest], y[rest]) for x, y in zip(*out))
