@@ -66,14 +66,16 @@ enum chem_cell_status {
     CHEM_CELL_HMIN = 2,         /* step size fell below hmin_rel * dt */
     CHEM_CELL_NONFINITE = 3,    /* adjoint only: the checkpointed rerun of a cell took more
                                    accepted steps than its sizing pass or the caller's
-                                   adjoint_nacc entry allows (the sizing pass runs the same
-                                   code on the same input, so only a wrong entry does it) */
+                                   adjoint_nacc entry allows (for large mechanisms two and
+                                   1/32 more: only a wrong entry does it) */
     CHEM_CELL_BADINPUT = 4      /* T <= 0, p <= 0 or a non-finite input */
 };
 
 enum chem_form {
     CHEM_FORM_AUTO = 0,         /* plain for a single field */
-    CHEM_FORM_PLAIN = 1,        /* one cell per lane, one launch per field */
+    CHEM_FORM_PLAIN = 1,        /* one launch per field, a cell per lane (large mechanisms:
+                                   per 16 lanes); above the lanes the GPU holds at once,
+                                   further cells go to lanes as they fall idle */
     CHEM_FORM_PERSISTENT = 2    /* persistent work-stealing launch in a HIP graph */
 };
 
