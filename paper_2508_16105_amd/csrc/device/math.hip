@@ -66,8 +66,10 @@ __device__ __forceinline__ double recip(double x)
 }
 
 // exp(x) where x is not large; very negative arguments (a Troe constant of
-// 1e-50 K) are held where the polynomial's reduced argument is still exact.
-__device__ __forceinline__ double exp_neg(double x) { return exp_poly(fmax(x, -800.0)); }
+// 1e-50 K) are held where the polynomial's reduced argument is still exact.  NaN
+// passes the comparison (fmax would drop it: a rate whose logarithm is NaN, a
+// Troe centre below zero, would be that rate switched off).
+__device__ __forceinline__ double exp_neg(double x) { return exp_poly(x < -800.0 ? -800.0 : x); }
 
 // ln(x).  x = 2^e m with m in [sqrt(1/2), sqrt(2)), s = (m - 1) / (m + 1) and
 // ln m = 2 atanh(s) = 2 s + 2 s z P(z), z = s^2, P the degree-6 polynomial that

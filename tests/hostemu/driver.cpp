@@ -6,7 +6,7 @@
 // cell order).  Built with the host sanitizers by tests/test_hostemu.py.
 //
 // usage: driver IN OUT.  IN: int32 mode (0 integrate, 1 fixed step, 2 source
-// terms + Jacobian, 3 adjoint), int32 ncell, int32 ns, int32 nr, then
+// terms + Jacobian, 3 adjoint, 4 source terms alone), int32 ncell, int32 ns, int32 nr, then
 // doubles: dt (or h), rtol, atol, par[3 nr] (ln A, b, Ea/R), T[ncell],
 // p[ncell], Y[ncell ns], and for mode 3 gT[ncell], gY[ncell ns].
 #include "shim.h"
@@ -99,6 +99,11 @@ int main(int argc, char** argv)
         launch_lanes(n, [] { chem_eval(g_ea); });
         wr(out, f, n * N);
         wr(out, J, n * N * N);
+    } else if (mode == 4) {
+        double* f = (double*)calloc(n * N + 1, sizeof(double));
+        g_ea = EvalArgs{par, T, p, Y, n, f, nullptr};
+        launch_lanes(n, [] { chem_eval(g_ea); });
+        wr(out, f, n * N);
     } else if (mode == 3) {
         double* gT = rd<double>(in, n);
         double* gY = rd<double>(in, n * ns);

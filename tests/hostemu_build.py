@@ -102,6 +102,9 @@ def run(exe: pathlib.Path, workdir: pathlib.Path, mode: int, par, T, p, Y, dt_or
         take("f", n * n1, np.float64); take("J", n * n1 * n1, np.float64)
         out["f"] = out["f"].reshape(n, n1)
         out["J"] = out["J"].reshape(n, n1, n1)
+    elif mode == 4:
+        take("f", n * n1, np.float64)
+        out["f"] = out["f"].reshape(n, n1)
     else:
         take("gT0", n, np.float64); take("gY0", n * ns, np.float64); take("gpar", 3 * nr, np.float64)
         take("Te", n, np.float64); take("Ye", n * ns, np.float64); take("status", n, np.int32)
