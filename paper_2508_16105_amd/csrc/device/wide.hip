@@ -289,8 +289,11 @@ __device__ __forceinline__ void reaction(const Entry& en, const Slots<DERIV>& sl
         const double f = dnu > 0 ? x.rtp : x.prt;
         ikc = (dnu >= q || dnu <= -q) ? ikc * f : ikc;
     }
-    if (mech::HAS_LNKC && !((misc >> 4) & 1)) {
-        double lnKc = (double)dnu * x.lnPRT;
+    // (K_c out of the range of the factors: by its logarithm)
+    const bool by_log = mech::HAS_LNKC && !((misc >> 4) & 1);
+    double lnKc = 0.0;
+    if (by_log) {
+        lnKc = (double)dnu * x.lnPRT;
 #pragma unroll
         for (int s = 0; s < MOLR; ++s) lnKc = lnKc - L[L_G + sl.ra[s]];
 #pragma unroll
@@ -428,11 +431,17 @@ __device__ __forceinline__ void reaction(const Entry& en, const Slots<DERIV>& sl
         kf = chem_math::exp_poly(lnk);
     }
     const double net = fma(-ikc, pr, pf);
-    const double kfn = kf * net;
+    double kfn = kf * net, kr = kf * ikc;
+    if (by_log && !fall) {
+        // 1/K_c may be beyond the largest double, and k_f below the smallest,
+        // where their product, the reverse rate constant, is an ordinary number
+        kr = chem_math::exp_poly(lnk - lnKc);
+        kfn = kf * pf - kr * pr;
+    }
     o.q = FULL ? fac * kfn : kfn;
     if (DERIV) {
         o.kf = FULL ? fac * kf : kf;
-        o.kr = o.kf * ikc;
+        o.kr = FULL ? fac * kr : kr;
         const double fwd = o.kf * pf, rev = o.kr * pr;
         double dH = 0.0;
 #pragma unroll

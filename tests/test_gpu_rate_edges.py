@@ -51,3 +51,19 @@ def test_a_troe_centre_below_zero_is_not_a_number(evaluate, centre, form, lane_m
     rc.check_source(f, fo)
     rc.check_source(fj, fo)
     assert np.array_equal(np.isnan(J).any(axis=(1, 2)), np.isnan(fo).any(axis=1))
+
+
+@pytest.mark.parametrize("form,lane_max", FORMS)
+@pytest.mark.parametrize("kind", sorted(rc.FAR))
+@pytest.mark.parametrize("y", rc.FAR_Y)
+def test_a_reverse_rate_whose_equilibrium_constant_is_out_of_range(evaluate, kind, form, lane_max, y):
+    """Tolerance: the exponential's argument is a difference of terms up to 837,
+    each rounded (2^-53 of it), a few such errors: 1e-12; a forward rate constant
+    below the smallest normal double keeps its rounding of 2^-1074, in source terms
+    below 1e-290."""
+    T, p, Y = rc.states(3, rc.FAR_T, y=y)
+    f, fj, J, _ = evaluate(rc.FAR[kind], lane_max, T, p, Y)
+    ref = rc.far_source(kind, T, p, Y)
+    assert np.isfinite(J).all()
+    for g in (f, fj):
+        assert np.all(np.abs(g - ref) <= 1e-12 * np.abs(ref).max(axis=1, keepdims=True) + 1e-290), (g, ref)
