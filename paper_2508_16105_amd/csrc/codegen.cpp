@@ -479,7 +479,7 @@ struct Emitter {
                     o << "    const S tg = -logFc * 2.0 * tx * (iopx2*iopx2);\n"
                          "    const S dF_dPr = floored ? S(0.0) : tg * tn * (itden*itden);\n"
                          "    const S dF_dFc = iopx2 + tg * (-0.67*tn + 1.27*tu) * (itden*itden);\n"
-                         "    const S dlogFc_dT = dFc * chem_math::recip(Fc * " << lit(std::log(10.0)) << ");\n";
+                         "    const S dlogFc_dT = dFc / (Fc * " << lit(std::log(10.0)) << ");\n";
                 }
             } else if (r.kind == RxnKind::Sri) {
                 // F = d [a exp(-b/T) + exp(-T/c)]^X T^e with X = 1 / (1 + log10(P_r)^2)
@@ -488,7 +488,7 @@ struct Emitter {
                                                          : std::string("0.0")) << ";\n"
                      "    const S sec = chem_math::exp_poly(-T * " << lit(1.0 / c[2]) << ");\n"
                      "    const S sY = sea + sec;\n"
-                     "    const S lnsY = chem_math::ln(sY);\n"
+                     "    const S lnsY = chem_math::ln<true>(sY);\n"
                      "    const S sX = chem_math::recip(1.0 + logPr * logPr);\n"
                      "    const S Fb = chem_math::exp_poly(sX * lnsY + " << lit(c[4]) << " * lnT + " << lit(std::log(c[3]))
                   << ");\n";

@@ -80,7 +80,8 @@ __device__ __forceinline__ double exp_neg(double x) { return exp_poly(x < -800.0
 // b ln T - Ea/RT that it enters, and with one to three of them per source
 // evaluation they were a tenth of the 13-species one.  Zero, negative
 // arguments, infinity and NaN give NaN (the library's -inf and inf make the
-// stage that meets them fail just the same).  SUB: x may be subnormal.
+// stage that meets them fail just the same).  SUB: x may be subnormal (without it
+// such an x is read with a leading one it does not have).
 template <bool SUB = false>
 __device__ __forceinline__ double ln(double x)
 {
@@ -182,8 +183,10 @@ __device__ __forceinline__ Dual exp_neg(Dual x)
     const double e = exp_neg(x.v);
     return {e, e * x.d};
 }
-__device__ __forceinline__ Dual ln(Dual x) { return {ln(x.v), x.d * recip(x.v)}; }
-__device__ __forceinline__ Dual lg(Dual x) { return {lg(x.v), x.d * recip(x.v * 2.302585092994045684)}; }
+// (divided where the value may be so small that its reciprocal overflows)
+template <bool SUB = false>
+__device__ __forceinline__ Dual ln(Dual x) { return {ln<SUB>(x.v), SUB ? x.d / x.v : x.d * recip(x.v)}; }
+__device__ __forceinline__ Dual lg(Dual x) { return {lg(x.v), x.d / (x.v * 2.302585092994045684)}; }
 __device__ __forceinline__ Dual log(Dual x) { return {::log(x.v), x.d / x.v}; }
 __device__ __forceinline__ Dual log10(Dual x) { return {::log10(x.v), x.d / (x.v * 2.302585092994045684)}; }
 

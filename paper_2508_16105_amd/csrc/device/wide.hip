@@ -400,7 +400,7 @@ __device__ __forceinline__ void reaction(const Entry& en, const Slots<DERIV>& sl
                 const double d = tg * tn * (itd * itd);
                 dF_dPr = troe && !floored ? d : dF_dPr;
                 const double dF_dFc = iop + tg * (-0.67 * tn + 1.27 * tu) * (itd * itd);
-                const double dT = mech::LN10 * dF_dFc * (dFc * chem_math::recip(Fc * mech::LN10));
+                const double dT = mech::LN10 * dF_dFc * (dFc / (Fc * mech::LN10));
                 dlnF_T = troe ? dT : dlnF_T;
             }
         }
@@ -410,7 +410,7 @@ __device__ __forceinline__ void reaction(const Entry& en, const Slots<DERIV>& sl
             const double sea = tw[0] * chem_math::exp_neg(tw[1] * x.iT);
             const double sec = chem_math::exp_neg(-x.T * tw[2]);
             const double sY = sea + sec;
-            const double lnsY = chem_math::ln(sY);
+            const double lnsY = chem_math::ln<true>(sY);
             const double sX = chem_math::recip(1.0 + logPr * logPr);
             Fb = chem_math::exp_poly(sX * lnsY + tw[5] * x.lnT + tw[4]);
             if (DERIV) {

@@ -57,6 +57,20 @@ def far_source(kind, T, p, Y):
     return f
 
 
+# A logarithm of a subnormal number: the sum of an SRI factor, or a Troe centre,
+# that is e^{-T/2} alone.  log10(P_r) is about 10, so F stays an ordinary number.
+SMALL = {"sri": tiny.falloff(kind="sri", A0=1e28, sri=(0.0, 300.0, 2.0, 1.0, 0.0)),
+         "troe": tiny.falloff(kind="troe", A0=1e28, troe=(1.0, 300.0, 2.0, None))}
+SMALL_T = [1000.0, 1424.0, 1432.0, 1440.0]
+
+
+def small_tolerance(T):
+    """The bar of the parity tests, and what one unit in the last place of the
+    subnormal e^{-T/2} (2^-1074) makes of it: its logarithm enters F with a factor
+    of order one."""
+    return 1e-11 + 4.0 * 2.0 ** -1074 / np.exp(-np.asarray(T) / 2.0)
+
+
 def oracle_source(om, T, p, Y):
     return np.array([om.rhs(p[i], np.concatenate([[T[i]], Y[i]])) for i in range(len(T))])
 
@@ -67,3 +81,15 @@ def check_source(f, fo):
     assert np.array_equal(np.isnan(f), np.isnan(fo)), (f, fo)
     ok = ~np.isnan(fo).any(axis=1)
     assert np.all(np.abs(f - fo)[ok] <= 1e-11 * np.abs(fo[ok]).max(axis=1, keepdims=True) + 1e-300), (f, fo)
+
+
+def oracle_jacobian(om, T, p, Y):
+    return np.array([om.jac(p[i], np.concatenate([[T[i]], Y[i]])) for i in range(len(T))])
+
+
+def check_small(f, fj, J, fo, Jo, T):
+    tol = small_tolerance(T)
+    for g in (f, fj):
+        assert np.all(np.abs(g - fo) <= tol[:, None] * np.abs(fo).max(axis=1, keepdims=True)), (g, fo)
+    scale = np.abs(Jo).max(axis=2, keepdims=True)
+    assert np.all(np.abs(J - Jo) <= 10.0 * tol[:, None, None] * scale), (J, Jo)

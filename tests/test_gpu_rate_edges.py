@@ -15,7 +15,7 @@ FORMS = [("lane", None), ("wave", "0")]
 
 @pytest.fixture(scope="module")
 def evaluate(tmp_path_factory, oracle_lib):
-    """(text, CHEM_LANE_MAX_SPECIES) -> source terms alone, with the Jacobian, the oracle's"""
+    """(text, CHEM_LANE_MAX_SPECIES) -> source terms alone, with the Jacobian, the oracle's both"""
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     import paper_2508_16105_amd as chem
     wd = tmp_path_factory.mktemp("rates")
@@ -39,7 +39,7 @@ def evaluate(tmp_path_factory, oracle_lib):
         a = [torch.tensor(v, dtype=torch.float64, device="cuda:0") for v in (T, p, Y)]
         f = chem.eval_source(gm, *a, jacobian=False)[0].cpu().numpy()
         fj, J = (v.cpu().numpy() for v in chem.eval_source(gm, *a, jacobian=True))
-        return f, fj, J, rc.oracle_source(om, T, p, Y)
+        return f, fj, J, rc.oracle_source(om, T, p, Y), rc.oracle_jacobian(om, T, p, Y)
     return run
 
 
@@ -47,7 +47,7 @@ def evaluate(tmp_path_factory, oracle_lib):
 @pytest.mark.parametrize("centre", sorted(rc.CENTRE))
 def test_a_troe_centre_below_zero_is_not_a_number(evaluate, centre, form, lane_max):
     T, p, Y = rc.states(4, rc.CENTRE_T)
-    f, fj, J, fo = evaluate(rc.CENTRE[centre], lane_max, T, p, Y)
+    f, fj, J, fo, _ = evaluate(rc.CENTRE[centre], lane_max, T, p, Y)
     rc.check_source(f, fo)
     rc.check_source(fj, fo)
     assert np.array_equal(np.isnan(J).any(axis=(1, 2)), np.isnan(fo).any(axis=1))
@@ -62,8 +62,16 @@ def test_a_reverse_rate_whose_equilibrium_constant_is_out_of_range(evaluate, kin
     below the smallest normal double keeps its rounding of 2^-1074, in source terms
     below 1e-290."""
     T, p, Y = rc.states(3, rc.FAR_T, y=y)
-    f, fj, J, _ = evaluate(rc.FAR[kind], lane_max, T, p, Y)
+    f, fj, J, _, _ = evaluate(rc.FAR[kind], lane_max, T, p, Y)
     ref = rc.far_source(kind, T, p, Y)
     assert np.isfinite(J).all()
     for g in (f, fj):
         assert np.all(np.abs(g - ref) <= 1e-12 * np.abs(ref).max(axis=1, keepdims=True) + 1e-290), (g, ref)
+
+
+@pytest.mark.parametrize("form,lane_max", FORMS)
+@pytest.mark.parametrize("kind", sorted(rc.SMALL))
+def test_logarithms_of_subnormal_numbers(evaluate, kind, form, lane_max):
+    T, p, Y = rc.states(4, rc.SMALL_T)
+    f, fj, J, fo, Jo = evaluate(rc.SMALL[kind], lane_max, T, p, Y)
+    rc.check_small(f, fj, J, fo, Jo, T)
