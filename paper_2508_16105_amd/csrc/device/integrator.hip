@@ -234,13 +234,19 @@ struct StashLayout {
 // ROLL: the five stages as a loop.  Unrolled, the 13-species step is 230 KB of
 // code, 3.5 times the instruction cache that two CUs share; as a loop 121 KB:
 // 115 against 129 ms on a 100,000-cell field, 31 against 33 ms on 4,096
-// reactors, 139 against 142 ms on 400,000 cells in seven fields.  The
-// unrolled kernel is also one the compiler gets wrong: after a step that fails
-// from its first source term on (all mass fractions zero) its next step size
-// came out below any limit.  Nine species (113 KB unrolled) gain nothing (28.7
-// and 29.0 ms on 1M cells), and a kernel that makes one step fetches its code
-// once either way and loses the overlap of the stages (13 species, 124 against
-// 112 us), so those unroll.
+// reactors, 139 against 142 ms on 400,000 cells in seven fields.  Nine species
+// (113 KB unrolled) gain nothing (28.7 and 29.0 ms on 1M cells), and a kernel
+// that makes one step fetches its code once either way and loses the overlap of
+// the stages (13 species, 124 against 112 us), so those unroll.
+//
+// A step has no divergent branch: what a rate does not need in some lane is
+// formed all the same and dropped by a select.  At the join of a divergent
+// branch the compiler may put copies of registers live across it before the
+// restore of the execution mask, so a lane that skipped the block goes on
+// without them.  It did so in the unrolled 13-species kernel around a falloff
+// reaction's logarithm, which was skipped where P_r is floored (a state without
+// mass): that lane went on with other numbers as two of its mass fractions, and
+// its steps, which hold NaN throughout, were accepted.
 constexpr bool kRollStages = kFactorsInLds;
 template <bool STASH, bool ROLL>
 __device__ __forceinline__ bool ros_step_impl(const double* __restrict__ par, double p, double ip,

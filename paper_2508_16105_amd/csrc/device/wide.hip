@@ -372,7 +372,8 @@ __device__ __forceinline__ void reaction(const Entry& en, const Slots<DERIV>& sl
         const double r0 = chem_math::exp_poly(lnr0);
         const double Pr = r0 * Mc;
         const bool floored = !(Pr >= 1e-300);
-        const double logPr = floored ? -300.0 : chem_math::lg(Pr);
+        const double lgPr = chem_math::lg(Pr);
+        const double logPr = floored ? -300.0 : lgPr;
         const double ipr1 = chem_math::recip(1.0 + Pr);
         double Fb = 1.0, dF_dPr = 0.0, dlnF_T = 0.0;
         if (mech::HAS_TROE) {

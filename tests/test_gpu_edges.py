@@ -147,3 +147,41 @@ def test_steps_that_fail_shrink_to_the_smallest(chem, name, lane_max, state):
     assert out[1][2].tolist() == [0, 0, 0, 0, 2, 0, 0, 0, 0] and out[1][3][4] == 0 and out[1][4][4] == 29
     rest = [0, 1, 2, 3, 5, 6, 7, 8]
     assert all(torch.equal(x[rest], y[rest]) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("name", ["m9", "m13"])
+@pytest.mark.parametrize("state", ["no mass", "negative T"])
+def test_a_failed_single_step_one_cell_per_lane(chem, oracle_lib, name, state):
+    """NaN in T and in every species some reaction changes (the oracle's are), the
+    cells beside it untouched."""
+    gm, om = _load(chem, name), oracle_lib.Mechanism(mech_path(name))
+    n = 70                                        # a whole wave and a part of one
+    T, p, Y = uniform_cells(mech_text(name), n, 5)
+    run = lambda: [v.cpu() for v in chem.step_fixed(gm, _g(T), _g(p), _g(Y), 1e-13, RTOL, ATOL)]
+    good = run()
+    assert bool((good[2] == 1).all()) and bool(torch.isfinite(good[0]).all())
+    if state == "no mass":
+        Y[3] = Y[66] = 0.0
+    else:
+        T[3] = T[66] = -1.0
+    yn, en, ok = run()
+    rest = [k for k in range(n) if k not in (3, 66)]
+    assert ok[rest].tolist() == [1] * len(rest) and ok[[3, 66]].tolist() == [0, 0]
+    assert torch.equal(yn[rest], good[0][rest]) and torch.equal(en[rest], good[1][rest])
+    reacting = np.isnan(om.rhs(p[3], np.concatenate([[T[3]], Y[3]])))
+    for c in (3, 66):
+        assert bool(torch.isnan(en[c])) and np.all(np.isnan(yn[c].numpy())[reacting])
+
+
+@pytest.mark.parametrize("name,lane_max", [("m13", None), ("m13", 0), ("m13x", None), ("m9", None), ("m16", None)])
+def test_a_state_without_mass_never_passes(chem, name, lane_max):
+    """Every form of launch leaves it as it was and reports it failed."""
+    gm = _load(chem, name, lane_max)
+    T, p, Y = uniform_cells(mech_text(name), 130, 5)
+    cells = [0, 1, 4, 9, 64, 100, 129]
+    Y[cells] = 0.0
+    for form in (chem.FORM_PLAIN, chem.FORM_PERSISTENT):
+        Tw, Yw, _, st, na, _ = chem.integrate(gm, _g(T), _g(p), _g(Y), 1e-9, RTOL, ATOL, form=form, return_counts=True,
+                                              allow_failed=True)
+        assert st[cells].tolist() == [2] * len(cells) and na[cells].tolist() == [0] * len(cells), form
+        assert torch.equal(Tw[cells].cpu(), torch.tensor(T[cells])) and bool((Yw[cells] == 0.0).all())
