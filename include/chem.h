@@ -66,8 +66,10 @@ enum chem_cell_status {
     CHEM_CELL_HMIN = 2,         /* step size fell below hmin_rel * dt */
     CHEM_CELL_NONFINITE = 3,    /* adjoint only: the checkpointed rerun of a cell took more
                                    accepted steps than its sizing pass or the caller's
-                                   adjoint_nacc entry allows (for large mechanisms two and
-                                   1/32 more: only a wrong entry does it) */
+                                   adjoint_nacc entry allows (only a wrong entry does it:
+                                   where the rerun rounds differently from the forward
+                                   kernels, cells it outruns a right entry in go again
+                                   with room to spare) */
     CHEM_CELL_BADINPUT = 4      /* T <= 0, p <= 0 or a non-finite input */
 };
 
@@ -328,7 +330,8 @@ int chem_integrate_batched(const chem_mechanism *m, int nfield, double *const *T
    summed over cells in a fixed order (bitwise reproducible).  T_end/Y_end
    (device, both or neither) receive the forward result, bitwise equal to
    chem_integrate's.  The call first runs a sizing pass (unless
-   opt->adjoint_nacc gives the step counts), then stores each cell's state
+   opt->adjoint_nacc gives the step counts; the wave-cooperative form runs it all
+   the same if T_end/Y_end are wanted), then stores each cell's state
    every opt->checkpoint_every accepted steps (see chem_options; by default
    every step whenever memory allows) and recomputes in between, keeping what
    a replayed step's adjoint needs in a per-lane buffer of that many steps;

@@ -271,7 +271,8 @@ def integrate_adjoint(mech: Mechanism, T0, p, Y0, dt, rtol, atol, gT, gY, *, sta
     allow_failed) get NaN gT0/gY0 and add nothing to the parameter gradients.
     forward_nacc: the int32 per-cell accepted steps of a forward integration
     of the same input (integrate's nacc), which spares the adjoint its own
-    sizing pass.  end_state=False: T_end and Y_end are not wanted (None)."""
+    sizing pass.  end_state=False: T_end and Y_end are not wanted (None), which
+    with forward_nacc spares large mechanisms a forward integration."""
     torch = _torch()
     n = T0.shape[0]
     for t, nm, sh in ((T0, "T0", (n,)), (p, "p", (n,)), (Y0, "Y0", (n, mech.ns)),

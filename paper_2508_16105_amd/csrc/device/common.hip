@@ -196,7 +196,9 @@ struct AdjointArgs {
     // nullable, K = 1 only: every accepted step's factors and stage vectors
     // from the forward rerun, slot off_h[cell] + cell + step (one spare slot
     // per cell for an attempt past its count)
-    double* trail;
+    double* trail;    // wave-cooperative form, nullable: the cells' status in the forward kernels,
+    // which round differently from the rerun; a cell that failed there fails
+    const int* forward_status;
 };
 
 // lanes per group of the grouped adjoint (a power of two >= the RODAS4 stages)

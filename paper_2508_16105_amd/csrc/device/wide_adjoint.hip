@@ -964,21 +964,6 @@ __device__ __noinline__ void step_adjoint(const double* __restrict__ par, double
 
 }  // namespace chemw
 
-// ---- accepted steps of every cell (the arenas' sizes), cells in index order ----
-extern "C" __global__ void __launch_bounds__(64, 2) chem_adjoint_size(chem::IntegrateArgs a)
-{
-    using namespace chemw;
-    extern __shared__ double lds[];
-    const int grp = (int)threadIdx.x / G;
-    const long cell = (long)blockIdx.x * CPW + grp;
-    if (cell >= a.ncell) return;
-    double* L = lds + grp * mech::LDS_CELL;
-    Cell c;
-    cell_begin(c, a.T[cell], a.p[cell], a.Y + cell * NS, a.h0 ? a.h0[cell] : a.step.dt);
-    while (!c.done) cell_attempt(c, a.par, a.step, L, L + mech::L_J);
-    cell_store(c, a.T, a.Y, cell, a.status, a.nacc, a.nrej);
-}
-
 // ---- discrete adjoint: one group per cell, cells in descending cost order ----
 // The forward solve is rerun, storing every accepted step size and the state
 // every K accepted steps; then the reverse sweep recomputes each segment from
@@ -1024,6 +1009,7 @@ extern "C" __global__ void __launch_bounds__(64) chem_adjoint(AdjointArgs a)
                 if (i == 0) hs[c.nacc - 1] = hacc;
             }
         }
+        if (a.forward_status && a.forward_status[cell] != chem::CELL_OK) c.status = a.forward_status[cell];
         cell_store(c, a.Tend, a.Yend, cell, a.status, a.nacc, a.nrej);
         if (c.status == chem::CELL_BADINPUT) {
             if (i == 0) a.Tend[cell] = a.T0[cell];

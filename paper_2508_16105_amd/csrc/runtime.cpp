@@ -93,10 +93,7 @@ int device_state(chem_mechanism* m, hipStream_t stream, DeviceState** out)
         rc = rc ? rc : load_function(d.module, "chem_reduce_stats", &d.f_stats);
         rc = rc ? rc : load_function(d.module, "chem_persistent", &d.f_persistent);
         rc = rc ? rc : load_function(d.module, "chem_reset_heads", &d.f_reset);
-        if (m->wide) {
-            HIPCHECK(hipModuleLoadData(&d.adjoint_module, m->adjoint_code.data()), "hipModuleLoadData");
-            rc = rc ? rc : load_function(d.adjoint_module, "chem_adjoint_size", &d.f_adj_size);
-        }
+        if (m->wide) HIPCHECK(hipModuleLoadData(&d.adjoint_module, m->adjoint_code.data()), "hipModuleLoadData");
         rc = rc ? rc : load_function(m->wide ? d.adjoint_module : d.module, "chem_adjoint", &d.f_adjoint);
         rc = rc ? rc : load_function(d.module, "chem_reduce_params", &d.f_rparams);
         rc = rc ? rc : load_function(d.module, "chem_source_begin", &d.f_src_begin);
@@ -894,10 +891,28 @@ int run_euler1d(chem_mechanism* m, int64_t ncell, double dx, double dt, const do
 
 namespace {
 
-int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, const double* T0, const double* p,
-                 const double* Y0, const double* gT, const double* gY, double* gT0, double* gY0, double* g_lnA,
-                 double* g_b, double* g_Ea, double* T_end, double* Y_end, const Options& o, int K, const StepArgs& step,
-                 int32_t* i32, const std::vector<int32_t>& nacc_h, chem_stats* stats, hipStream_t stream);
+// One call of the adjoint: its arrays, and the device buffers its passes share.
+struct Adjoint {
+    chem_mechanism* m;
+    DeviceState* d;
+    Scratch& s;
+    int64_t ncell;
+    const double *T0, *p, *Y0, *gT, *gY;
+    double *gT0, *gY0, *T_end, *Y_end;
+    const Options& o;
+    hipStream_t stream;
+    int32_t *st, *limit, *na, *nj;   // status, most accepted steps, accepted, rejected [ncell]
+    const int32_t* forward_status;   // nullable
+    int K;
+    // parameter gradients: partial sums of every pass, and the kernels' time
+    std::vector<std::pair<double*, int64_t>> sums;
+    float ms = 0.f;
+
+    int pass(const std::vector<int32_t>& limit_h, const std::vector<int32_t>& order, const StepArgs& step);
+    int reduce(double* g_lnA, double* g_b, double* g_Ea, chem_stats* stats);
+};
+
+std::vector<int32_t> by_descending_steps(const std::vector<int32_t>& steps);
 
 }  // namespace
 
@@ -921,94 +936,129 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
         return launch_1d(d->f_rparams, (int64_t)3 * nr * 256, 256, &rp, sizeof rp, stream, "chem_reduce_params");
     }
     Scratch s(stream);
-    double *Tw, *Yw;
     int32_t* i32;
-    if (int rc = s.alloc(&Tw, ncell, "adjoint T")) return rc;
-    if (int rc = s.alloc(&Yw, (size_t)ncell * ns, "adjoint Y")) return rc;
     if (int rc = s.alloc(&i32, 4 * (size_t)ncell, "adjoint counters")) return rc;
-    int32_t *st = i32, *na_fwd = i32 + ncell, *na = i32 + 2 * ncell, *nj = i32 + 3 * ncell;
-    // sizing pass: the accepted steps of every cell fix the arena offsets
-    HIPCHECK(hipMemcpyAsync(Tw, T0, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T0");
-    HIPCHECK(hipMemcpyAsync(Yw, Y0, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y0");
+    int32_t *st = i32, *limit = i32 + ncell, *na = i32 + 2 * ncell, *nj = i32 + 3 * ncell;
     const StepArgs step = step_args(dt, rtol, atol, o);
-    if (o.adjoint_nacc)   // the caller's forward already counted the steps
-        HIPCHECK(hipMemcpyAsync(na_fwd, o.adjoint_nacc, sizeof(int32_t) * ncell, hipMemcpyDeviceToDevice, stream),
-                 "copy the forward's step counts");
-    // (the wave-cooperative adjoint's own rerun rounds differently from the
-    // forward kernels, whose end state the caller gets: see below)
-    const bool forward = !o.adjoint_nacc || (m->wide && end_wanted);
-    if (forward) {
-        int32_t* counts = o.adjoint_nacc ? na : na_fwd;
+    // The forward kernels: end state, status and accepted steps of every cell
+    // (status and counts in buffers of their own, as the adjoint's rerun writes
+    // its own to the call's).
+    struct {
+        double *T = nullptr, *Y = nullptr;
+        int32_t *status = nullptr, *counts = nullptr;
+    } fwd;
+    auto run_forward = [&]() -> int {
+        int32_t* b;
+        if (int rc = s.alloc(&fwd.T, ncell, "adjoint T")) return rc;
+        if (int rc = s.alloc(&fwd.Y, (size_t)ncell * ns, "adjoint Y")) return rc;
+        if (int rc = s.alloc(&b, 3 * (size_t)ncell, "adjoint forward counters")) return rc;
+        fwd.status = b;
+        fwd.counts = b + ncell;
+        int32_t* rejected = b + 2 * ncell;
+        HIPCHECK(hipMemcpyAsync(fwd.T, T0, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T0");
+        HIPCHECK(hipMemcpyAsync(fwd.Y, Y0, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y0");
         if (o.h0) {
-            IntegrateArgs ia{d->par, Tw, p, Yw, (long)ncell, o.h0, st, counts, nj, step, nullptr};
-            if (int rc = launch_plain(m, *d, ia, stream)) return rc;
-        } else {   // the persistent form takes the same steps, bitwise, sooner
-            FieldView fv{Tw, p, Yw, ncell, st, counts, nj, nullptr, nullptr};
-            Options po = o;
-            po.form = CHEM_FORM_PERSISTENT;
-            if (int rc = run_persistent(m, &fv, 1, dt, rtol, atol, po, nullptr, stream)) return rc;
+            IntegrateArgs ia{d->par, fwd.T, p, fwd.Y, (long)ncell, o.h0, fwd.status, fwd.counts, rejected, step,
+                             nullptr};
+            return launch_plain(m, *d, ia, stream);
         }
-    }
-    std::vector<int32_t> nacc_h(ncell);
-    HIPCHECK(hipMemcpyAsync(nacc_h.data(), na_fwd, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
+        // (the persistent form takes the same steps, bitwise, sooner)
+        FieldView fv{fwd.T, p, fwd.Y, ncell, fwd.status, fwd.counts, rejected, nullptr, nullptr};
+        Options po = o;
+        po.form = CHEM_FORM_PERSISTENT;
+        return run_persistent(m, &fv, 1, dt, rtol, atol, po, nullptr, stream);
+    };
+    // The most steps a cell's rerun may accept fixes its place in the arenas:
+    // the caller's counts, or those of a forward integration.  The
+    // wave-cooperative rerun rounds differently from the forward kernels, whose
+    // end state the caller gets and whose failures are the call's.
+    if (!o.adjoint_nacc || (m->wide && end_wanted))
+        if (int rc = run_forward()) return rc;
+    HIPCHECK(hipMemcpyAsync(limit, o.adjoint_nacc ? o.adjoint_nacc : fwd.counts, sizeof(int32_t) * ncell,
+                            hipMemcpyDeviceToDevice, stream),
+             "copy the forward's step counts");
+    std::vector<int32_t> limit_h(ncell);
+    HIPCHECK(hipMemcpyAsync(limit_h.data(), limit, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
              "copy step counts");
     HIPCHECK(hipStreamSynchronize(stream), "sync sizing pass");
-    if (m->wide) {
-        // the rerun may take a step more or less than the forward kernels where
-        // an error estimate sits at the acceptance limit: two and 1 in 32 spare
-        for (auto& c : nacc_h)
-            if (c > 0) c += 2 + c / 32;
-        HIPCHECK(hipMemcpyAsync(na_fwd, nacc_h.data(), sizeof(int32_t) * ncell, hipMemcpyHostToDevice, stream),
-                 "copy step limits");
-    }
-    auto pass = [&] {
-        return adjoint_pass(m, *d, s, ncell, T0, p, Y0, gT, gY, gT0, gY0, g_lnA, g_b, g_Ea, T_end, Y_end, o, K, step,
-                            i32, nacc_h, stats, stream);
-    };
-    int rc = pass();
-    if (rc == CHEM_E_CELL_FAILED && m->wide && !o.adjoint_nacc) {
-        // a cell that outran the spare steps as well: the rerun's own counts
-        std::vector<int32_t> status_h(ncell);
-        HIPCHECK(hipMemcpyAsync(status_h.data(), st, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
-                 "copy status");
-        HIPCHECK(hipStreamSynchronize(stream), "sync status");
-        if (std::count(status_h.begin(), status_h.end(), (int32_t)CHEM_CELL_NONFINITE)) {
-            double *Ts, *Ys;
-            if (int rc2 = s.alloc(&Ts, ncell, "adjoint T")) return rc2;
-            if (int rc2 = s.alloc(&Ys, (size_t)ncell * ns, "adjoint Y")) return rc2;
-            HIPCHECK(hipMemcpyAsync(Ts, T0, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T0");
-            HIPCHECK(hipMemcpyAsync(Ys, Y0, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y0");
-            IntegrateArgs ia{d->par, Ts, p, Ys, (long)ncell, o.h0, st, na_fwd, nj, step, nullptr};
-            if (int rc2 = launch_1d(d->f_adj_size, ncell * m->rows.G, 64, &ia, sizeof ia, stream, "chem_adjoint_size",
-                                    m->rows.lds_bytes()))
-                return rc2;
-            HIPCHECK(hipMemcpyAsync(nacc_h.data(), na_fwd, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
-                     "copy step counts");
-            HIPCHECK(hipStreamSynchronize(stream), "sync sizing pass");
-            rc = pass();
+    Adjoint a{m, d, s, ncell, T0, p, Y0, gT, gY, gT0, gY0, T_end, Y_end, o, stream, st, limit, na, nj,
+              m->wide ? fwd.status : nullptr, K, {}};
+    if (int rc = a.pass(limit_h, by_descending_steps(limit_h), step)) return rc;
+    int rc = a.reduce(g_lnA, g_b, g_Ea, stats);
+    if (rc && rc != CHEM_E_CELL_FAILED) return rc;
+    if (rc && m->wide) {
+        // Cells that failed in the rerun alone, by a step its rounding accepted or
+        // rejected otherwise (an error estimate at the limit; 10^6 steps of fields
+        // of 16 and 32 species had none): they go again with room to spare.  An
+        // entry of the caller's below the forward's count is wrong, and fails.
+        auto host = [&](const int32_t* dev, std::vector<int32_t>& h) -> int {
+            h.resize(ncell);
+            HIPCHECK(hipMemcpyAsync(h.data(), dev, sizeof(int32_t) * ncell, hipMemcpyDeviceToHost, stream),
+                     "copy status");
+            HIPCHECK(hipStreamSynchronize(stream), "sync status");
+            return 0;
+        };
+        auto differs = [](int32_t x) {
+            return x == CHEM_CELL_MAXSTEPS || x == CHEM_CELL_HMIN || x == CHEM_CELL_NONFINITE;
+        };
+        std::vector<int32_t> st_h, fst_h, count_h, again;
+        if (int rc2 = host(st, st_h)) return rc2;
+        if (std::any_of(st_h.begin(), st_h.end(), differs)) {
+            if (!fwd.status)
+                if (int rc2 = run_forward()) return rc2;
+            if (int rc2 = host(fwd.status, fst_h)) return rc2;
+            if (int rc2 = host(fwd.counts, count_h)) return rc2;
+            for (int64_t c = 0; c < ncell; ++c)
+                if (differs(st_h[c]) && fst_h[c] == CHEM_CELL_OK && limit_h[c] >= count_h[c]) again.push_back((int32_t)c);
         }
+        StepArgs loose = step;
+        loose.max_substeps = (int)std::min<int64_t>(INT32_MAX, (int64_t)step.max_substeps + step.max_substeps / 32 + 64);
+        loose.hmin *= 0.5;
+        for (int attempt = 0; attempt < 3 && !again.empty(); ++attempt) {
+            for (int32_t c : again) limit_h[c] = (int32_t)std::min<int64_t>(loose.max_substeps, 2 * (int64_t)limit_h[c] + 64);
+            std::stable_sort(again.begin(), again.end(), [&](int32_t x, int32_t y) { return limit_h[x] > limit_h[y]; });
+            HIPCHECK(hipMemcpyAsync(limit, limit_h.data(), sizeof(int32_t) * ncell, hipMemcpyHostToDevice, stream),
+                     "copy step limits");
+            if (int rc2 = a.pass(limit_h, again, loose)) return rc2;
+            if (int rc2 = host(st, st_h)) return rc2;
+            again.erase(std::remove_if(again.begin(), again.end(),
+                                       [&](int32_t c) { return st_h[c] != CHEM_CELL_NONFINITE; }),
+                        again.end());
+            rc = CHEM_OK;
+        }
+        if (!rc) rc = a.reduce(g_lnA, g_b, g_Ea, stats);
+        if (rc && rc != CHEM_E_CELL_FAILED) return rc;
     }
-    if (!m->wide || !forward || (rc && rc != CHEM_E_CELL_FAILED)) return rc;
-    // the end state is the forward kernels' (bitwise chem_integrate's), not the
-    // rerun's
-    HIPCHECK(hipMemcpyAsync(T_end, Tw, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T");
-    HIPCHECK(hipMemcpyAsync(Y_end, Yw, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y");
+    if (m->wide && end_wanted) {   // the forward kernels' (bitwise chem_integrate's), not the rerun's
+        HIPCHECK(hipMemcpyAsync(T_end, fwd.T, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T");
+        HIPCHECK(hipMemcpyAsync(Y_end, fwd.Y, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y");
+    }
     return rc;
 }
 
 namespace {
 
-// The adjoint proper: arenas for nacc_h accepted steps a cell, the kernel, and
-// the parameter reduction.  i32: the call's counters (status, the steps on the
-// device, accepted, rejected).
-int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, const double* T0, const double* p,
-                 const double* Y0, const double* gT, const double* gY, double* gT0, double* gY0, double* g_lnA,
-                 double* g_b, double* g_Ea, double* T_end, double* Y_end, const Options& o, int K, const StepArgs& step,
-                 int32_t* i32, const std::vector<int32_t>& nacc_h, chem_stats* stats, hipStream_t stream)
+// cells by descending step counts (a counting sort, stable in cell index)
+std::vector<int32_t> by_descending_steps(const std::vector<int32_t>& steps)
 {
-    DeviceState* d = &ds;
+    const int64_t ncell = (int64_t)steps.size();
+    std::vector<int32_t> order(ncell);
+    int32_t mx = 0;
+    for (int64_t c = 0; c < ncell; ++c) mx = std::max(mx, std::max<int32_t>(steps[c], 0));
+    std::vector<int64_t> start(mx + 2, 0);
+    for (int64_t c = 0; c < ncell; ++c) ++start[mx - std::max<int32_t>(steps[c], 0) + 1];
+    for (int32_t b = 0; b <= mx; ++b) start[b + 1] += start[b];
+    for (int64_t c = 0; c < ncell; ++c) order[start[mx - std::max<int32_t>(steps[c], 0)]++] = (int32_t)c;
+    return order;
+}
+
+// The adjoint kernel over the cells of `order` (by descending limits): arenas
+// for limit_h accepted steps a cell (the device has them in `limit`).  Waits
+// for the kernel.
+int Adjoint::pass(const std::vector<int32_t>& limit_h, const std::vector<int32_t>& order, const StepArgs& step)
+{
     const int n = m->data.ns() + 1, nr = m->data.nr();
-    int32_t *st = i32, *na_fwd = i32 + ncell, *na = i32 + 2 * ncell, *nj = i32 + 3 * ncell;
+    const int64_t cells = (int64_t)order.size();
     if (K == 0) {
         // the densest checkpoints whose arena fits a quarter of the free device
         // memory: every step stored means no recomputation in the reverse sweep
@@ -1017,7 +1067,7 @@ int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, 
         K = 16;
         for (int k : {1, 2, 4, 8, 16}) {
             double bytes = 0.0;
-            for (int64_t c = 0; c < ncell; ++c) bytes += (double)((std::max<int32_t>(nacc_h[c], 0) + k - 1) / k);
+            for (int32_t c : order) bytes += (double)(((int64_t)std::max<int32_t>(limit_h[c], 0) + k - 1) / k);
             if (bytes * n * sizeof(double) <= 0.25 * (double)freeb) {
                 K = k;
                 break;
@@ -1026,26 +1076,20 @@ int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, 
     }
     std::vector<long> off(2 * (size_t)ncell);
     long th = 0, tc = 0;
-    for (int64_t c = 0; c < ncell; ++c) {
+    auto place = [&](int64_t c) {
         off[c] = th;
         off[ncell + c] = tc;
-        const long k = std::max<int32_t>(nacc_h[c], 0);
+        const long k = std::max<int32_t>(limit_h[c], 0);
         th += k;
         tc += (k + K - 1) / K;
-    }
-    // cells by descending accepted steps (a counting sort, stable in cell index)
-    std::vector<int32_t> order(ncell);
-    {
-        int32_t mx = 0;
-        for (int64_t c = 0; c < ncell; ++c) mx = std::max(mx, std::max<int32_t>(nacc_h[c], 0));
-        std::vector<int64_t> start(mx + 2, 0);
-        for (int64_t c = 0; c < ncell; ++c) ++start[mx - std::max<int32_t>(nacc_h[c], 0) + 1];
-        for (int32_t b = 0; b <= mx; ++b) start[b + 1] += start[b];
-        for (int64_t c = 0; c < ncell; ++c) order[start[mx - std::max<int32_t>(nacc_h[c], 0)]++] = (int32_t)c;
-    }
+    };
+    if (cells == ncell)
+        for (int64_t c = 0; c < ncell; ++c) place(c);
+    else
+        for (int32_t c : order) place(c);
     int32_t* order_d;
-    if (int rc = s.alloc(&order_d, (size_t)ncell, "adjoint order")) return rc;
-    HIPCHECK(hipMemcpyAsync(order_d, order.data(), sizeof(int32_t) * ncell, hipMemcpyHostToDevice, stream),
+    if (int rc = s.alloc(&order_d, (size_t)cells, "adjoint order")) return rc;
+    HIPCHECK(hipMemcpyAsync(order_d, order.data(), sizeof(int32_t) * cells, hipMemcpyHostToDevice, stream),
              "copy order");
     // as many lanes (lane groups) as the device keeps resident; each takes the
     // cells s, s + nslot, ... of the cost order and keeps one row of partial
@@ -1055,14 +1099,14 @@ int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, 
     if (m->wide) {
         ashmem = m->rows.adj_lds_bytes();
         const int64_t waves_per_cu = std::max<int64_t>(1, std::min<int64_t>(8, (160 * 1024) / std::max(1u, ashmem)));
-        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * waves_per_cu * m->rows.cells_per_wave());
+        nslot = std::min<int64_t>(cells, (int64_t)d->num_cu * waves_per_cu * m->rows.cells_per_wave());
     } else {
         // the stage vectors (5 n doubles a lane), and during a step adjoint the
         // 3 nr parameter accumulators when they fit 80 doubles a lane (the
         // device code's kAdjParamsInLds)
         const int words = std::max(d->lane_words(), 3 * nr <= 80 ? 3 * nr : 0);
         ashmem = (unsigned)(64 * words * sizeof(double));
-        nslot = std::min<int64_t>(ncell, (int64_t)d->num_cu * 4 * 64);
+        nslot = std::min<int64_t>(cells, (int64_t)d->num_cu * 4 * 64);
     }
     // One cell per lane: the most expensive cells (those within a fraction of
     // the largest step count) go to groups of kAdjGroupLanes lanes, which split
@@ -1070,19 +1114,19 @@ int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, 
     // kernel's critical path; whole waves of groups, at most a quarter of the
     // resident waves, the rest of the lanes one cell each.
     long ngroup = 0, gcells = 0;
-    if (!m->wide && ncell > 0) {
+    if (!m->wide && cells > 0) {
         const int64_t cap = (int64_t)d->num_cu * 4 * 64;
         const double frac = adjoint_group_fraction();
-        const int32_t top = std::max<int32_t>(nacc_h[order[0]], 0);
+        const int32_t top = std::max<int32_t>(limit_h[order[0]], 0);
         int64_t cand = 0;
         if (frac > 0.0 && top > 0)
-            while (cand < ncell && std::max<int32_t>(nacc_h[order[cand]], 0) >= frac * top) ++cand;
+            while (cand < cells && std::max<int32_t>(limit_h[order[cand]], 0) >= frac * top) ++cand;
         const int64_t per_wave = 64 / kAdjGroupLanes;
         const int64_t gw = std::min<int64_t>((cand + per_wave - 1) / per_wave, cap / 64 / 4);
         if (gw > 0) {
             ngroup = (long)(gw * per_wave);
-            gcells = (long)std::min<int64_t>(ncell, ngroup);
-            nslot = gw * 64 + std::min<int64_t>(ncell - gcells, cap - gw * 64);
+            gcells = (long)std::min<int64_t>(cells, ngroup);
+            nslot = gw * 64 + std::min<int64_t>(cells - gcells, cap - gw * 64);
         }
     }
     long* off_d;
@@ -1119,24 +1163,49 @@ int adjoint_pass(chem_mechanism* m, DeviceState& ds, Scratch& s, int64_t ncell, 
         if (!(e && std::atoi(e) == 0) && slots * words * sizeof(double) <= freeb / 8)
             if (int rc = s.alloc(&trail, slots * words, "adjoint trail")) return rc;
     }
-    AdjointArgs aa{d->par, T0, p, Y0, (long)ncell, gT, gY, gT0, gY0, gpar, (long)nslot, T_end, Y_end, off_d,
-                   off_d + ncell, na_fwd, order_d, o.h0, hs, ck, st, na, nj, step, K, ngroup, gcells, stash, trail};
+    AdjointArgs aa{d->par, T0, p, Y0, (long)cells, gT, gY, gT0, gY0, gpar, (long)nslot, T_end, Y_end, off_d,
+                   off_d + ncell, limit, order_d, o.h0, hs, ck, st, na, nj, step, K, ngroup, gcells, stash, trail,
+                   forward_status};
     HIPCHECK(hipEventRecord(d->ev0, stream), "event");
     const int64_t alanes = m->wide ? nslot * m->rows.G : nslot;
     if (int rc = launch_1d(d->f_adjoint, alanes, 64, &aa, sizeof aa, stream, "chem_adjoint", ashmem)) return rc;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
+    sums.emplace_back(gpar, nslot);
+    // (also: the host arrays copied from above end here)
+    HIPCHECK(hipEventSynchronize(d->ev1), "event sync");
+    float t = 0.f;
+    HIPCHECK(hipEventElapsedTime(&t, d->ev0, d->ev1), "elapsed");
+    ms += t;
+    return 0;
+}
+
+// The parameter gradients, summed in a fixed order over the passes' lanes, and
+// the counters (synchronises the stream).
+int Adjoint::reduce(double* g_lnA, double* g_b, double* g_Ea, chem_stats* stats)
+{
+    const int nr = m->data.nr();
+    if (sums.size() > 1) {
+        int64_t rows = 0;
+        for (auto& q : sums) rows += q.second;
+        double* all;
+        if (int rc = s.alloc(&all, (size_t)rows * 3 * nr, "adjoint parameter partial sums")) return rc;
+        rows = 0;
+        for (auto& q : sums) {
+            HIPCHECK(hipMemcpyAsync(all + rows * 3 * nr, q.first, sizeof(double) * q.second * 3 * nr,
+                                    hipMemcpyDeviceToDevice, stream),
+                     "copy parameter partial sums");
+            rows += q.second;
+        }
+        sums.assign(1, {all, rows});
+    }
     struct {
         const double* g;
         long n;
         int np;
         double *a, *b, *e;
-    } rp{gpar, (long)nslot, 3 * nr, g_lnA, g_b, g_Ea};
-    if (int rc = launch_1d(d->f_rparams, (int64_t)3 * nr * 256, 256, &rp, sizeof rp, stream,
-                           "chem_reduce_params"))
+    } rp{sums[0].first, (long)sums[0].second, 3 * nr, g_lnA, g_b, g_Ea};
+    if (int rc = launch_1d(d->f_rparams, (int64_t)3 * nr * 256, 256, &rp, sizeof rp, stream, "chem_reduce_params"))
         return rc;
-    HIPCHECK(hipEventSynchronize(d->ev1), "event sync");
-    float ms = 0.f;
-    HIPCHECK(hipEventElapsedTime(&ms, d->ev0, d->ev1), "elapsed");
     chem_stats local{};
     return collect_stats(*d, st, na, nj, ncell, ms, stats ? stats : &local, stream);
 }

@@ -90,6 +90,7 @@ struct AdjointArgs {
     long gcells;       // cells (first positions of the cost order) the groups take
     double* stash;     // nullable: [nslot][K][stash words] (see StashLayout)
     double* trail;     // nullable, K = 1: [accepted steps + ncell][stash words]
+    const int* forward_status;   // nullable: the cells' status in the forward kernels
 };
 
 // lanes per group of the grouped one-cell-per-lane adjoint (device: kAdjGroup)
@@ -185,7 +186,7 @@ struct DeviceState {
                   f_stats = nullptr, f_persistent = nullptr, f_reset = nullptr, f_gather = nullptr,
                   f_okey = nullptr, f_oscan = nullptr, f_oscatter = nullptr, f_adjoint = nullptr,
                   f_rparams = nullptr, f_src_begin = nullptr, f_src_end = nullptr, f_euler_prim = nullptr,
-                  f_euler_update = nullptr, f_euler_init = nullptr, f_adj_size = nullptr,
+                  f_euler_update = nullptr, f_euler_init = nullptr,
                   f_dealt = nullptr;
     double* par = nullptr;               // 3 * nr device doubles
     uint64_t par_version = 0;
