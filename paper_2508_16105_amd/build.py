@@ -36,6 +36,7 @@ def embed_device_source():
     for var, name in (("kMathSource", "math.hip"), ("kCommonSource", "common.hip"),
                       ("kIntegratorSource", "integrator.hip"), ("kWideSource", "wide.hip"),
                       ("kWideAdjointSource", "wide_adjoint.hip"),
+                      ("kWideRowsSource", "wide_rows.hip"),
                       ("kEulerSource", "euler.hip")):
         src = (CSRC / "device" / name).read_text()
         assert f"){delim}\"" not in src
@@ -57,45 +58,63 @@ def compile_host(verbose=False):
     os.replace(tmp, LIB)
 
 
-def prebuild_mechanisms(builds=None):
-    """Compile the device code of the committed mechanisms into the cache."""
+def _prebuild(kind, nm, lane_max=None):
+    """Compile the device code of one mechanism into the cache."""
     # torch brings its own hipRTC; loaded first it is the compiler a program
     # that imports torch gets, and the cache key names the compiler
     import torch  # noqa: F401
+    import tempfile
     sys.path.insert(0, str(ROOT))
     from paper_2508_16105_amd import _lib
-    mdir = ROOT / "workloads" / "mech"
-    old = os.environ.get("CHEM_LANE_MAX_SPECIES")
-    try:
-        for nm, lane_max in builds or PREBUILT:
-            if lane_max is None:
-                os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
+    from workloads import gen_mech, resized
+    os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
+    if lane_max is not None:
+        os.environ["CHEM_LANE_MAX_SPECIES"] = lane_max
+    golden = ROOT / "tests" / "golden"
+    with tempfile.TemporaryDirectory() as td:
+        td = pathlib.Path(td)
+        if kind == "mech":
+            _lib.load_mechanism_handle(str(ROOT / "workloads" / "mech" / f"{nm}.mech"))
+        elif kind == "resized":
+            p = td / f"{nm}.mech"
+            p.write_text(resized.CASES[nm]())
+            _lib.load_mechanism_handle(str(p))
+        elif kind == "chemkin":
+            p = td / f"{nm}.inp"
+            p.write_text(gen_mech.to_chemkin(gen_mech.build_mechanism(nm)))
+            _lib.load_mechanism_handle(str(p))
+        elif kind == "openfoam":
+            r, t = gen_mech.to_openfoam(gen_mech.build_mechanism(nm))
+            rp, tp = td / f"{nm}.foam", td / "thermo"
+            rp.write_text(r)
+            tp.write_text(t)
+            _lib.load_mechanism_handle(str(rp), str(tp), "openfoam")
+        elif kind == "golden":
+            if nm == "foam_small":
+                _lib.load_mechanism_handle(str(golden / nm / "reactions"), str(golden / nm / "thermo"), "openfoam")
             else:
-                os.environ["CHEM_LANE_MAX_SPECIES"] = lane_max
-            _lib.load_mechanism_handle(str(mdir / f"{nm}.mech"))
-        os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
-        _lib.load_mechanism_handle(str(ROOT / "tests" / "golden" / "ck_small.inp"))
-        if builds is None:
-            import tempfile
-            from workloads import gen_mech
-            with tempfile.TemporaryDirectory() as td:
-                for nm in PREBUILT_CHEMKIN:
-                    p = pathlib.Path(td) / f"{nm}.inp"
-                    p.write_text(gen_mech.to_chemkin(gen_mech.build_mechanism(nm)))
-                    _lib.load_mechanism_handle(str(p))
-                for nm in PREBUILT_OPENFOAM:
-                    r, t = gen_mech.to_openfoam(gen_mech.build_mechanism(nm))
-                    rp, tp = pathlib.Path(td) / f"{nm}.foam", pathlib.Path(td) / "thermo"
-                    rp.write_text(r)
-                    tp.write_text(t)
-                    _lib.load_mechanism_handle(str(rp), str(tp), "openfoam")
-            fx = ROOT / "tests" / "golden" / "foam_small"
-            _lib.load_mechanism_handle(str(fx / "reactions"), str(fx / "thermo"), "openfoam")
-    finally:
-        if old is None:
-            os.environ.pop("CHEM_LANE_MAX_SPECIES", None)
-        else:
-            os.environ["CHEM_LANE_MAX_SPECIES"] = old
+                _lib.load_mechanism_handle(str(golden / f"{nm}.inp"))
+
+
+def prebuild_mechanisms(builds=None):
+    """Compile the device code of the committed mechanisms into the cache, a few
+    at a time in processes of their own."""
+    import concurrent.futures
+    sys.path.insert(0, str(ROOT))
+    from workloads import resized
+    jobs = [("mech", *b) for b in builds or PREBUILT]
+    if builds is None:
+        # (the ones that take longest first)
+        jobs = [("resized", nm) for nm in resized.CASES] + jobs
+        jobs += [("chemkin", nm) for nm in PREBUILT_CHEMKIN]
+        jobs += [("openfoam", nm) for nm in PREBUILT_OPENFOAM]
+        jobs += [("golden", nm) for nm in ("ck_small", "foam_small")]
+
+    def run(job):
+        subprocess.run([sys.executable, str(pathlib.Path(__file__).resolve()), *(a for a in job if a is not None)],
+                       check=True)
+    with concurrent.futures.ThreadPoolExecutor(min(4, len(os.sched_getaffinity(0)))) as pool:
+        list(pool.map(run, jobs))
 
 
 def prune_cache(since):
@@ -116,4 +135,7 @@ def build(verbose=False, mechanisms=True):
 
 
 if __name__ == "__main__":
-    build(verbose=True)
+    if sys.argv[1:]:
+        _prebuild(*sys.argv[1:])
+    else:
+        build(verbose=True)

@@ -133,16 +133,23 @@ int finish_load(std::unique_ptr<chem_mechanism> m, chem_mechanism** out)
         // so those keep the clamped conversion
         m->source = device_source(generate_mechanism_source(m->data), DeviceForm::Lane, m->data.ns() + 1 <= 10);
     } else {
-        m->layout = wide_layout(m->data);
-        if (m->layout.G == 0)
+        const WideLayout layout = wide_layout(m->data);
+        if (layout.G == 0)
             return set_error(CHEM_E_UNSUPPORTED, "mechanism outside the wave-cooperative tables (over 3 terms or a "
                                                      "coefficient over 3 on a reaction side, |dnu| over 4, or over "
                                                      "511 third-body or falloff reactions, or over 511 PLOG reactions)");
         m->wide = true;
-        m->source = device_source(generate_wide_source(m->data, m->layout), DeviceForm::Wide, true);
         m->rows = row_layout(m->data);
-        const std::string adjoint = device_source(generate_row_source(m->data, m->rows), DeviceForm::WideAdjoint, true);
-        if (int rc = build_code_object(adjoint, m->adjoint_code, err)) return set_error(rc, err);
+        if (layout.better()) {
+            m->wave = WaveLaunch{layout.block(), layout.cpw * layout.wpb, layout.lds_bytes(), layout.blocks_per_cu()};
+            m->source = device_source(generate_wide_source(m->data, layout), DeviceForm::Wide, true);
+            const std::string adjoint =
+                device_source(generate_row_source(m->data, m->rows), DeviceForm::WideAdjoint, true);
+            if (int rc = build_code_object(adjoint, m->adjoint_code, err)) return set_error(rc, err);
+        } else {
+            m->wave = WaveLaunch{64, m->rows.cells_per_wave(), m->rows.lds_bytes(), m->rows.blocks_per_cu()};
+            m->source = device_source(generate_row_source(m->data, m->rows), DeviceForm::WideRows, true);
+        }
     }
     if (int rc = build_code_object(m->source, m->code, err, &m->cache_file)) return set_error(rc, err);
     // with a gfx950 device current, load the code there now, so that the
@@ -282,12 +289,12 @@ int chem_eval_source(const chem_mechanism* mc, int64_t ncell, const double* T, c
     DeviceState* d;
     if (int rc = device_state(m, (hipStream_t)stream, &d)) return rc;
     EvalArgs a{d->par, T, p, Y, (long)ncell, f, J};
-    if (m->wide)
-        return launch_1d(d->f_eval,
-                         std::min<int64_t>(m->layout.lanes(ncell),
-                                           (int64_t)d->num_cu * m->layout.blocks_per_cu() * m->layout.block()),
-                         m->layout.block(), &a, sizeof a, (hipStream_t)stream, "chem_eval",
-                         m->layout.lds_bytes());
+    if (m->wide) {
+        // (the 16-lane form's resident workgroups share out the cells)
+        const int64_t lanes = m->wave.lanes(ncell), resident = (int64_t)d->num_cu * m->wave.blocks_per_cu * m->wave.block;
+        return launch_1d(d->f_eval, m->adjoint_apart() ? std::min(lanes, resident) : lanes, m->wave.block, &a, sizeof a,
+                         (hipStream_t)stream, "chem_eval", m->wave.lds);
+    }
     return launch_1d(d->f_eval, ncell, 64, &a, sizeof a, (hipStream_t)stream, "chem_eval");
 }
 
@@ -309,8 +316,8 @@ int chem_step_fixed(const chem_mechanism* mc, int64_t ncell, const double* T, co
     if (int rc = device_state(m, (hipStream_t)stream, &d)) return rc;
     FixedStepArgs a{d->par, T, p, Y, (long)ncell, h, ynew, errnorm, rtol, atol, ok};
     if (m->wide)
-        return launch_1d(d->f_fixed, m->layout.lanes(ncell), m->layout.block(), &a, sizeof a, (hipStream_t)stream, "chem_fixed_step",
-                         m->layout.lds_bytes());
+        return launch_1d(d->f_fixed, m->wave.lanes(ncell), m->wave.block, &a, sizeof a, (hipStream_t)stream,
+                         "chem_fixed_step", m->wave.lds);
     return launch_1d(d->f_fixed, ncell, 64, &a, sizeof a, (hipStream_t)stream, "chem_fixed_step",
                      d->stage_lds(64));
 }

@@ -41,9 +41,10 @@ struct WideLayout {
         const int by_lds = (int)(160u * 1024u / lds_bytes()), by_regs = 4 * waves_per_simd() / wpb;
         return by_lds < 1 ? 1 : by_lds < by_regs ? by_lds : by_regs;
     }
-    // workgroups, and lanes, of a launch over ncell cells
-    int64_t blocks(int64_t ncell) const { return (ncell + cpw * wpb - 1) / (cpw * wpb); }
-    int64_t lanes(int64_t ncell) const { return blocks(ncell) * block(); }
+    // The form is the better one where it fits: a lane owns at most three
+    // matrix rows (measured where the row-per-lane kernels are), and one cell's
+    // scratch and the tables fit the LDS.
+    bool better() const { return r <= 3 && lds_bytes() <= 160u * 1024u; }
 };
 
 // The layout for m, or an empty optional-like result (G = 0) if m does not
@@ -68,6 +69,12 @@ struct RowLayout {
     int adj_lds_cell = 0;  // doubles per cell in the adjoint: the scratch for dual numbers,
                            // then the pivot row and indices (untouched by source evaluations)
     int cells_per_wave() const { return 64 / G; }
+    // resident waves per compute unit of the forward kernels, by registers and LDS
+    int blocks_per_cu() const
+    {
+        const int by_lds = (int)(160u * 1024u / lds_bytes());
+        return by_lds < 1 ? 1 : by_lds < 8 ? by_lds : 8;
+    }
     unsigned lds_bytes() const { return (unsigned)(cells_per_wave() * lds_cell * sizeof(double)); }
     unsigned adj_lds_bytes() const { return (unsigned)(cells_per_wave() * adj_lds_cell * sizeof(double)); }
 };
@@ -79,5 +86,14 @@ RowLayout row_layout(const MechanismData& m);
 // HIP source of namespace mech for the wave-cooperative adjoint: sizes,
 // layout constants and the thermo, reaction and species tables they read.
 std::string generate_row_source(const MechanismData& m, const RowLayout& w);
+
+// The launches of a mechanism's wave-cooperative forward kernels.
+struct WaveLaunch {
+    int block = 64, cells = 1;       // lanes, and cells, of a workgroup
+    unsigned lds = 0;                // bytes of a workgroup
+    int blocks_per_cu = 1;           // resident workgroups per compute unit
+    int64_t blocks(int64_t ncell) const { return (ncell + cells - 1) / cells; }
+    int64_t lanes(int64_t ncell) const { return blocks(ncell) * block; }
+};
 
 }  // namespace chemmi

@@ -852,8 +852,10 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
         }
         const double J00 = -mech::RU * (cpw + x.T * HwT - HS) * rcpinv - fT * (dcp * icp - x.iT);
         A[0][0] = i == 0 ? J00 : A[0][0];
-#pragma unroll
-        for (int m = 0; m < NC - 1; ++m) {
+        // (static_for: a pragma stops unrolling above some 45 columns, and the rows
+        // then sit in scratch memory)
+        static_for<0, NC - 1>([&](auto mc) {
+            constexpr int m = decltype(mc)::v;
             double HJ = 0.0;
 #pragma unroll
             for (int r = 0; r < R; ++r) HJ = fma(th.HRT[r], A[r][1 + m], HJ);
@@ -873,7 +875,7 @@ __device__ __forceinline__ void rhs(const double* __restrict__ tab, double p, do
                 if (r * 16 + 15 >= NACT) v = a < NACT ? v : 0.0;
                 A[r][1 + m] = v;
             }
-        }
+        });
         if (R * 16 > NACT) A[R - 1][0] = (R - 1) * 16 + i < NACT ? A[R - 1][0] : 0.0;
     }
 }
@@ -1292,10 +1294,11 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_eval(EvalArgs 
             double A[R][N];
             rhs<true, N>(lds, c.p, c.ip, c.y, c.ywi, L, f, A);
             double za = 0.0;
+            static_for<0, N>([&](auto cc) {
+                constexpr int col = decltype(cc)::v;
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int col = 0; col < N; ++col) za = fma(0.0, A[r][col], za);
+                for (int r = 0; r < R; ++r) za = fma(0.0, A[r][col], za);
+            });
             za = gsum(za);
             double* const J = a.J + cell * N * N;
 #pragma unroll
@@ -1303,11 +1306,11 @@ extern "C" __global__ void __launch_bounds__(256, mech::WPS) chem_eval(EvalArgs 
                 const int k = mech::PSPEC[r * 16 + i];
                 const int row = r == 0 && i == 0 ? 0 : 1 + k;
                 if (row > 0 || (r == 0 && i == 0)) {
-#pragma unroll
-                    for (int col = 0; col < N; ++col) {
+                    static_for<0, N>([&](auto cc) {
+                        constexpr int col = decltype(cc)::v;
                         const int oc = col == 0 ? 0 : 1 + mech::COLSPEC[col - 1];
                         J[row * N + oc] = r < R ? A[r < R ? r : 0][col] : za;
-                    }
+                    });
                 }
             }
         } else {

@@ -2,7 +2,8 @@
 // matrices do not fit the registers of one lane (CDNA4, gfx950).
 //
 // Compiled into a code object of its own, with tables of its own, beside the
-// forward kernels of wide.hip.  It keeps one matrix row per lane and its own
+// forward kernels of wide.hip (with those of wide_rows.hip it is a form of its
+// own).  It keeps one matrix row per lane and its own
 // forward rerun.  On the flow fields of the 32-species mechanism the gradient
 // of a cell can have a condition of 1e7 and more (a species that is absent,
 // with rates of 1e20: a change of T by one unit in the last place moves the

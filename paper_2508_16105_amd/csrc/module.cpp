@@ -19,7 +19,7 @@
 
 namespace chemmi {
 
-#include "_device_source.inc"   // kMathSource, kCommonSource, kIntegratorSource, kWideSource, kWideAdjointSource, kEulerSource
+#include "_device_source.inc"   // kMathSource, kCommonSource, kIntegratorSource, kWideSource, kWideAdjointSource, kWideRowsSource, kEulerSource
 
 std::string device_source(const std::string& mechanism_code, DeviceForm form, bool exp_saturating)
 {
@@ -28,6 +28,9 @@ std::string device_source(const std::string& mechanism_code, DeviceForm form, bo
     const std::string shared = config + std::string(kMathSource) + "\n" + mechanism_code + "\n" +
                                std::string(kCommonSource) + "\n";
     if (form == DeviceForm::WideAdjoint) return shared + std::string(kWideAdjointSource);
+    if (form == DeviceForm::WideRows)
+        return shared + std::string(kWideAdjointSource) + "\n" + std::string(kWideRowsSource) + "\n" +
+               std::string(kEulerSource);
     return shared + std::string(form == DeviceForm::Wide ? kWideSource : kIntegratorSource) + "\n" +
            std::string(kEulerSource);
 }

@@ -9,9 +9,10 @@
 
 namespace chemmi {
 
-// The code objects of a mechanism: one cell per lane (everything), or the
-// wave-cooperative form's forward kernels and, apart, its adjoint.
-enum class DeviceForm { Lane, Wide, WideAdjoint };
+// The code objects of a mechanism: one cell per lane (everything), the
+// wave-cooperative form's forward kernels and, apart, its adjoint, or its
+// row-per-lane form (everything).
+enum class DeviceForm { Lane, Wide, WideAdjoint, WideRows };
 
 // The complete device source of one: the math, the generated mechanism code,
 // the shared and form-specific kernels.  exp_saturating picks how exp_poly

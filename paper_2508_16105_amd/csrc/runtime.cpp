@@ -93,8 +93,9 @@ int device_state(chem_mechanism* m, hipStream_t stream, DeviceState** out)
         rc = rc ? rc : load_function(d.module, "chem_reduce_stats", &d.f_stats);
         rc = rc ? rc : load_function(d.module, "chem_persistent", &d.f_persistent);
         rc = rc ? rc : load_function(d.module, "chem_reset_heads", &d.f_reset);
-        if (m->wide) HIPCHECK(hipModuleLoadData(&d.adjoint_module, m->adjoint_code.data()), "hipModuleLoadData");
-        rc = rc ? rc : load_function(m->wide ? d.adjoint_module : d.module, "chem_adjoint", &d.f_adjoint);
+        if (m->adjoint_apart())
+            HIPCHECK(hipModuleLoadData(&d.adjoint_module, m->adjoint_code.data()), "hipModuleLoadData");
+        rc = rc ? rc : load_function(m->adjoint_apart() ? d.adjoint_module : d.module, "chem_adjoint", &d.f_adjoint);
         rc = rc ? rc : load_function(d.module, "chem_reduce_params", &d.f_rparams);
         rc = rc ? rc : load_function(d.module, "chem_source_begin", &d.f_src_begin);
         rc = rc ? rc : load_function(d.module, "chem_source_end", &d.f_src_end);
@@ -243,9 +244,11 @@ namespace {
 
 int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t stream)
 {
-    int64_t lanes = m->wide ? m->layout.lanes(a.ncell) : a.ncell;
-    const unsigned shmem = m->wide ? m->layout.lds_bytes() : d.stage_lds(64);
-    const int block = m->wide ? m->layout.block() : 64;
+    int64_t lanes = m->wide ? m->wave.lanes(a.ncell) : a.ncell;
+    const unsigned shmem = m->wide ? m->wave.lds : d.stage_lds(64);
+    const int block = m->wide ? m->wave.block : 64;
+    if (m->wide && !m->adjoint_apart())   // row-per-lane form: by the grid at any size
+        return launch_1d(d.f_plain, lanes, block, &a, sizeof a, stream, "chem_plain", shmem);
     if (!d.plain_blocks_per_cu) {
         int n = 0;
         HIPCHECK(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, d.f_dealt, block, shmem), "occupancy");
@@ -470,8 +473,8 @@ int launch_graph_wide(DeviceState& d, const chem_mechanism* m, int64_t blocks, h
         void* pcfg[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &pa, HIP_LAUNCH_PARAM_BUFFER_SIZE, &ps, HIP_LAUNCH_PARAM_END};
         hipError_t e = hipModuleLaunchKernel(d.f_reset, 1, 1, 1, 256, 1, 1, 0, d.capture_stream, nullptr, rcfg);
         if (e == hipSuccess)
-            e = hipModuleLaunchKernel(d.f_persistent, (unsigned)blocks, 1, 1, (unsigned)m->layout.block(), 1, 1,
-                                      m->layout.lds_bytes(), d.capture_stream, nullptr, pcfg);
+            e = hipModuleLaunchKernel(d.f_persistent, (unsigned)blocks, 1, 1, (unsigned)m->wave.block, 1, 1,
+                                      m->wave.lds, d.capture_stream, nullptr, pcfg);
         hipError_t e2 = hipStreamEndCapture(d.capture_stream, &g);
         if (e != hipSuccess) return hip_error(e, "capture wave-cooperative launch");
         if (e2 != hipSuccess) return hip_error(e2, "end capture");
@@ -594,7 +597,7 @@ int run_persistent_wide(chem_mechanism* m, const FieldView* fv, int nfield, doub
     if (int rc = write_block(*d, fields, header_for(*d, total, nfield, c, s, CHEM_ORDER_NATURAL), stream)) return rc;
     if (stats) HIPCHECK(hipEventRecord(d->ev0, stream), "event");
     // resident workgroups: as many as the registers and the LDS scratch allow
-    const int64_t blocks = std::min<int64_t>((int64_t)d->num_cu * m->layout.blocks_per_cu(), m->layout.blocks(total));
+    const int64_t blocks = std::min<int64_t>((int64_t)d->num_cu * m->wave.blocks_per_cu, m->wave.blocks(total));
     if (int rc = launch_graph_wide(*d, m, blocks, stream)) return rc;
     if (!stats) return 0;
     HIPCHECK(hipEventRecord(d->ev1, stream), "event");
@@ -734,10 +737,9 @@ int run_noalloc(chem_mechanism* m, int64_t ncell, double* T, const double* p, do
     struct { const char* blk; unsigned long long* heads; const double* par; } pa{blk, heads, d->par};
     if (m->wide) {
         if (int rc = launch_1d(d->f_reset, 256, 256, &ra, sizeof ra, stream, "chem_reset_heads")) return rc;
-        const int64_t blocks =
-            std::min<int64_t>((int64_t)d->num_cu * m->layout.blocks_per_cu(), m->layout.blocks(ncell));
-        return launch_1d(d->f_persistent, blocks * m->layout.block(), m->layout.block(), &pa, sizeof pa, stream,
-                         "chem_persistent", m->layout.lds_bytes());
+        const int64_t blocks = std::min<int64_t>((int64_t)d->num_cu * m->wave.blocks_per_cu, m->wave.blocks(ncell));
+        return launch_1d(d->f_persistent, blocks * m->wave.block, m->wave.block, &pa, sizeof pa, stream,
+                         "chem_persistent", m->wave.lds);
     }
     auto launch = [&](hipFunction_t fn, unsigned grid, unsigned block, unsigned shmem, void* args, size_t size,
                       const char* what) {
@@ -970,9 +972,10 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
     };
     // The most steps a cell's rerun may accept fixes its place in the arenas:
     // the caller's counts, or those of a forward integration.  The
-    // wave-cooperative rerun rounds differently from the forward kernels, whose
+    // 16-lane form's rerun rounds differently from the forward kernels, whose
     // end state the caller gets and whose failures are the call's.
-    if (!o.adjoint_nacc || (m->wide && end_wanted))
+    const bool apart = m->adjoint_apart();
+    if (!o.adjoint_nacc || (apart && end_wanted))
         if (int rc = run_forward()) return rc;
     HIPCHECK(hipMemcpyAsync(limit, o.adjoint_nacc ? o.adjoint_nacc : fwd.counts, sizeof(int32_t) * ncell,
                             hipMemcpyDeviceToDevice, stream),
@@ -982,11 +985,11 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
              "copy step counts");
     HIPCHECK(hipStreamSynchronize(stream), "sync sizing pass");
     Adjoint a{m, d, s, ncell, T0, p, Y0, gT, gY, gT0, gY0, T_end, Y_end, o, stream, st, limit, na, nj,
-              m->wide ? fwd.status : nullptr, K, {}};
+              apart ? fwd.status : nullptr, K, {}};
     if (int rc = a.pass(limit_h, by_descending_steps(limit_h), step)) return rc;
     int rc = a.reduce(g_lnA, g_b, g_Ea, stats);
     if (rc && rc != CHEM_E_CELL_FAILED) return rc;
-    if (rc && m->wide) {
+    if (rc && apart) {
         // Cells that failed in the rerun alone, by a step its rounding accepted or
         // rejected otherwise (an error estimate at the limit; 10^6 steps of fields
         // of 16 and 32 species had none): they go again with room to spare.  An
@@ -1029,7 +1032,7 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
         if (!rc) rc = a.reduce(g_lnA, g_b, g_Ea, stats);
         if (rc && rc != CHEM_E_CELL_FAILED) return rc;
     }
-    if (m->wide && end_wanted) {   // the forward kernels' (bitwise chem_integrate's), not the rerun's
+    if (apart && end_wanted) {   // the forward kernels' (bitwise chem_integrate's), not the rerun's
         HIPCHECK(hipMemcpyAsync(T_end, fwd.T, sizeof(double) * ncell, hipMemcpyDeviceToDevice, stream), "copy T");
         HIPCHECK(hipMemcpyAsync(Y_end, fwd.Y, sizeof(double) * ncell * ns, hipMemcpyDeviceToDevice, stream), "copy Y");
     }

@@ -235,9 +235,12 @@ struct DeviceState {
 struct chem_mechanism {
     chemmi::MechanismData data;
     bool wide = false;                   // wave-cooperative kernels (else one cell per lane)
-    chemmi::WideLayout layout;           // of the wave-cooperative form
-    chemmi::RowLayout rows;              // of its adjoint
-    std::vector<char> adjoint_code;      // the adjoint's code object (wave-cooperative form)
+    chemmi::WaveLaunch wave;             // launches of the wave-cooperative form
+    chemmi::RowLayout rows;              // of its adjoint (and of all of its row-per-lane form)
+    // the adjoint's code object where the forward kernels are of the 16-lane
+    // form, which its rerun rounds differently from (else it is in `code`)
+    std::vector<char> adjoint_code;
+    bool adjoint_apart() const { return !adjoint_code.empty(); }
     std::vector<double> params;          // lnA[nr], b[nr], Ea/R[nr]
     uint64_t params_version = 1;
     std::string source;
