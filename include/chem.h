@@ -77,7 +77,8 @@ enum chem_form {
     CHEM_FORM_AUTO = 0,         /* plain for a single field */
     CHEM_FORM_PLAIN = 1,        /* one launch per field, a cell per lane (large mechanisms:
                                    per 16 lanes); above the lanes the GPU holds at once,
-                                   further cells go to lanes as they fall idle */
+                                   further cells go to lanes as they fall idle (not under
+                                   stream capture) */
     CHEM_FORM_PERSISTENT = 2    /* persistent work-stealing launch in a HIP graph */
 };
 

@@ -239,7 +239,7 @@ StepArgs step_args(double dt, double rtol, double atol, const Options& o)
 // The plain kernel over a.ncell cells.  Up to what the device holds at once
 // every cell has its place in the grid; above that the resident workgroups
 // take the cells through a counter (cleared first; the per-device state's
-// queue heads, which one call at a time uses).
+// queue heads, which one call at a time uses).  Under capture by the grid.
 namespace {
 
 int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t stream)
@@ -256,7 +256,11 @@ int launch_plain(chem_mechanism* m, DeviceState& d, IntegrateArgs a, hipStream_t
     }
     const int64_t resident = (int64_t)d.num_cu * d.plain_blocks_per_cu * block;
     a.head = nullptr;
-    if (lanes > resident) {
+    // (a graph may be replayed while another call on the handle runs, so a
+    // captured launch takes no counter of the handle's: by the grid)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIPCHECK(hipStreamIsCapturing(stream, &capture), "stream capture state");
+    if (lanes > resident && capture == hipStreamCaptureStatusNone) {
         lanes = resident;
         a.head = d.heads;
         struct { unsigned long long* p; int n; } za{d.heads, 1};

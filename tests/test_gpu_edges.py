@@ -185,3 +185,30 @@ def test_a_state_without_mass_never_passes(chem, name, lane_max):
                                               allow_failed=True)
         assert st[cells].tolist() == [2] * len(cells) and na[cells].tolist() == [0] * len(cells), form
         assert torch.equal(Tw[cells].cpu(), torch.tensor(T[cells])) and bool((Yw[cells] == 0.0).all())
+
+
+@pytest.mark.parametrize("name,n", [("m9", 65536 + 777), ("m16", 8192 + 777)])
+def test_a_captured_plain_launch_stands_alone(chem, name, n):
+    """Replays of a plain launch above the resident lanes beside other calls on the
+    same handle on another stream: each ends as it does alone."""
+    gm = _load(chem, name)
+    T, p, Y = uniform_cells(mech_text(name), n, 17)
+    a, b = ([_g(v) for v in (T[s], p[s], Y[s])] for s in (slice(None), slice(None, None, -1)))
+    run = lambda s: chem.integrate(gm, *s, 2e-10, RTOL, ATOL, form=chem.FORM_PLAIN, stats=False)[:2]
+    alone = run(a), run(b)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = run(a)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    for k in range(4):
+        with torch.cuda.stream(one):
+            for v in out:
+                v.zero_()
+            graph.replay()
+        with torch.cuda.stream(two):
+            other = [run(b) for _ in range(3)]
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(out, alone[0])), k
+        for o in other:
+            assert all(torch.equal(x, y) for x, y in zip(o, alone[1])), k
