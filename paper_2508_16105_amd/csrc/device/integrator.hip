@@ -50,12 +50,14 @@ __device__ __forceinline__ constexpr int P(int a) { return mech::PERM[a]; }
 constexpr int kLaneStride = 64;
 // entries of the LU factors the solves read
 constexpr int kFactorEntries = NACT * NACT;
-// From 11 unknowns the factors no longer fit beside the source-term temporaries
+// From 12 unknowns the factors no longer fit beside the source-term temporaries
 // and spill to private memory (measured at 12: 1.4 KB a lane), where every
 // solve waits on them; below, they stay in accumulation registers, whose two
-// moves per read cost less than an LDS load in the solve's chain (measured at
-// 9).
-constexpr bool kFactorsInLds = NACT >= 11;
+// moves per read cost less than an LDS load in the solve's chain.  65,536 cells
+// with them in registers against LDS, five mechanisms of 10 to 13 species: at 10
+// unknowns 93 against 111 ms and 69 against 82, at 11 74 against 85, 117 against
+// 131, and no difference in the fifth.
+constexpr bool kFactorsInLds = NACT >= 12;
 constexpr int kLdsBudget = 80;     // doubles a lane: 160 KB over four 64-lane waves
 constexpr int kFactorsLds = kFactorsInLds ? (kFactorEntries < kLdsBudget ? kFactorEntries : kLdsBudget) : 0;
 constexpr int kLaneWords = kFactorsInLds ? kFactorsLds : 5 * NACT;

@@ -224,9 +224,9 @@ struct DeviceState {
     int plain_blocks_per_cu = 0;         // resident workgroups of the plain kernel (0: not asked yet)
     int nact = 0;                        // unknowns of a step (active_unknowns)
     // LDS doubles a lane of the one-cell-per-lane kernels holds: the RODAS4
-    // stage vectors u_1..u_5, or from 11 unknowns on up to 80 entries of the
+    // stage vectors u_1..u_5, or from 12 unknowns on up to 80 entries of the
     // LU factors (the device code's kLaneWords never exceeds this)
-    int lane_words() const { return nact >= 11 ? 80 : 5 * nact; }
+    int lane_words() const { return nact >= 12 ? 80 : 5 * nact; }
     unsigned stage_lds(int block) const { return (unsigned)(block * lane_words() * sizeof(double)); }
 };
 

@@ -1,5 +1,6 @@
-"""Mechanisms at the sizes where the wave-cooperative form changes: three matrix
-rows a lane (34 species: one unknown in the third row; 48: 47 unknowns), and the
+"""Mechanisms at the sizes where the kernels change: 11 unknowns of the lane form
+(the most whose factors stay in registers); wave-cooperatively three matrix rows
+a lane (34 species: one unknown in the third row; 48: 47 unknowns), and the
 row-per-lane form (48 reacting species; 1,782 reactions, whose tables do not fit
 the LDS in the 16-lane form).  Bars as in the other parity tests."""
 import numpy as np
@@ -80,7 +81,9 @@ def test_integration(chem, mech):
 def test_fixed_step(chem, mech):
     gm, om, text, name = mech
     T, p, Y = uniform_cells(text, 21, 75)
-    h = 1e-11
+    # (hot cells of the 13-species reactions are stiffer: as in the other fixed-step
+    # tests they take smaller steps, or the oracle's own spread hides the step)
+    h = 1e-12 if name == "13" else 1e-11
     yn, en, ok = (v.cpu().numpy() for v in chem.step_fixed(gm, _g(T), _g(p), _g(Y), h, RTOL, ATOL))
     assert np.all(ok == 1)
     skipped = 0

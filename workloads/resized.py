@@ -1,6 +1,6 @@
-"""Mechanisms of other sizes made from the 32-species one: fewer species (the
-first of the list, and the reactions among them), or more (copies of reacting
-species, with some of the reactions of the species each is a copy of)."""
+"""Mechanisms of other sizes made from the 32-species one (or another): fewer
+species (the first of the list, and the reactions among them), or more (copies of
+reacting species, with some of the reactions of the species each is a copy of)."""
 import re
 
 from workloads import mech_text
@@ -33,10 +33,10 @@ def _sides(line):
     return w, side(w[2]), side(w[3])
 
 
-def resized(ns, per_copy=6, inert=True):
+def resized(ns, per_copy=6, inert=True, base="m32", first=None):
     """The text of an ns-species mechanism, named after its size; without `inert`
-    every species reacts."""
-    lines = [ln for ln in mech_text("m32").splitlines() if ln.strip() and not ln.startswith("#")]
+    every species reacts.  first: species kept of the base's (default ns)."""
+    lines = [ln for ln in mech_text(base).splitlines() if ln.strip() and not ln.startswith("#")]
     species = [ln.split()[1] for ln in lines if ln.startswith("species ")]
     comp = {ln.split()[1]: ln for ln in lines if ln.startswith("species ")}
     thermo = {ln.split()[1]: ln for ln in lines if ln.startswith("thermo ")}
@@ -44,7 +44,7 @@ def resized(ns, per_copy=6, inert=True):
     if not inert:
         used = {s for ln in reactions for side in _sides(ln)[1:] for s, _ in side}
         species = [s for s in species if s in used]
-    keep = species[:ns]
+    keep = species[:first or ns]
     rx = []
     for ln in reactions:
         _, a, b = _sides(ln)
@@ -69,11 +69,13 @@ def resized(ns, per_copy=6, inert=True):
             rx.append(" ".join(w))
         k += 1
     head = [ln for ln in lines if ln.startswith(("chemmi-mech", "element"))]
-    return "\n".join([head[0], f"name m32to{ns}" + ("" if inert else "r")] + head[1:] + out_comp + out_thermo + rx + ["end"]) + "\n"
+    return "\n".join([head[0], f"name {base}to{ns}" + ("" if inert else "r")] + head[1:] + out_comp + out_thermo + rx + ["end"]) + "\n"
 
 
-# The sizes at which the wave-cooperative form changes: the fewest and the most
-# unknowns at three matrix rows a lane; above them, and where the tables of a
+# The sizes at which the kernels change: the most unknowns of the lane form whose
+# factors stay in registers (11); the fewest and the most unknowns at three matrix
+# rows a lane of the wave-cooperative form; above them, and where the tables of a
 # mechanism do not fit the LDS in that form, its row-per-lane form.
-CASES = {"34": lambda: resized(34), "48": lambda: resized(48), "48r": lambda: resized(48, 5, inert=False),
+CASES = {"13": lambda: resized(13, 4, base="m13", first=11),
+         "34": lambda: resized(34), "48": lambda: resized(48), "48r": lambda: resized(48, 5, inert=False),
          "34by11": lambda: split(resized(34), 11)}
