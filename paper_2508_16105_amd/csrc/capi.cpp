@@ -26,15 +26,15 @@ using namespace chemmi;
 namespace {
 // Mechanisms with up to kLaneSpecies species run one cell per lane (the
 // cell's Jacobian and LU factors in one lane's registers); larger ones run
-// wave-cooperatively (16 lanes a cell).  At 13 species the two are close: the
-// lane form spills but keeps 64 cells in flight per SIMD against 8 and gives
-// the higher rate when work abounds (50,000 fixed steps: 124 us against 245),
-// the wave-cooperative form takes a third of the time per substep of a cell
-// and wins where the costliest cell is what is waited for (20,000-cell field:
-// 40 ms against 138; 1M cells: 242 against 303).  From 14 species on, the lane
-// form's spills grow steeply (14, 15, 16 and 18 species measured at 3-4 times
-// the time of the wave-cooperative form of that day, which has become 2-3
-// times faster), so 13 is the default limit.
+// wave-cooperatively (16 lanes a cell).  At 13 species the lane form spills but
+// keeps 64 cells in flight per SIMD against 8: it has the higher rate where work
+// abounds (64 fields of 28M cells in all: 2.25 s against 4.49; 50,000 fixed steps
+// 0.14 ms against 0.26), the wave-cooperative form the shorter chain where the
+// costliest cell is what is waited for (fields of 20,000 cells 28 ms against 105,
+// 100,000 cells 42 against 120, 1M cells 191 against 208; 4,096 reactors 7.1
+// against 27).  From 14 species on, the lane form's spills grow steeply (14, 15,
+// 16 and 18 species measured at 3-4 times the time of a wave-cooperative form
+// that has since become 2-3 times faster), so 13 is the default limit.
 // CHEM_LANE_MAX_SPECIES overrides the choice at load time (the lane form is
 // built for at most kMaxLaneSpecies species).
 constexpr int kLaneSpecies = 13;

@@ -219,7 +219,7 @@ struct Rate {
 // A wave here is bound by such latencies, not by issue (vector instructions
 // issued in 45 % of the cycles, 40 % in waits): with the same grouping of the
 // list and thermo loads and the falloff terms as one block, a substep of a lone
-// wave went from 85,000 to 70,000 cycles (16 species), and the 1M-cell field of
+// wave went from 84,800 to 64,200 cycles (16 species), and the 1M-cell field of
 // 32 species from 27.0 to 21.2 ms.
 struct Entry {
     double lnA, b, Ea;
