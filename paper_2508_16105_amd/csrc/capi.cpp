@@ -59,7 +59,7 @@ thread_local std::string g_last_error;
 int set_error(int code, const std::string& msg)
 {
     g_last_error = msg;
-    if (std::getenv("CHEM_LOG")) std::fprintf(stderr, "[chem] error %d: %s\n", code, msg.c_str());
+    if (code && std::getenv("CHEM_LOG")) std::fprintf(stderr, "[chem] error %d: %s\n", code, msg.c_str());
     return code;
 }
 

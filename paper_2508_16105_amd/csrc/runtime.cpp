@@ -1031,7 +1031,7 @@ int run_adjoint(chem_mechanism* m, int64_t ncell, const double* T0, const double
             again.erase(std::remove_if(again.begin(), again.end(),
                                        [&](int32_t c) { return st_h[c] != CHEM_CELL_NONFINITE; }),
                         again.end());
-            rc = CHEM_OK;
+            rc = set_error(CHEM_OK, "");     // the message of the first pass
         }
         if (!rc) rc = a.reduce(g_lnA, g_b, g_Ea, stats);
         if (rc && rc != CHEM_E_CELL_FAILED) return rc;
