@@ -452,10 +452,11 @@ struct Emitter {
                  "    const S r0 = chem_math::exp_poly(lnr0);\n"
                  "    const S Pr = r0 * Mc;\n"
                  "    const bool floored = !(Pr >= 1e-300);\n"
-                 // (the logarithm taken in every lane and dropped where floored: as a
-                 // branch it would be divergent control flow inside the step, see
-                 // ros_step_impl)
-                 "    const S lgPr = chem_math::lg(Pr);\n"
+                 // (a branch of the whole wave, with a select in it for the floored lanes:
+                 // one of each lane's own would be divergent control flow inside the
+                 // step, see ros_step_impl)
+                 "    S lgPr = S(-300.0);\n"
+                 "    if (__any(!floored)) lgPr = chem_math::lg(Pr);\n"
                  "    const S logPr = floored ? S(-300.0) : lgPr;\n";
             if (r.kind == RxnKind::Troe) {
                 o << "    const S e3 = chem_math::exp_neg(-T * " << lit(1.0 / r.T3) << ");\n"

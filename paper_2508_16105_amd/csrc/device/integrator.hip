@@ -242,7 +242,8 @@ struct StashLayout {
 // the stages (13 species, 124 against 112 us), so those unroll.
 //
 // A step has no divergent branch: what a rate does not need in some lane is
-// formed all the same and dropped by a select.  At the join of a divergent
+// formed all the same and dropped by a select (branches are of the whole wave,
+// on a scalar).  At the join of a divergent
 // branch the compiler may put copies of registers live across it before the
 // restore of the execution mask, so a lane that skipped the block goes on
 // without them.  It did so in the unrolled 13-species kernel around a falloff
