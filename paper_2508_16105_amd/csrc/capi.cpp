@@ -28,7 +28,7 @@ namespace {
 // cell's Jacobian and LU factors in one lane's registers); larger ones run
 // wave-cooperatively (16 lanes a cell).  At 13 species the lane form spills but
 // keeps 64 cells in flight per SIMD against 8: it has the higher rate where work
-// abounds (64 fields of 28M cells in all: 2.25 s against 4.49; 50,000 fixed steps
+// abounds (64 fields of 28M cells in all: 2.16 s against 4.49; 50,000 fixed steps
 // 0.14 ms against 0.26), the wave-cooperative form the shorter chain where the
 // costliest cell is what is waited for (fields of 20,000 cells 28 ms against 105,
 // 100,000 cells 42 against 120, 1M cells 191 against 208; 4,096 reactors 7.1
